@@ -20,15 +20,15 @@ constexpr int kAdjSB = 4;              // spectral adjoint: sources per pass ove
 constexpr int kAdjSBWide = 8;          // the same with 2-frame chunks and more than kAdjSB sources
 constexpr int kAdjSBOne = 16;          // the same with 1-frame chunks (more than kAdjSBWide sources)
 constexpr int kAdjBlocks = 512;        // spectral adjoint: work groups aimed at per launch
-constexpr int kAdjMinRows = 4;         // spectral adjoint: fewest rows per thread
-constexpr int kAdjMaxRows = 64;        // spectral adjoint: most rows per work group
+constexpr int kAdjMinRows = 4;         // spectral adjoint: fewest rows of the P grid per thread
+constexpr int kAdjMaxRows = 64;        // spectral adjoint: most rows of the P grid per work group
 constexpr int kAdjRB = 3;              // spectral adjoint: rows of a thread whose loads are issued together
 constexpr int kSumBins = 64;           // chunk-spectrum sums: bins of a work group
 constexpr int kSumParts = 4;           // chunk-spectrum sums: runs of chunks per bin (threads)
 constexpr int kSumBatch = 16;          // chunk-spectrum sums: loads of a run in flight together
-// spectral adjoint: column lanes of a work group (64, 128 or 256, a divisor of its
-// threads), the smallest that covers the P/2+1 columns
-__host__ __device__ inline int adj_lanes(int HP) { return HP <= 64 ? 64 : (HP <= 128 ? 128 : 256); }
+// values of a P x P spectrum in alias order (see starred_fft.hip): s^2 for each bin of the
+// Q x (Q/2+1) half plane
+__host__ __device__ inline long long alias_bins(int P, int Q) { return (long long)(P / Q) * P * (Q / 2 + 1); }
 
 // A 1-D transform length L = product of radices (4, 2, 3, 5) and the offset of
 // its twiddle table e^{-2 pi i m / L}, m < L.
@@ -45,7 +45,7 @@ struct ClassFft {
     int P, Q, F, n, o, K;
     FftLen fP, fQ;
     long long th_off;   // [F][P/2+1]   rows of the h window
-    long long hh_off;   // [P][P/2+1]   spectrum of the h window
+    long long hh_off;   // spectrum of the h window, alias order
     long long tab_off;  // [(1 + 2M) P] window and point-source factor tables
     float sscale;       // 1 / (s^2 Q^2)
     int cf_off;         // first entry of this class in the class-ordered frame list
@@ -53,10 +53,10 @@ struct ClassFft {
     int ngch;           // frame chunks of the frequency-domain adjoint
     int gfch;           // frames per chunk
     int ngch_cap;       // chunks the class's gp region holds (its smallest allowed chunks)
-    long long gp_off;   // [ngch][P][P/2+1] summed adjoint spectra of each chunk (total in chunk 0)
+    long long gp_off;   // [ngch] summed adjoint spectra of each chunk, alias order (total in chunk 0)
     long long hc_off;   // [F][F] the class's contribution to dL/dh (its window)
     int fused;          // frames of this class take the one-launch forward (spectra fit in LDS)
-    int arr;            // spectral adjoint: row representatives per work group (2s rows each)
+    int arr;            // spectral adjoint: rows of the Q grid per work group (s rows of the P grid each)
     int nrr;            // spectral adjoint: row ranges (per-frame partial slots)
     int direct;         // the class runs the direct algorithm (the FFT launches skip it)
 };
@@ -65,7 +65,7 @@ struct FrameFft {
     int cls;
     int pad;
     long long kern_off;  // packed K^2 kernels
-    long long s_off;     // [P][P/2+1] kernel spectrum S''
+    long long s_off;     // kernel spectrum S'', alias order
     long long t_off;     // [n][Q/2+1] row spectra (model / rho)
     long long r_off;     // [Q][Q/2+1] rho_hat
     long long t3_off;    // [P][P/2+1] scratch of the adjoint (and of the kernel transform)
@@ -110,7 +110,7 @@ struct FusedItem {
 struct AdjItem {
     int cls;
     int nf;                      // frames in the chunk
-    int y0, y1;                  // representatives [y0, y1) of the rows (y <= Q/2: rows = +-y mod Q)
+    int y0, y1;                  // rows [y0, y1) of the Q grid
     int P, Q;
     int pb;                      // row range index (the per-frame partial slot)
     int pad;
@@ -148,7 +148,7 @@ struct FftPlanDev {
     int n_aspec = 0;
     int adj_fc = kAdjFrames;   // frames per chunk of the current items
     int maxpb = 0;           // per-frame partial slots (largest nrr)
-    long long total_bins = 0;  // sum over classes of P (P/2 + 1)
+    long long total_bins = 0;  // sum over classes of alias_bins
     double *apart = nullptr; // [E][maxpb][1 + 3M]
     float2 *Gp = nullptr;
     float *hcls = nullptr;
@@ -200,7 +200,7 @@ hipError_t fft_adj_cols(hipStream_t st, const FftPlanDev &d);
 hipError_t fft_adj_rows(hipStream_t st, const FftPlanDev &d, float *g);
 hipError_t fft_resid_rows(hipStream_t st, const FftPlanDev &d, const float *resid);
 hipError_t fft_adjoint(hipStream_t st, const FftPlanDev &d, float *g);
-hipError_t fft_spec_adj(hipStream_t st, const FftPlanDev &d, int M);
+hipError_t fft_spec_adj(hipStream_t st, const FftPlanDev &d, int M, int s);
 hipError_t fft_adj_sums(hipStream_t st, const FftPlanDev &d, int M, double *fsum);
 struct FinalArgs;
 // dL/dh of the classes: the column inverse alone, and (one class whose window

@@ -425,6 +425,49 @@ __device__ __forceinline__ float2 half_get(const float2 *__restrict__ X, int P, 
     return v;
 }
 
+// Spectra that meet an alias fold (S'', the class's H and the summed adjoint spectra) are
+// held in alias order: [ky < Q][kx <= Q/2][b < s][a < s] is the bin K = (ky + aQ, kx + bQ)
+// of the full P x P plane. The s^2 values that fold onto one bin of the Q grid are then
+// s^2 consecutive values, read with wide loads once per fold, with no mirrored rows or
+// conjugations; the columns kx = 0 and Q/2 hold both members of their conjugate pairs
+// (2 P more values than the half plane for s = 2). alias_get reads any bin of the plane,
+// alias_put stores a bin of the half plane Kx <= P/2 at its one or two places.
+__device__ __forceinline__ int alias_idx(int Q, int s, int Ky, int Kx)
+{
+    const int a = Ky / Q, b = Kx / Q;
+    return (((Ky - a * Q) * (Q / 2 + 1) + (Kx - b * Q)) * s + b) * s + a;
+}
+
+__device__ __forceinline__ float2 alias_get(const float2 *__restrict__ X, int P, int Q, int Ky, int Kx)
+{
+    const bool lo = 2 * (Kx % Q) <= Q;
+    float2 v = X[alias_idx(Q, P / Q, lo ? Ky : (Ky == 0 ? 0 : P - Ky), lo ? Kx : P - Kx)];
+    v.y = lo ? v.y : -v.y;
+    return v;
+}
+
+__device__ __forceinline__ void alias_put(float2 *__restrict__ X, int P, int Q, int Ky, int Kx, float2 v)
+{
+    if (2 * (Kx % Q) <= Q) X[alias_idx(Q, P / Q, Ky, Kx)] = v;
+    const int mx = P - Kx;
+    if (Kx > 0 && 2 * Kx < P && 2 * (mx % Q) <= Q)
+        X[alias_idx(Q, P / Q, Ky == 0 ? 0 : P - Ky, mx)] = make_float2(v.x, -v.y);
+}
+
+// the S values (ky + aQ, kx + bQ), a < S, of one column alias: S consecutive values
+template <int S>
+__device__ __forceinline__ void alias_load(const float2 *__restrict__ X, int at, float2 (&v)[S])
+{
+    if constexpr (S == 2) {
+        const float4 q = *reinterpret_cast<const float4 *>(X + at);  // (at is even: 16-byte aligned)
+        v[0] = make_float2(q.x, q.y);
+        v[1] = make_float2(q.z, q.w);
+    } else {
+        #pragma unroll
+        for (int a = 0; a < S; ++a) v[a] = X[at + a];
+    }
+}
+
 // ---- pass A: rows of the h window of each class (real -> half spectrum) ----
 // Its launch carries extra work groups per class (when M > 0) that compute the
 // per-evaluation factor tables alongside: 16 for up to four sources,
@@ -463,7 +506,7 @@ struct OpHRows {
     }
 };
 
-// ---- pass B: columns -> H_hat[P][P/2+1] ----
+// ---- pass B: columns -> H_hat, alias order ----
 struct OpHCols {
     const float2 *Th;
     float2 *Hh;
@@ -478,8 +521,7 @@ struct OpHCols {
     }
     __device__ void store(const ClassFft &c, int, int kx, int ky, float2 v) const
     {
-        const int H = c.P / 2 + 1;
-        Hh[c.hh_off + (long long)ky * H + kx] = v;
+        alias_put(Hh + c.hh_off, c.P, c.Q, ky, kx, v);
     }
 };
 
@@ -531,8 +573,7 @@ struct OpKCols {
     }
     __device__ void store(const ClassFft &c, int i, int kx, int ky, float2 v) const
     {
-        const int H = c.P / 2 + 1;
-        S[fr[i].s_off + (long long)ky * H + kx] = cscale(v, c.sscale);
+        alias_put(S + fr[i].s_off, c.P, c.Q, ky, kx, cscale(v, c.sscale));
     }
 };
 
@@ -540,43 +581,22 @@ struct OpKCols {
 struct OpFwdCols {
     const FrameFft *fr;
     const float2 *S;
-    const float2 *Hh;
-    const float2 *tab;
-    const float *params;
-    int N, E, M, s;
+    int s;
     float2 *T;
-    const float2 *scene_spec;  // per-frame scene spectra (standalone operator) or NULL
+    const float2 *scene_spec;  // per-frame scene spectra [P][P/2+1]
     static constexpr bool col = true;
     static constexpr bool rowsum = false;
     static constexpr bool inverse = true;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fQ; }
-    // scene spectrum at K (any Kx in [0,P)): Gamma w(Ky) w(Kx) + H(K) + sum_k a g_y(Ky) g_x(Kx)
-    __device__ float2 scene_hat(const ClassFft &c, int i, int Ky, int Kx) const
-    {
-        const int P = c.P;
-        if (scene_spec) return half_get(scene_spec + fr[i].t3_off, P, Ky, Kx);
-        const float2 *t = tab + c.tab_off;
-        float2 v = half_get(Hh + c.hh_off, P, Ky, Kx);
-        const float G = params[(long long)N * N + i];
-        v = cadd(v, cscale(cmul(t[Ky], t[Kx]), G));
-        const float *a = params + (long long)N * N + E + (long long)i * M;
-        for (int k = 0; k < M; ++k) {
-            const float2 *tk = t + (long long)(1 + 4 * k) * P;  // [gx | gy | dgx | dgy]
-            v = cadd(v, cscale(cmul(tk[P + Ky], tk[Kx]), a[k]));
-        }
-        return v;
-    }
     __device__ float2 load(const ClassFft &c, int i, int kx, int ky) const
     {
         const FrameFft &f = fr[i];
         const int P = c.P, Q = c.Q;
-        const float2 *Si = S + f.s_off;
+        const float2 *Si = S + f.s_off + (ky * (Q / 2 + 1) + kx) * s * s;
         float2 acc = make_float2(0.f, 0.f);
         for (int al = 0; al < s; ++al)
-            for (int be = 0; be < s; ++be) {
-                const int Ky = ky + al * Q, Kx = kx + be * Q;
-                acc = cadd(acc, cmul(half_get(Si, P, Ky, Kx), scene_hat(c, i, Ky, Kx)));
-            }
+            for (int be = 0; be < s; ++be)
+                acc = cadd(acc, cmul(Si[be * s + al], half_get(scene_spec + f.t3_off, P, ky + al * Q, kx + be * Q)));
         return acc;
     }
     __device__ void store(const ClassFft &c, int i, int kx, int y, float2 v) const
@@ -618,12 +638,15 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_fwd(const SpecItem *__rest
         Kxs[a] = kx + a * Q;
     }
     #pragma unroll
-    for (int a = 0; a < S; ++a)
+    for (int b = 0; b < S; ++b) {
+        float2 ha[S];
+        alias_load<S>(Hh + c.hh_off, (bin * S + b) * S, ha);
         #pragma unroll
-        for (int b = 0; b < S; ++b) {
-            hv[a * S + b] = half_get(Hh + c.hh_off, P, Kys[a], Kxs[b]);
+        for (int a = 0; a < S; ++a) {
+            hv[a * S + b] = ha[a];
             wv[a * S + b] = cmul(t[Kys[a]], t[Kxs[b]]);
         }
+    }
     constexpr int MR = MS > 0 ? MS : 1;
     float2 rk[S * S][MR];
     if (MS > 0) {
@@ -656,9 +679,12 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_fwd(const SpecItem *__rest
                 #pragma unroll
                 for (int k = 0; k < MR; ++k) av[u][k] = (MS > 0 && k < M) ? ai[k] : 0.f;
                 #pragma unroll
-                for (int a = 0; a < S; ++a)
+                for (int b = 0; b < S; ++b) {
+                    float2 sa[S];
+                    alias_load<S>(Sp + fi.s_off, (bin * S + b) * S, sa);
                     #pragma unroll
-                    for (int b = 0; b < S; ++b) sv[u][a * S + b] = half_get(Sp + fi.s_off, P, Kys[a], Kxs[b]);
+                    for (int a = 0; a < S; ++a) sv[u][a * S + b] = sa[a];
+                }
             }
         }
         if (MS > 0) {
@@ -779,8 +805,8 @@ struct OpAdjCols {
     __device__ float2 load(const ClassFft &c, int i, int Kx, int Ky) const
     {
         const FrameFft &f = fr[i];
-        const int P = c.P, Q = c.Q, HP = P / 2 + 1;
-        const float2 sv = S[f.s_off + (long long)Ky * HP + Kx];
+        const int P = c.P, Q = c.Q;
+        const float2 sv = alias_get(S + f.s_off, P, Q, Ky, Kx);
         const int ky = Ky % Q, kx = Kx % Q;
         const float2 rv = half_get(Rh + f.r_off, Q, ky, kx);
         return cmulc(rv, sv);
@@ -1071,33 +1097,22 @@ __global__ __launch_bounds__(kFusedThreads) void k_frame_fwd(const FusedItem *__
     constexpr int MR = MS > 0 ? MS : 1;
     if (colw) {
         const int kx = lane;
-        const int HP = P / 2 + 1;
         float2 wxG[S], px[S][MR];
-        // half-spectrum access of the column aliases Kx_b (Hermitian fold for Kx >= P/2+1)
-        bool lob[S];
-        int rxb[S];
         #pragma unroll
         for (int b = 0; b < S; ++b) {
             const int Kx = kx + b * Q;
-            lob[b] = Kx < HP;
-            rxb[b] = lob[b] ? Kx : P - Kx;
             wxG[b] = cscale(t[Kx], G);
             #pragma unroll
             for (int k = 0; k < MR; ++k)
                 px[b][k] = (MS > 0 && k < M) ? cscale(t[(1 + 4 * k) * P + Kx], ai[k]) : make_float2(0.f, 0.f);
         }
-        // the s^2 alias terms of the model spectrum at (kx, ky), from the loaded bins
+        // the s^2 alias terms of the model spectrum at (kx, ky): consecutive in alias order
         auto load_row = [&](int ky, float2 (&hv)[S][S], float2 (&sv)[S][S]) {
+            const int at = (ky * HQ + kx) * S * S;
             #pragma unroll
-            for (int a = 0; a < S; ++a) {
-                const int Ky = ky + a * Q;
-                const int rlo = Ky * HP, rhi = (Ky == 0 ? 0 : P - Ky) * HP;
-                #pragma unroll
-                for (int b = 0; b < S; ++b) {
-                    const int hidx = (lob[b] ? rlo : rhi) + rxb[b];
-                    hv[a][b] = Hc[hidx];
-                    sv[a][b] = Si[hidx];
-                }
+            for (int b = 0; b < S; ++b) {
+                alias_load<S>(Hc, at + b * S, hv[b]);
+                alias_load<S>(Si, at + b * S, sv[b]);
             }
         };
         auto row_sum = [&](int ky, const float2 (&hv)[S][S], const float2 (&sv)[S][S]) {
@@ -1113,11 +1128,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_frame_fwd(const FusedItem *__
                 #pragma unroll
                 for (int b = 0; b < S; ++b) {
                     const int Kx = kx + b * Q;
-                    float2 h = hv[a][b], sk = sv[a][b];
-                    if (!lob[b]) {
-                        h.y = -h.y;
-                        sk.y = -sk.y;
-                    }
+                    const float2 h = hv[b][a], sk = sv[b][a];
                     float2 F = cadd(h, cmul(wy, wxG[b]));
                     if (MS > 0) {
                         #pragma unroll
@@ -1338,16 +1349,18 @@ __device__ void tables_part(const ClassFft &c, const float2 *__restrict__ tw, co
 // window indicator (dGamma_i), r_k (da_ik) and r_k (X - c_k)/sigma^2 (dc_k, x and y).
 // Those spectra are products ty(Ky) tx(Kx) of 1-D tables, so each dot product is
 //   sum_Kx wgt(Kx) Re( conj(tx(Kx)) V_ty(Kx) ),  V_ty(Kx) = sum_Ky G(Ky, Kx) conj(ty(Ky)),
-// with one column sum V per y-table (window, gy_k, dgy_k). A block takes a chunk of
-// FC frames and the rows of a range of representatives y (rows congruent to y or
-// -y modulo Q, see below), SB sources per pass (one when M <= 1; four, or eight with
-// 2-frame chunks and more than four sources, otherwise); a thread owns columns Kx (lanes)
-// and every RG-th row of the range, accumulates V over its rows, folds it with the
-// x-tables, and the block reduces the dot products once per group of SB sources through
-// LDS. Each pass reads the chunk's spectra again, so fewer, wider passes save reads.
-// The per-block partials are summed per frame (and the chunk spectra over chunks)
-// by k_adj_sums.
-template <int FC, int SB>
+// with one column sum V per y-table (window, gy_k, dgy_k). In alias order the spectra of
+// the s bins (ky + aQ, kx + bQ), a < s, are consecutive and share one value of rho_hat, so
+// a thread owns a column alias (kx, b) and walks the rows ky of the block's range (every
+// RG-th of them): per row and frame one wide load of S'' and one of rho_hat. The sum over
+// the full spectrum is the sum over all (ky, a, b) and kx in [0, Q/2], with weight 2 off
+// the columns kx = 0 and Q/2. A block takes a chunk of FC frames and a range of rows, SB
+// sources per pass (one when M <= 1; four, or eight with 2-frame chunks and more than four
+// sources, otherwise), folds V with the x-tables and reduces the dot products once per
+// group of SB sources through LDS. Each pass reads the chunk's spectra again, so fewer,
+// wider passes save reads. The per-block partials are summed per frame (and the chunk
+// spectra over chunks) by k_adj_sums.
+template <int S, int FC, int SB>
 __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restrict__ items,
                                                           const float2 *__restrict__ Sp,
                                                           const float2 *__restrict__ Rh,
@@ -1355,8 +1368,8 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restr
                                                           float2 *__restrict__ Gp, double *__restrict__ part)
 {
     constexpr int NY = 1 + 2 * SB, NQ = 1 + 3 * SB;
-    // rows of a thread whose loads are issued together: about 12-16 loads in flight
-    constexpr int RB = FC >= 8 ? 1 : (FC >= 4 ? 2 : kAdjRB);
+    // rows of a thread whose loads are issued together: about 8-16 wide loads in flight
+    constexpr int RB = FC >= 4 ? (S == 1 && FC == 4 ? 2 : 1) : (FC == 2 ? 2 : kAdjRB);
     static_assert(FC <= kAdjMaxFrames, "chunk larger than the work items hold");
     constexpr int kRow = kFftThreads + 8;  // padded LDS rows of per-thread partials
     // rows of per-thread partials reduced per pass (LDS kept small for occupancy)
@@ -1364,102 +1377,76 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restr
     static_assert(FC * NQ <= 2 * 32, "two reduction passes of 32 quantities");
     __shared__ float red[NRED * kRow];
     const AdjItem &it = items[blockIdx.x];
-    const int P = it.P, Q = it.Q, HP = P / 2 + 1;
-    const int y0 = it.y0, y1 = it.y1, pb = it.pb;
-    // The block's rows: for each representative y in [y0, y1) (0 <= y <= Q/2) the rows
-    // Ky = y + aQ and Ky = (Q - y) + aQ, a < s, i.e. every row whose rho_hat row is y or
-    // its mirror Q - y; local row i: representative i / 2s, a = (i % 2s) / 2, mirrored
-    // when i is odd (no mirrored rows for y = 0 and y = Q/2, which are their own
-    // mirrors). So the s^2 reads of each rho_hat value fall in one block.
-    const int S2 = 2 * (P / Q);
-    const int nloc = S2 * (y1 - y0);
-    auto row_of = [&](int li, bool &valid) {
-        const int y = y0 + li / S2, j = li % S2;
-        const bool mir = j & 1;
-        valid = !(mir && (y == 0 || 2 * y == Q));
-        return (mir && valid ? Q - y : y) + (j >> 1) * Q;
-    };
-    // lanes over columns, row groups over rows
-    const int CX = adj_lanes(HP), RG = kFftThreads / CX;
+    const int P = it.P, Q = it.Q, HQ = Q / 2 + 1, C = S * HQ;
+    const int y0 = it.y0, y1 = it.y1, pb = it.pb, nrow = y1 - y0;
+    // column aliases packed over the threads, row groups over the rest
+    const int CX = min(C, kFftThreads), RG = kFftThreads / CX;
     const int lane = threadIdx.x % CX, rg = threadIdx.x / CX;
     const float2 *t = tab + it.tab_off;
     const int Q3 = 1 + 3 * M;
     float2 *gout = Gp + it.gout;
-    const int HQ = Q / 2 + 1;
-    __shared__ float2 tys[NY * kAdjMaxRows];  // y-tables of the block's rows
+    __shared__ float2 tys[NY * kAdjMaxRows];  // y-tables of the block's rows, [u][row][a]
     for (int k0 = 0; k0 < max(M, 1); k0 += SB) {
         const int nk = min(SB, M - k0);  // sources of this group (may be 0 when M = 0)
         const bool first = (k0 == 0);
         // y-tables of this group for the block's rows: window, gy_k, dgy_k
-        for (int e = threadIdx.x; e < NY * nloc; e += kFftThreads) {
-            const int u = e / nloc, r = e - u * nloc;
-            bool valid;
-            const int Ky = row_of(r, valid);
+        for (int e = threadIdx.x; e < NY * nrow * S; e += kFftThreads) {
+            const int u = e / (nrow * S), ra = e - u * (nrow * S);
+            const int Ky = y0 + ra / S + (ra % S) * Q;
             float2 v = make_float2(0.f, 0.f);
-            if (valid) {
-                if (u == 0) v = t[Ky];
-                else if (u <= SB) { if (u - 1 < nk) v = t[(1 + 4 * (k0 + u - 1)) * P + P + Ky]; }
-                else if (u - 1 - SB < nk) v = t[(1 + 4 * (k0 + u - 1 - SB)) * P + 3 * P + Ky];
-            }
-            tys[u * kAdjMaxRows + r] = v;
+            if (u == 0) v = t[Ky];
+            else if (u <= SB) { if (u - 1 < nk) v = t[(1 + 4 * (k0 + u - 1)) * P + P + Ky]; }
+            else if (u - 1 - SB < nk) v = t[(1 + 4 * (k0 + u - 1 - SB)) * P + 3 * P + Ky];
+            tys[u * kAdjMaxRows + ra] = v;
         }
         __syncthreads();
         // spectra of the chunk's frames (a slot past the chunk's frames reads its first
         // frame again; its product is discarded)
         int fid[FC];
-        long long soff[FC], roff[FC];
+        const float2 *sp[FC], *rp[FC];
         #pragma unroll
         for (int f = 0; f < FC; ++f) {
             fid[f] = it.fid[f];
-            soff[f] = it.soff[f];
-            roff[f] = it.roff[f];
+            sp[f] = Sp + it.soff[f];
+            rp[f] = Rh + it.roff[f];
         }
         float dot[FC][NQ];
         #pragma unroll
         for (int f = 0; f < FC; ++f)
             #pragma unroll
             for (int q = 0; q < NQ; ++q) dot[f][q] = 0.f;
-        for (int Kx = lane; Kx < HP; Kx += CX) {
+        for (int c = lane; c < C && rg < RG; c += CX) {
+            const int kx = c / S, b = c - kx * S;
             float2 V[FC][NY];
             #pragma unroll
             for (int f = 0; f < FC; ++f)
                 #pragma unroll
                 for (int u = 0; u < NY; ++u) V[f][u] = make_float2(0.f, 0.f);
-            // rho_hat is indexed by K mod Q (Kx < P/2 + 1 <= 2Q, so one subtraction)
-            const int kxq = Kx >= Q ? Kx - Q : Kx;
-            const bool lo = kxq < HQ;
-            const int rx = lo ? kxq : Q - kxq;
-            const float cj = lo ? 1.f : -1.f;
-            // RB rows of this thread at a time: every load of the batch is issued
-            // before the first is used (a row group is whole waves, so the row tests are uniform)
-            for (int ib = rg; ib < nloc; ib += RB * RG) {
-                float2 sv[RB][FC], rv[RB][FC];
-                int kyb[RB];
-                bool okb[RB];
+            // RB rows of this thread at a time: every load of the batch is issued before
+            // the first is used (past the range: the batch's first row again, discarded)
+            for (int ib = rg; ib < nrow; ib += RB * RG) {
+                float2 sv[RB][FC][S], rv[RB][FC];
                 #pragma unroll
-                for (int b = 0; b < RB; ++b) {
-                    const int li = ib + b * RG;
-                    bool valid;
-                    const int Ky = row_of(li < nloc ? li : ib, valid);  // (past the range: a row loaded again)
-                    okb[b] = valid && li < nloc;  // (an invalid slot still names a row in range)
-                    kyb[b] = Ky;
-                    const int ryq = Ky % Q;
-                    const long long bin = (long long)Ky * HP + Kx;
-                    const int ridx = (lo ? ryq : (ryq == 0 ? 0 : Q - ryq)) * HQ + rx;
+                for (int q = 0; q < RB; ++q) {
+                    const int li = ib + q * RG;
+                    const int ky = y0 + (li < nrow ? li : ib);
                     #pragma unroll
                     for (int f = 0; f < FC; ++f) {
-                        sv[b][f] = Sp[soff[f] + bin];
-                        rv[b][f] = Rh[roff[f] + ridx];
+                        alias_load<S>(sp[f], (ky * C + c) * S, sv[q][f]);
+                        rv[q][f] = rp[f][ky * HQ + kx];
                     }
                 }
                 #pragma unroll
-                for (int b = 0; b < RB; ++b) {
-                    if (!okb[b]) continue;
-                    const int Ky = kyb[b], li = ib + b * RG;
-                    float2 ty[NY];
+                for (int q = 0; q < RB; ++q) {
+                    const int li = ib + q * RG;
+                    if (li >= nrow) continue;
+                    float2 ty[S][NY], gsum[S];
                     #pragma unroll
-                    for (int u = 0; u < NY; ++u) ty[u] = tys[u * kAdjMaxRows + li];
-                    float2 gsum = make_float2(0.f, 0.f);
+                    for (int a = 0; a < S; ++a) {
+                        gsum[a] = make_float2(0.f, 0.f);
+                        #pragma unroll
+                        for (int u = 0; u < NY; ++u) ty[a][u] = tys[u * kAdjMaxRows + li * S + a];
+                    }
                     #pragma unroll
                     for (int f = 0; f < FC; ++f) {
                         // a missing frame's product is replaced by zero with a select (a branch
@@ -1467,18 +1454,25 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restr
                         // a product with zero would let a non-finite value through)
                         const bool on = f < it.nf;
                         const float2 z = make_float2(0.f, 0.f);
-                        float2 r = on ? rv[b][f] : z;
-                        r.y *= cj;
-                        const float2 G = cmulc(r, on ? sv[b][f] : z);
-                        gsum = cadd(gsum, G);
+                        const float2 r = on ? rv[q][f] : z;
                         #pragma unroll
-                        for (int u = 0; u < NY; ++u) V[f][u] = cadd(V[f][u], cmulc(G, ty[u]));
+                        for (int a = 0; a < S; ++a) {
+                            const float2 G = cmulc(r, on ? sv[q][f][a] : z);
+                            gsum[a] = cadd(gsum[a], G);
+                            #pragma unroll
+                            for (int u = 0; u < NY; ++u) V[f][u] = cadd(V[f][u], cmulc(G, ty[a][u]));
+                        }
                     }
-                    if (first) gout[(long long)Ky * HP + Kx] = gsum;
+                    if (first) {
+                        float2 *go = gout + ((y0 + li) * C + c) * S;
+                        #pragma unroll
+                        for (int a = 0; a < S; ++a) go[a] = gsum[a];
+                    }
                 }
             }
             // fold with the x-tables of this column
-            const float wgt = (Kx == 0 || 2 * Kx == P) ? 1.f : 2.f;
+            const int Kx = kx + b * Q;
+            const float wgt = (kx == 0 || 2 * kx == Q) ? 1.f : 2.f;
             float2 tx[1 + 2 * SB];
             tx[0] = t[Kx];
             #pragma unroll
@@ -1554,7 +1548,7 @@ __global__ __launch_bounds__(256) void k_adj_sums(const ClassFft *__restrict__ c
         for (int ci = 0; ci < ncls; ++ci) {
             const ClassFft &c = classes[ci];
             if (c.direct) continue;  // classes on the direct algorithm have no spectra here
-            const int nb = c.P * (c.P / 2 + 1);
+            const int nb = (int)alias_bins(c.P, c.Q);
             if (g < nb) {
                 gp = Gp + c.gp_off + g;
                 ngch = c.ngch;
@@ -1605,7 +1599,7 @@ struct OpGCols {
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
     __device__ float2 load(const ClassFft &c, int, int Kx, int Ky) const
     {
-        return Gp[c.gp_off + (long long)Ky * (c.P / 2 + 1) + Kx];  // chunk sum, in the first slot
+        return alias_get(Gp + c.gp_off, c.P, c.Q, Ky, Kx);  // chunk sum, in the first slot
     }
     __device__ void store(const ClassFft &c, int, int Kx, int y, float2 v) const
     {
@@ -1760,7 +1754,7 @@ hipError_t fft_scene_model(hipStream_t st, const FftPlanDev &d, const float *sce
     e = run_lines(st, d.scols, d.classes, d.tw, OpSceneCols{d.frames, d.T3});
     if (e != hipSuccess) return e;
     e = run_lines(st, d.fcols, d.classes, d.tw,
-                  OpFwdCols{d.frames, d.S, d.Hh, d.tab, nullptr, 0, 0, 0, s, d.T, d.T3});
+                  OpFwdCols{d.frames, d.S, s, d.T, d.T3});
     if (e != hipSuccess) return e;
     if (d.frows.n_items > 0) {
         hipLaunchKernelGGL(k_fwd_rows, dim3(d.frows.n_items), dim3(kFftThreads), d.frows.lds_bytes, st,
@@ -1778,7 +1772,7 @@ hipError_t fft_xf_forward(hipStream_t st, const FftPlanDev &d, const float *scen
     if (e != hipSuccess) return e;
     e = run_lines(st, d.scols_x, d.classes, d.tw, OpSceneCols{d.frames, d.T3});
     if (e != hipSuccess) return e;
-    e = run_lines(st, d.fcols_x, d.classes, d.tw, OpFwdCols{d.frames, d.S, d.Hh, d.tab, nullptr, 0, 0, 0, s, d.T, d.T3});
+    e = run_lines(st, d.fcols_x, d.classes, d.tw, OpFwdCols{d.frames, d.S, s, d.T, d.T3});
     if (e != hipSuccess || d.frows_x.n_items <= 0) return e;
     hipLaunchKernelGGL(k_fwd_rows, dim3(d.frows_x.n_items), dim3(kFftThreads), d.frows_x.lds_bytes, st,
                        d.frows_x.items, d.classes, d.frames, d.tw, d.T, data, invvar, d.T2, nullptr, part_chi);
@@ -1859,12 +1853,12 @@ hipError_t fft_adj_rows(hipStream_t st, const FftPlanDev &d, float *g)
     return run_lines(st, d.arows, d.classes, d.tw, OpAdjRows{d.frames, d.T3, g, d.gpart});
 }
 
-hipError_t fft_spec_adj(hipStream_t st, const FftPlanDev &d, int M)
+template <int S>
+static hipError_t spec_adj(hipStream_t st, const FftPlanDev &d, int M)
 {
-    if (d.n_aspec == 0) return hipSuccess;
     const dim3 g(d.n_aspec), b(kFftThreads);
-#define SPEC_ADJ(FC, SB)                                                                               \
-    hipLaunchKernelGGL((k_spec_adj<FC, SB>), g, b, 0, st, d.aspec, d.S, d.Rh, d.tab, M, d.maxpb, d.Gp, \
+#define SPEC_ADJ(FC, SB)                                                                                  \
+    hipLaunchKernelGGL((k_spec_adj<S, FC, SB>), g, b, 0, st, d.aspec, d.S, d.Rh, d.tab, M, d.maxpb, d.Gp, \
                        d.apart)
     if (M <= 1) {
         switch (d.adj_fc) {
@@ -1888,6 +1882,12 @@ hipError_t fft_spec_adj(hipStream_t st, const FftPlanDev &d, int M)
     }
 #undef SPEC_ADJ
     return hipGetLastError();
+}
+
+hipError_t fft_spec_adj(hipStream_t st, const FftPlanDev &d, int M, int s)
+{
+    if (d.n_aspec == 0) return hipSuccess;
+    return s == 1 ? spec_adj<1>(st, d, M) : (s == 2 ? spec_adj<2>(st, d, M) : spec_adj<3>(st, d, M));
 }
 
 hipError_t fft_adj_sums(hipStream_t st, const FftPlanDev &d, int M, double *fsum)

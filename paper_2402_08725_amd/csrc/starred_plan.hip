@@ -592,7 +592,7 @@ static int build_fft(starred_plan *p)
         c.th_off = th;
         th += (long long)c.F * HP;
         c.hh_off = hh;
-        hh += (long long)c.P * HP;
+        hh += alias_bins(c.P, c.Q);
         c.tab_off = tb;
         tb += (long long)(1 + 4 * M) * c.P;
     }
@@ -630,7 +630,7 @@ static int build_fft(starred_plan *p)
         f.fine_off = p->fr[i].fine_off;
         const long long HP = c.P / 2 + 1, HQ = c.Q / 2 + 1;
         f.s_off = so;
-        so += (long long)c.P * HP;
+        so += alias_bins(c.P, c.Q);
         f.t_off = to;
         to += (long long)c.n * HQ;
         f.r_off = ro;
@@ -648,7 +648,7 @@ static int build_fft(starred_plan *p)
         cl.ngch = (cl.ncf + kAdjFrames - 1) / kAdjFrames;
         cl.ngch_cap = (cl.ncf + min_fc - 1) / min_fc;
         cl.gp_off = gp;
-        gp += (long long)cl.ngch_cap * cl.P * (cl.P / 2 + 1);
+        gp += cl.ngch_cap * alias_bins(cl.P, cl.Q);
         cl.hc_off = hc;
         hc += (long long)cl.F * cl.F;
     }
@@ -792,18 +792,16 @@ static int build_fft_lists(starred_plan *p)
             ClassFft &cl = p->cls[c];
             cl.arr = cl.nrr = 0;
             if (is_direct(c)) continue;
-            const int HP = cl.P / 2 + 1, nbins = cl.P * HP;
-            const int CX = adj_lanes(HP), RG = kFftThreads / CX;
+            const long long nbins = alias_bins(cl.P, cl.Q);
+            const int S = cl.P / cl.Q, C = S * (cl.Q / 2 + 1);
+            const int RG = kFftThreads / std::min(C, kFftThreads);
             const int want = std::max(1, (p->adj_blocks + nchunks - 1) / std::max(1, nchunks));
-            // a block takes the 2s rows of each of its representatives y <= Q/2 (the rows
-            // congruent to y or -y modulo Q): at least kAdjMinRows rows per thread, at
-            // most kAdjMaxRows rows
-            const int S2 = 2 * (cl.P / cl.Q), nrep = cl.Q / 2 + 1;
+            // a block takes rows of the Q grid, s rows of the P grid each: at least kAdjMinRows
+            // of those per thread, at most kAdjMaxRows per block
             const int rows = std::max(kAdjMinRows * RG, (cl.P + want - 1) / want);
-            int arr = std::max(1, (rows + S2 - 1) / S2);
-            arr = std::min(arr, kAdjMaxRows / S2);
+            const int arr = std::min((rows + S - 1) / S, kAdjMaxRows / S);
             cl.arr = arr;
-            cl.nrr = (nrep + arr - 1) / arr;
+            cl.nrr = (cl.Q + arr - 1) / arr;
             maxpb = std::max(maxpb, cl.nrr);
             for (int f0 = 0; f0 < cl.ncf; f0 += fc)
                 for (int r = 0; r < cl.nrr; ++r) {
@@ -811,7 +809,7 @@ static int build_fft_lists(starred_plan *p)
                     it.cls = c;
                     it.nf = std::min(fc, cl.ncf - f0);
                     it.y0 = r * arr;
-                    it.y1 = std::min(nrep, it.y0 + arr);
+                    it.y1 = std::min(cl.Q, it.y0 + arr);
                     it.P = cl.P;
                     it.Q = cl.Q;
                     it.pb = r;
@@ -824,7 +822,7 @@ static int build_fft_lists(starred_plan *p)
                         it.roff[f] = fi >= 0 ? p->ffr[fi].r_off : it.roff[0];
                     }
                     it.tab_off = cl.tab_off;
-                    it.gout = cl.gp_off + (long long)(f0 / cl.gfch) * nbins;
+                    it.gout = cl.gp_off + (f0 / cl.gfch) * nbins;
                     sp.push_back(it);
                 }
         }
@@ -835,7 +833,7 @@ static int build_fft_lists(starred_plan *p)
         d.maxpb = maxpb;
         d.total_bins = 0;
         for (int c = 0; c < (int)p->cls.size(); ++c)
-            if (!is_direct(c)) d.total_bins += (long long)p->cls[c].P * (p->cls[c].P / 2 + 1);
+            if (!is_direct(c)) d.total_bins += alias_bins(p->cls[c].P, p->cls[c].Q);
         if ((rc = p->alloc_list(&d.aspec, std::max<size_t>(1, sp.size())))) return rc;
         if ((rc = p->alloc_list(&d.apart, (size_t)E * maxpb * (1 + 3 * M) + 1))) return rc;
         if (!sp.empty()) HIP_TRY(hipMemcpy(d.aspec, sp.data(), sizeof(AdjItem) * sp.size(), hipMemcpyHostToDevice));
@@ -1574,7 +1572,7 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
             p->prof_stop(STARRED_STAGE_FFT_RCOLS, e1);
             if (split) HIP_TRY(hipStreamWaitEvent(p->st, p->ev_join3, 0));
             e1 = p->prof_start();
-            HIP_TRY(fft_spec_adj(p->st, p->fd, p->M));
+            HIP_TRY(fft_spec_adj(p->st, p->fd, p->M, p->s));
             p->prof_stop(STARRED_STAGE_FFT_ACOLS, e1);
             if (int rc = prior_flush()) return rc;
             if (late_adj) {
@@ -2497,7 +2495,7 @@ int starred_time_stage(starred_plan *p, const float *params, int32_t stage, int3
             return STARRED_OK;
         case STARRED_STAGE_FFT_ACOLS:
             if (!fft) break;
-            HIP_TRY(fft_spec_adj(p->st, p->fd, p->M));
+            HIP_TRY(fft_spec_adj(p->st, p->fd, p->M, p->s));
             return STARRED_OK;
         case STARRED_STAGE_FFT_FSUM:
             if (!fft) break;
