@@ -271,9 +271,8 @@ int starred_conv_algo(const starred_plan *plan);
 /* Shape classes of a deconvolution plan: the frames that share a (data side,
  * kernel side) pair. For each, the convolution algorithm it runs and, on the FFT
  * algorithm, the transform lengths P (fine grid) and Q = P/s (data grid) and
- * whether its forward is the one-launch form (fused = 1 with two LDS planes, 2 with
- * one plane transformed in place, for frames whose two planes do not fit) or the
- * batched line passes (0). starred_num_classes returns the count (>= 0) or a negative status;
+ * whether its forward is the one-launch form (fused = 1 for frames of which two would
+ * fit in LDS, 2 for those that fill it) or the batched line passes (0). starred_num_classes returns the count (>= 0) or a negative status;
  * starred_get_class_info fills *out for class c in [0, count). */
 typedef struct {
     int32_t n, K, n_frames;

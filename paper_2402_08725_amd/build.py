@@ -10,7 +10,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libstarred.so")
-SOURCES = ["starred_kernels.hip", "starred_fft.hip", "starred_psf.hip", "starred_noise.hip", "starred_opt.hip", "starred_starlet.hip", "starred_static.hip", "starred_lbfgsb.hip", "starred_plan.hip"]
+SOURCES = ["starred_fft.hip", "starred_frame_s2.hip", "starred_frame_s3.hip", "starred_frame_s1.hip",
+           "starred_kernels.hip", "starred_psf.hip", "starred_noise.hip", "starred_opt.hip", "starred_starlet.hip", "starred_static.hip", "starred_lbfgsb.hip", "starred_plan.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -19,7 +20,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-function"]
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every source to an object, then link the shared library."""
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)

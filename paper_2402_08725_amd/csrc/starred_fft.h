@@ -10,10 +10,9 @@ namespace starred {
 
 constexpr int kFftThreads = 256;
 constexpr int kFftTargetElems = 2048;  // complex elements per work group and buffer
-constexpr int kFusedThreads = 1024;     // one-launch forward: threads per frame
-constexpr size_t kFusedLdsMax = 150 * 1024;  // one-launch forward: LDS of its two Q x (Q+1) planes
+constexpr int kFusedThreads = 1024;     // one-launch forward: threads of a work group
+constexpr size_t kFusedLdsMax = 150 * 1024;  // one-launch forward: LDS of a work group
 constexpr int kFwdFrames = 4;          // spectral product: frames whose loads are issued together
-constexpr int kProdPairQ = 128;        // one-launch forward: columns of at least this length load two rows at once
 constexpr int kAdjFrames = 2;          // spectral adjoint: frames of a work group (a chunk), default
 constexpr int kAdjMaxFrames = 8;       // spectral adjoint: most frames of a chunk
 constexpr int kAdjSB = 4;              // spectral adjoint: sources per pass over the rows (M > 1)
@@ -89,19 +88,68 @@ struct SpecItem {
     int bin0;
 };
 
-// A work group of the one-launch forward: its frame with the offsets it reads,
-// resolved on the host (the class record itself is only needed for the
-// transforms' factor tables, later).
-struct FusedItem {
-    int frame, cls;
-    int P, Q, n;          // sizes
-    int inplace;          // one LDS plane transformed in place (else two planes)
-    long long tw_off;     // the Q-point twiddles
-    long long s_off;      // kernel spectrum S''
-    long long data_off;   // data and inverse variances
-    long long r_off;      // rho_hat (output)
-    long long tab_off;    // the class's factor tables
-    long long hh_off;     // the class's spectrum of h
+// The transform lengths of the one-launch forward (starred_frame.h): Q = RA RB, and the
+// frames NF that a work group takes of a class when frames outnumber the compute units
+// (X(Q, RA, RB, NF)): every even 5-smooth length from 18 to 180 but 162, which has no two
+// factors up to 16. RA is at least 8, so that the residual's reads come in runs of 32 bytes
+// or more. Two frames of 120 or more would need more registers than 1024 threads have (128
+// is the exception), or more LDS than there is.
+#define STARRED_FRAME_LENGTHS(X) \
+    X(18, 9, 2, 4)               \
+    X(20, 10, 2, 4)              \
+    X(24, 12, 2, 4)              \
+    X(30, 10, 3, 4)              \
+    X(32, 16, 2, 4)              \
+    X(36, 12, 3, 4)              \
+    X(40, 8, 5, 4)               \
+    X(48, 16, 3, 4)              \
+    X(50, 10, 5, 4)              \
+    X(54, 9, 6, 4)               \
+    X(60, 12, 5, 4)              \
+    X(64, 16, 4, 4)              \
+    X(72, 12, 6, 4)              \
+    X(80, 16, 5, 2)              \
+    X(90, 10, 9, 2)              \
+    X(96, 16, 6, 2)              \
+    X(100, 10, 10, 2)            \
+    X(108, 12, 9, 2)             \
+    X(120, 12, 10, 1)            \
+    X(128, 16, 8, 2)             \
+    X(144, 16, 9, 1)             \
+    X(150, 15, 10, 1)            \
+    X(160, 16, 10, 1)            \
+    X(180, 15, 12, 1)
+constexpr int kFrameMaxQ = 180;
+
+// frames that a work group may take of a class with transform length Q (0: no body);
+// several of them only for s = 2 (compile time)
+inline int frame_body_frames(int Q, int s)
+{
+#define STARRED_FRAME_NF(QQ, RA, RB, NF) \
+    if (Q == QQ) return s == 2 ? NF : 1;
+    STARRED_FRAME_LENGTHS(STARRED_FRAME_NF)
+#undef STARRED_FRAME_NF
+    return 0;
+}
+
+// sources whose tables a work group holds: the bodies take 1, 4 or (a loop) M of them
+__host__ __device__ constexpr int frame_sources(int M) { return M <= 1 ? 1 : (M <= 4 ? 4 : M); }
+
+// bytes of LDS of a work group with `per` frames: their planes of Q/2+1 lines of Q+1
+// values, the Q twiddles and the tables of P values (the window's, two per source)
+inline size_t frame_lds_bytes(int Q, int P, int M, int per)
+{
+    return ((size_t)per * (Q / 2 + 1) * (Q + 1) + Q + (size_t)(1 + 2 * frame_sources(M)) * P) * 8;
+}
+
+// A work group of the one-launch forward: up to `per` frames of a class.
+constexpr int kFrameMax = 4;
+struct FrameItem {
+    int nf, per;  // frames, and frames the body holds
+    int Q, n;
+    long long tw_off, tab_off, hh_off;
+    int frame[kFrameMax], chi[kFrameMax];  // frame indices and their chi-square slots
+    long long s_off[kFrameMax], data_off[kFrameMax], r_off[kFrameMax];
 };
 
 // A work group of the frequency-domain adjoint: a chunk of frames and a range of
@@ -153,13 +201,14 @@ struct FftPlanDev {
     float2 *Gp = nullptr;
     float *hcls = nullptr;
     LinePass gcols, grows;
-    // loss+gradient forward: frames of fused classes in one launch (a work group
-    // per frame); the line passes below cover the remaining frames
+    // loss+gradient forward: frames of fused classes in one launch; the line passes
+    // below cover the remaining frames
     SpecItem *spec_lg = nullptr;
     int n_spec_lg = 0;
-    FusedItem *fused = nullptr;
-    int n_fused = 0;
-    size_t fused_lds = 0;
+    FrameItem *frame_items = nullptr;
+    int n_frame_items = 0;
+    int n_fused = 0;  // frames they cover
+    size_t frame_lds = 0;
     LinePass fcols_lg, frows_lg, rcols_lg;
     // every frame, whatever its class runs: the per-frame convolution of rendered
     // scenes (frames with per-frame transforms), and its per-group sums of g
@@ -194,7 +243,7 @@ hipError_t fft_spec_fwd(hipStream_t st, const FftPlanDev &d, const float *params
                         bool lg = false);
 hipError_t fft_model_cols(hipStream_t st, const FftPlanDev &d);
 hipError_t fft_model_rows(hipStream_t st, const FftPlanDev &d, const float *data, const float *invvar,
-                          double *part_chi, float *model);
+                          double *part_chi, float *model, bool want_rho = true);
 hipError_t fft_rho_cols(hipStream_t st, const FftPlanDev &d);
 hipError_t fft_adj_cols(hipStream_t st, const FftPlanDev &d);
 hipError_t fft_adj_rows(hipStream_t st, const FftPlanDev &d, float *g);
@@ -210,28 +259,25 @@ hipError_t fft_grad_h_cols(hipStream_t st, const FftPlanDev &d, DensePiece *pd =
 // psum (or null): the composite-filter prior's planes after pass D1, summed per pixel instead of reading prior
 hipError_t fft_grad_h_rows_final(hipStream_t st, const FftPlanDev &d, const float *prior, const FinalArgs &fin,
                                  const DenseStar *psum = nullptr);
-// lines of each LDS plane of the one-launch forward: the Q/2+1 columns of the half
-// spectrum, or the (n+1)/2 pairs of real rows (two rows share a complex transform)
-__host__ __device__ inline int fused_plane_lines(int Q, int n)
-{
-    const int pairs = (n + 1) / 2;
-    return (Q / 2 + 1) > pairs ? (Q / 2 + 1) : pairs;
-}
-// bytes of LDS the one-launch forward needs for a class: `planes` (two, or one
-// transformed in place) of fused_plane_lines lines of Q+1 values, the Q twiddles
-// and the (1+4M) P table values
-inline size_t fused_lds_bytes(int Q, int n, int P, int M, int planes = 2)
-{
-    const int rows = fused_plane_lines(Q, n);
-    return ((size_t)planes * rows * (Q + 1) + Q + (size_t)(1 + 4 * M) * P) * 8;
-}
-// transform lengths with a single-plane (in-place) form in the one-launch forward
-__host__ __device__ inline bool fft_ip_length(int L) { return L == 128 || L == 144 || L == 160 || L == 192; }
+// want_rho: also rho_hat, which the adjoint reads (else the loss alone)
 hipError_t fft_fused_fwd(hipStream_t st, const FftPlanDev &d, const float *params, int N, int E, int M, int s,
-                         const float *data, const float *invvar, double *part_chi, DensePiece *pc = nullptr);
+                         const float *data, const float *invvar, double *part_chi, DensePiece *pc = nullptr,
+                         bool want_rho = true);
+struct FrameArgs {
+    const float2 *tw, *Sp, *Hh, *tab;
+    const float *params;
+    int N, E, M;
+    const float *data, *invvar;
+    float2 *Rh;  // null: the loss alone
+    double *part_chi;
+};
+
+hipError_t launch_frames_s1(hipStream_t st, const FftPlanDev &d, const FrameArgs &g, const DensePiece &dp, size_t lds);
+hipError_t launch_frames_s2(hipStream_t st, const FftPlanDev &d, const FrameArgs &g, const DensePiece &dp, size_t lds);
+hipError_t launch_frames_s3(hipStream_t st, const FftPlanDev &d, const FrameArgs &g, const DensePiece &dp, size_t lds);
 hipError_t fft_model_cols_lg(hipStream_t st, const FftPlanDev &d);
 hipError_t fft_model_rows_lg(hipStream_t st, const FftPlanDev &d, const float *data, const float *invvar,
-                             double *part_chi);
+                             double *part_chi, bool want_rho = true);
 hipError_t fft_rho_cols_lg(hipStream_t st, const FftPlanDev &d);
 hipError_t fft_grad_h_inverse(hipStream_t st, const FftPlanDev &d, DensePiece *pd = nullptr);
 hipError_t fft_scene_model(hipStream_t st, const FftPlanDev &d, const float *scene, int s, float *model);

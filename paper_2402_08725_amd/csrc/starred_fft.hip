@@ -19,6 +19,7 @@
 // residual / chi-square epilogue.
 #include "starred_fft.h"
 #include "starred_finalize.h"
+#include "starred_radix.h"
 
 #include <hip/hip_runtime.h>
 
@@ -26,19 +27,6 @@
 #include <type_traits>
 
 namespace starred {
-
-__device__ __forceinline__ float2 cmul(float2 a, float2 b)
-{
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ float2 cmulc(float2 a, float2 b)  // a * conj(b)
-{
-    return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-}
-__device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.y); }
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 
 // radix-R DFT of v in place; sign -1 forward (e^{-i}), +1 inverse
 template <int R>
@@ -248,69 +236,6 @@ __device__ __forceinline__ float2 *fft_ct(float2 *a, float2 *b, int nl, const fl
     }
 }
 
-// Single-plane (in-place) transforms for frames whose two planes do not fit in LDS:
-// each stage reads a thread's butterflies into registers, waits for every thread,
-// then writes the results over the same plane. A thread holds at most KB
-// butterflies (lines at most L/2+1, blocks of kFusedThreads threads).
-template <int R, int L, int NS, bool INV>
-__device__ __forceinline__ void stage_ct_ip(float2 *buf, int nl, const float2 *__restrict__ tw)
-{
-    constexpr int LR = L / R, Ls = L + 1, TS = L / (NS * R);
-    constexpr int KB = ((L / 2 + 1) * LR + kFusedThreads - 1) / kFusedThreads;
-    float2 v[KB][8];
-    int dst[KB];
-    #pragma unroll
-    for (int q = 0; q < KB; ++q) {
-        const int b = threadIdx.x + q * kFusedThreads;
-        dst[q] = -1;
-        if (b < nl * LR) {
-            const int l = b / LR, j = b - l * LR;
-            const float2 *in = buf + l * Ls;
-            const int k = j % NS;
-            #pragma unroll
-            for (int r = 0; r < R; ++r) v[q][r] = in[j + r * LR];
-            if (NS > 1) {
-                #pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    const float2 t = tw[r * k * TS];  // r k TS < L
-                    v[q][r] = INV ? cmulc(v[q][r], t) : cmul(v[q][r], t);
-                }
-            }
-            dft_small<R>(v[q], INV);
-            dst[q] = l * Ls + (j / NS) * NS * R + k;
-        }
-    }
-    __syncthreads();
-    #pragma unroll
-    for (int q = 0; q < KB; ++q)
-        if (dst[q] >= 0) {
-            #pragma unroll
-            for (int r = 0; r < R; ++r) buf[dst[q] + r * NS] = v[q][r];
-        }
-    __syncthreads();
-}
-
-template <int L, bool INV, int I = 0>
-__device__ __forceinline__ void fft_ct_ip(float2 *a, int nl, const float2 *__restrict__ tw)
-{
-    if constexpr (I < ct_nrad(L)) {
-        stage_ct_ip<ct_rad(L, I), L, ct_ns(L, I), INV>(a, nl, tw);
-        fft_ct_ip<L, INV, I + 1>(a, nl, tw);
-    }
-}
-
-template <bool INV>
-__device__ __forceinline__ void lds_fft_ip(float2 *a, int nl, const FftLen &f, const float2 *__restrict__ tw)
-{
-    switch (f.L) {  // the lengths fft_ip_length admits
-    case 128: fft_ct_ip<128, INV>(a, nl, tw); break;
-    case 144: fft_ct_ip<144, INV>(a, nl, tw); break;
-    case 160: fft_ct_ip<160, INV>(a, nl, tw); break;
-    case 192: fft_ct_ip<192, INV>(a, nl, tw); break;
-    default: break;
-    }
-}
-
 // Transform dispatch: compile-time bodies for the common lengths, the runtime
 // Stockham loop otherwise.
 template <bool INV>
@@ -333,19 +258,6 @@ __device__ __forceinline__ float2 *lds_fft_any(float2 *a, float2 *b, int nl, con
     case 576: return fft_ct<576, INV>(a, b, nl, tw);
     default: return lds_fft(a, b, nl, f, tw, INV);
     }
-}
-
-// One-launch forward: two planes (a source and a scratch plane; returns the one
-// holding the result) or, when ip, one plane transformed in place.
-template <bool INV>
-__device__ __forceinline__ float2 *lds_fft_plane(float2 *a, float2 *b, int nl, const FftLen &f,
-                                                 const float2 *__restrict__ tw, bool ip)
-{
-    if (ip) {
-        lds_fft_ip<INV>(a, nl, f, tw);
-        return a;
-    }
-    return lds_fft_any<INV>(a, b, nl, f, tw);
 }
 
 // --------------------------------------------------------------------------
@@ -452,20 +364,6 @@ __device__ __forceinline__ void alias_put(float2 *__restrict__ X, int P, int Q, 
     const int mx = P - Kx;
     if (Kx > 0 && 2 * Kx < P && 2 * (mx % Q) <= Q)
         X[alias_idx(Q, P / Q, Ky == 0 ? 0 : P - Ky, mx)] = make_float2(v.x, -v.y);
-}
-
-// the S values (ky + aQ, kx + bQ), a < S, of one column alias: S consecutive values
-template <int S>
-__device__ __forceinline__ void alias_load(const float2 *__restrict__ X, int at, float2 (&v)[S])
-{
-    if constexpr (S == 2) {
-        const float4 q = *reinterpret_cast<const float4 *>(X + at);  // (at is even: 16-byte aligned)
-        v[0] = make_float2(q.x, q.y);
-        v[1] = make_float2(q.z, q.w);
-    } else {
-        #pragma unroll
-        for (int a = 0; a < S; ++a) v[a] = X[at + a];
-    }
 }
 
 // ---- pass A: rows of the h window of each class (real -> half spectrum) ----
@@ -992,7 +890,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fwd_rows(const LineItem *__rest
     }
     const double tchi = block_sum_d_fft(chi, red);
     if (threadIdx.x == 0 && part_chi) part_chi[blockIdx.x] = tchi;
-    if (model) return;
+    if (model || !T2) return;
     __syncthreads();
     float2 *q = lds_fft_any<false>(o, r, np, fl, tw + fl.tw_off);
     // split the pair's spectrum Z into the two rows' half spectra:
@@ -1006,299 +904,6 @@ __global__ __launch_bounds__(kFftThreads) void k_fwd_rows(const LineItem *__rest
         dst[0] = make_float2(0.5f * (zk.x + zc.x), 0.5f * (zk.y + zc.y));
         if (2 * l + 1 < it.nl) dst[H] = make_float2(0.5f * (zk.y - zc.y), -0.5f * (zk.x - zc.x));
     }
-}
-
-// ---- one-launch forward of a frame whose Q-grid spectra fit in LDS ----
-// A work group per frame runs the whole forward of the loss in LDS: the
-// spectral product and alias fold into the Q x (Q/2+1) model spectrum (stored
-// column-major), the inverse transform along ky, the Hermitian rows and the
-// inverse along x (the model m, Eq. 8), the weighted residual rho and its
-// chi-square partial (Eq. 10), then the forward transforms of rho along x and
-// along y, and writes rho_hat [Q][Q/2+1] to memory for the adjoint. Two LDS
-// planes of max(Q/2+1, (n+1)/2) lines of stride Q+1 alternate as FFT source and
-// scratch; the Q-point twiddles and the class's factor tables sit behind them.
-template <int S, int MS>
-__global__ __launch_bounds__(kFusedThreads) void k_frame_fwd(const FusedItem *__restrict__ items,
-                                                             const ClassFft *__restrict__ classes,
-                                                             const float2 *__restrict__ tw,
-                                                             const float2 *__restrict__ Sp,
-                                                             const float2 *__restrict__ Hh,
-                                                             const float2 *__restrict__ tab,
-                                                             const float *__restrict__ params, int N, int E, int M,
-                                                             const float *__restrict__ data,
-                                                             const float *__restrict__ invvar,
-                                                             float2 *__restrict__ Rh, double *__restrict__ part_chi,
-                                                             DensePiece dp)
-{
-    extern __shared__ float2 sm[];
-    __shared__ double red[kFusedThreads / 64];
-    if (dense_piece_run(dp, sm, red)) return;  // a starlet-prior job carried by this launch
-    const FusedItem &f = items[blockIdx.x];
-    const int i = f.frame;
-    const FftLen &fl = classes[f.cls].fQ;
-    const float2 *twQ = tw + f.tw_off;
-    const int P = f.P, Q = f.Q, HQ = Q / 2 + 1, n = f.n, Ls = Q + 1;
-    const int rows = fused_plane_lines(Q, n);
-    // one plane transformed in place (frames whose two planes exceed the LDS), else two
-    // (not with 5-8 sources held in registers: that form keeps its registers for them)
-    const bool ip = MS != 8 && f.inplace != 0;
-    float2 *A = sm, *B = ip ? sm : sm + rows * Ls;
-    float2 *twl = sm + (ip ? 1 : 2) * rows * Ls;
-    float2 *t = twl + Q;
-    {
-        // the twiddles and the tables: all of a thread's loads issued before its LDS writes
-        const float2 *tg = tab + f.tab_off;
-        const int nt = (1 + 4 * M) * P;
-        constexpr int kTabBatch = 4;
-        for (int e = threadIdx.x; e < Q; e += blockDim.x) twl[e] = twQ[e];
-        for (int e0 = threadIdx.x; e0 < nt; e0 += kTabBatch * kFusedThreads) {
-            float2 v[kTabBatch];
-            #pragma unroll
-            for (int u = 0; u < kTabBatch; ++u) v[u] = tg[min(e0 + u * kFusedThreads, nt - 1)];
-            #pragma unroll
-            for (int u = 0; u < kTabBatch; ++u)
-                if (e0 + u * kFusedThreads < nt) t[e0 + u * kFusedThreads] = v[u];
-        }
-    }
-    twQ = twl;
-    const float2 *Si = Sp + f.s_off;
-    const float2 *Hc = Hh + f.hh_off;
-    const float G = params[(long long)N * N + i];
-    const float *ai = params + (long long)N * N + E + (long long)i * M;
-
-    // lanes over columns kx, row groups over ky (no index divisions in the loops)
-    // (threads packed over the HQ columns: column lane = tid % HQ, row group tid / HQ)
-    const int RGF = kFusedThreads / HQ;
-    const int Q0L = Q <= 64 ? 64 : 128;  // lanes along a row of Q values
-    // this thread's data and weights for the residual (its first kPreRows row pairs),
-    // loaded now so that they arrive during the transforms
-    constexpr int kPreRows = S <= 2 ? 4 : 0;  // (s = 3 keeps its registers for the aliases)
-    const int n2 = (n + 1) / 2;
-    float pre[kPreRows > 0 ? kPreRows : 1][4];
-    {
-        const int x = threadIdx.x % Q0L;
-        #pragma unroll
-        for (int k = 0; k < kPreRows; ++k) {
-            const int yp = threadIdx.x / Q0L + k * (kFusedThreads / Q0L);
-            const bool va = x < n && yp < n2, vb = va && 2 * yp + 1 < n;
-            const long long ia = f.data_off + (long long)(va ? 2 * yp : 0) * n + (va ? x : 0);
-            const long long ib = vb ? ia + n : ia;
-            pre[k][0] = data[ia];
-            pre[k][1] = invvar[ia];
-            pre[k][2] = data[ib];
-            pre[k][3] = invvar[ib];
-        }
-    }
-    __syncthreads();
-    const int lane = threadIdx.x % HQ, rg = threadIdx.x / HQ;
-    const bool colw = rg < RGF;  // this thread works in the column-wise loops
-    // model spectrum, column-major: A[kx][ky]
-    // (with MS > 0 sources at most, the column factors a_k gx_k(Kx) stay in registers)
-    constexpr int MR = MS > 0 ? MS : 1;
-    if (colw) {
-        const int kx = lane;
-        float2 wxG[S], px[S][MR];
-        #pragma unroll
-        for (int b = 0; b < S; ++b) {
-            const int Kx = kx + b * Q;
-            wxG[b] = cscale(t[Kx], G);
-            #pragma unroll
-            for (int k = 0; k < MR; ++k)
-                px[b][k] = (MS > 0 && k < M) ? cscale(t[(1 + 4 * k) * P + Kx], ai[k]) : make_float2(0.f, 0.f);
-        }
-        // the s^2 alias terms of the model spectrum at (kx, ky): consecutive in alias order
-        auto load_row = [&](int ky, float2 (&hv)[S][S], float2 (&sv)[S][S]) {
-            const int at = (ky * HQ + kx) * S * S;
-            #pragma unroll
-            for (int b = 0; b < S; ++b) {
-                alias_load<S>(Hc, at + b * S, hv[b]);
-                alias_load<S>(Si, at + b * S, sv[b]);
-            }
-        };
-        auto row_sum = [&](int ky, const float2 (&hv)[S][S], const float2 (&sv)[S][S]) {
-            float2 acc = make_float2(0.f, 0.f);
-            #pragma unroll
-            for (int a = 0; a < S; ++a) {
-                const int Ky = ky + a * Q;
-                const float2 wy = t[Ky];
-                float2 gy[MR];
-                #pragma unroll
-                for (int k = 0; k < MR; ++k)
-                    gy[k] = (MS > 0 && k < M) ? t[(1 + 4 * k) * P + P + Ky] : make_float2(0.f, 0.f);
-                #pragma unroll
-                for (int b = 0; b < S; ++b) {
-                    const int Kx = kx + b * Q;
-                    const float2 h = hv[b][a], sk = sv[b][a];
-                    float2 F = cadd(h, cmul(wy, wxG[b]));
-                    if (MS > 0) {
-                        #pragma unroll
-                        for (int k = 0; k < MR; ++k) {
-                            F.x = fmaf(gy[k].x, px[b][k].x, fmaf(-gy[k].y, px[b][k].y, F.x));
-                            F.y = fmaf(gy[k].x, px[b][k].y, fmaf(gy[k].y, px[b][k].x, F.y));
-                        }
-                    } else {
-                        for (int k = 0; k < M; ++k) {
-                            const float2 *tk = t + (1 + 4 * k) * P;  // [gx | gy | dgx | dgy]
-                            F = cadd(F, cscale(cmul(tk[P + Ky], tk[Kx]), ai[k]));
-                        }
-                    }
-                    acc = cadd(acc, cmul(sk, F));
-                }
-            }
-            return acc;
-        };
-        if (S <= 2 && MS != 8 && Q >= kProdPairQ) {
-            // long columns: the loads of two rows in flight together (the loop is a chain
-            // of memory round trips otherwise)
-            for (int ky0 = rg; ky0 < Q; ky0 += 2 * RGF) {
-                const int ky1 = ky0 + RGF;
-                float2 h0[S][S], s0[S][S], h1[S][S], s1[S][S];
-                load_row(ky0, h0, s0);
-                load_row(ky1 < Q ? ky1 : ky0, h1, s1);  // (past the end: row ky0 again, unused)
-                A[kx * Ls + ky0] = row_sum(ky0, h0, s0);
-                if (ky1 < Q) A[kx * Ls + ky1] = row_sum(ky1, h1, s1);
-            }
-        } else {
-            for (int ky = rg; ky < Q; ky += RGF) {
-                float2 h0[S][S], s0[S][S];
-                load_row(ky, h0, s0);
-                A[kx * Ls + ky] = row_sum(ky, h0, s0);
-            }
-        }
-    }
-    __syncthreads();
-    float2 *r = lds_fft_plane<true>(A, B, HQ, fl, twQ, ip);  // along ky
-    float2 *o = (r == A) ? B : A;
-    // Rows in pairs (two real rows per complex transform): the inverse of
-    // Z = X_2p + i X_2p+1, X_y the Hermitian rows of the column results, is
-    // x_2p + i x_2p+1; a missing second row (odd n) is zero.
-    auto pair_in = [&](int yp, int kx) {
-        const int ya = 2 * yp, yb = 2 * yp + 1;
-        const bool lo = kx < HQ;
-        const int col = lo ? kx : Q - kx;
-        float2 xa = r[col * Ls + ya];
-        float2 xb = yb < n ? r[col * Ls + yb] : make_float2(0.f, 0.f);
-        if (!lo) {
-            xa.y = -xa.y;
-            xb.y = -xb.y;
-        }
-        return make_float2(xa.x - xb.y, xa.y + xb.x);  // xa + i xb
-    };
-    if (!ip) {
-        for (int yp = threadIdx.x / Q0L; yp < n2; yp += kFusedThreads / Q0L)
-            for (int kx = threadIdx.x % Q0L; kx < Q; kx += Q0L) o[yp * Ls + kx] = pair_in(yp, kx);
-    } else {
-        // in place: every value read before any is overwritten (Q in (64, 192]: 128
-        // lanes along a row, 8 row pairs per sweep, at most 97 pairs)
-        constexpr int IY = (192 / 2 + 1 + 7) / 8;
-        float2 hold[IY][2];
-        #pragma unroll
-        for (int iy = 0; iy < IY; ++iy)
-            #pragma unroll
-            for (int ix = 0; ix < 2; ++ix) {
-                const int yp = threadIdx.x / 128 + iy * 8, kx = threadIdx.x % 128 + ix * 128;
-                hold[iy][ix] = (yp < n2 && kx < Q) ? pair_in(yp, kx) : make_float2(0.f, 0.f);
-            }
-        __syncthreads();
-        #pragma unroll
-        for (int iy = 0; iy < IY; ++iy)
-            #pragma unroll
-            for (int ix = 0; ix < 2; ++ix) {
-                const int yp = threadIdx.x / 128 + iy * 8, kx = threadIdx.x % 128 + ix * 128;
-                if (yp < n2 && kx < Q) o[yp * Ls + kx] = hold[iy][ix];
-            }
-    }
-    __syncthreads();
-    r = lds_fft_plane<true>(o, r, n2, fl, twQ, ip);  // along x: model rows 2p, 2p+1 in the real, imaginary parts
-    o = (r == A) ? B : A;
-    double chi = 0.0;
-    for (int k = 0, yp = threadIdx.x / Q0L; yp < n2; ++k, yp += kFusedThreads / Q0L)
-        for (int x = threadIdx.x % Q0L; x < Q; x += Q0L) {
-            float va = 0.f, vb = 0.f;
-            if (x < n) {
-                const float2 mv = r[yp * Ls + x];
-                const long long ia = f.data_off + (long long)(2 * yp) * n + x;
-                // prefetched for the first kPreRows row pairs of the first column sweep
-                const bool have = k < kPreRows && x < Q0L;
-                float da = 0.f, wa = 0.f, db = 0.f, wb = 0.f;
-                #pragma unroll
-                for (int kk = 0; kk < kPreRows; ++kk)
-                    if (kk == k) {
-                        da = pre[kk][0];
-                        wa = pre[kk][1];
-                        db = pre[kk][2];
-                        wb = pre[kk][3];
-                    }
-                if (!have) {
-                    da = data[ia];
-                    wa = invvar[ia];
-                    if (2 * yp + 1 < n) {
-                        db = data[ia + n];
-                        wb = invvar[ia + n];
-                    }
-                }
-                const float ra = mv.x - da;
-                va = wa * ra;
-                chi += 0.5 * (double)wa * (double)ra * (double)ra;
-                if (2 * yp + 1 < n) {
-                    const float rb = mv.y - db;
-                    vb = wb * rb;
-                    chi += 0.5 * (double)wb * (double)rb * (double)rb;
-                }
-            }
-            o[yp * Ls + x] = make_float2(va, vb);  // rho rows 2p + i (2p+1)
-        }
-    // the frame's chi-square: wave sums in LDS across the barrier the transform needs
-    // anyway, then thread 0 adds them (in wave order) while the others transform
-    #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) chi += __shfl_xor(chi, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = chi;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double tchi = 0.0;
-        #pragma unroll
-        for (int w = 0; w < kFusedThreads / 64; ++w) tchi += red[w];
-        part_chi[blockIdx.x] = tchi;
-    }
-    r = lds_fft_plane<false>(o, r, n2, fl, twQ, ip);  // rho pairs along x
-    o = (r == A) ? B : A;
-    // split each pair's spectrum Z into the two rows' (Hermitian) spectra,
-    // R_a = (Z(k) + conj Z(-k)) / 2 and R_b = (Z(k) - conj Z(-k)) / 2i, and lay the
-    // half spectra out column-major with zero rows y >= n
-    const int km = lane == 0 ? 0 : Q - lane;
-    auto split_at = [&](int y) {
-        float2 v = make_float2(0.f, 0.f);
-        if (y < n) {
-            const float2 z = r[(y >> 1) * Ls + lane], zm = r[(y >> 1) * Ls + km];
-            v = (y & 1) ? make_float2(0.5f * (z.y + zm.y), 0.5f * (zm.x - z.x))
-                        : make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));
-        }
-        return v;
-    };
-    if (!ip) {
-        if (colw)
-            for (int y = rg; y < Q; y += RGF) o[lane * Ls + y] = split_at(y);
-    } else {
-        // in place: at most 192 rows over at least 10 row groups (Q/2+1 <= 97 lanes)
-        constexpr int IS = (192 + 9) / 10;
-        float2 hold[IS];
-        #pragma unroll
-        for (int i2 = 0; i2 < IS; ++i2) {
-            const int y = rg + i2 * RGF;
-            hold[i2] = (colw && y < Q) ? split_at(y) : make_float2(0.f, 0.f);
-        }
-        __syncthreads();
-        #pragma unroll
-        for (int i2 = 0; i2 < IS; ++i2) {
-            const int y = rg + i2 * RGF;
-            if (colw && y < Q) o[lane * Ls + y] = hold[i2];
-        }
-    }
-    __syncthreads();
-    r = lds_fft_plane<false>(o, r, HQ, fl, twQ, ip);  // along y
-    float2 *R = Rh + f.r_off;
-    if (colw)
-        for (int ky = rg; ky < Q; ky += RGF) R[ky * HQ + lane] = r[lane * Ls + ky];
 }
 
 // ---- per-eval tables: window indicator and point-source factors ----
@@ -1738,11 +1343,11 @@ hipError_t fft_model_cols(hipStream_t st, const FftPlanDev &d)
 }
 
 hipError_t fft_model_rows(hipStream_t st, const FftPlanDev &d, const float *data, const float *invvar,
-                          double *part_chi, float *model)
+                          double *part_chi, float *model, bool want_rho)
 {
     if (d.frows.n_items <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fwd_rows, dim3(d.frows.n_items), dim3(kFftThreads), d.frows.lds_bytes, st, d.frows.items,
-                       d.classes, d.frames, d.tw, d.T, data, invvar, d.T2, model, part_chi);
+                       d.classes, d.frames, d.tw, d.T, data, invvar, want_rho ? d.T2 : nullptr, model, part_chi);
     return hipGetLastError();
 }
 
@@ -1793,30 +1398,31 @@ hipError_t fft_resid_rows(hipStream_t st, const FftPlanDev &d, const float *resi
 }
 
 hipError_t fft_fused_fwd(hipStream_t st, const FftPlanDev &d, const float *params, int N, int E, int M, int s,
-                         const float *data, const float *invvar, double *part_chi, DensePiece *pc)
+                         const float *data, const float *invvar, double *part_chi, DensePiece *pc, bool want_rho)
 {
-    if (d.n_fused <= 0) return hipSuccess;
+    if (d.n_frame_items <= 0) return hipSuccess;
     DensePiece dp;
-    size_t lds = d.fused_lds;
+    size_t lds = d.frame_lds;
     if (pc && pc->pass >= 0) {
         dp = *pc;
-        dp.first = d.n_fused;
+        dp.first = d.n_frame_items;
         lds = std::max(lds, piece_lds(dp));
     }
-    const int grid = d.n_fused + (dp.pass >= 0 ? dp.jobs : 0);
-#define FUSED_FWD(SS, MS)                                                                                     \
-    hipLaunchKernelGGL((k_frame_fwd<SS, MS>), dim3(grid), dim3(kFusedThreads), lds, st, d.fused, d.classes,      \
-                       d.tw, d.S, d.Hh, d.tab, params, N, E, M, data, invvar, d.Rh, part_chi, dp)
-#define FUSED_FWD_M(SS)                       \
-    if (M <= 4) FUSED_FWD(SS, 4);             \
-    else if (M <= 8) FUSED_FWD(SS, 8);        \
-    else FUSED_FWD(SS, 0)
-    if (s == 1) { FUSED_FWD_M(1); }
-    else if (s == 2) { FUSED_FWD_M(2); }
-    else { FUSED_FWD_M(3); }
-#undef FUSED_FWD_M
-#undef FUSED_FWD
-    return hipGetLastError();
+    FrameArgs g;
+    g.tw = d.tw;
+    g.Sp = d.S;
+    g.Hh = d.Hh;
+    g.tab = d.tab;
+    g.params = params;
+    g.N = N;
+    g.E = E;
+    g.M = M;
+    g.data = data;
+    g.invvar = invvar;
+    g.Rh = want_rho ? d.Rh : nullptr;
+    g.part_chi = part_chi;
+    return s == 1 ? launch_frames_s1(st, d, g, dp, lds)
+                  : (s == 2 ? launch_frames_s2(st, d, g, dp, lds) : launch_frames_s3(st, d, g, dp, lds));
 }
 
 hipError_t fft_model_cols_lg(hipStream_t st, const FftPlanDev &d)
@@ -1825,11 +1431,11 @@ hipError_t fft_model_cols_lg(hipStream_t st, const FftPlanDev &d)
 }
 
 hipError_t fft_model_rows_lg(hipStream_t st, const FftPlanDev &d, const float *data, const float *invvar,
-                             double *part_chi)
+                             double *part_chi, bool want_rho)
 {
     if (d.frows_lg.n_items <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fwd_rows, dim3(d.frows_lg.n_items), dim3(kFftThreads), d.frows_lg.lds_bytes, st,
-                       d.frows_lg.items, d.classes, d.frames, d.tw, d.T, data, invvar, d.T2, nullptr, part_chi);
+                       d.frows_lg.items, d.classes, d.frames, d.tw, d.T, data, invvar, want_rho ? d.T2 : nullptr, nullptr, part_chi);
     return hipGetLastError();
 }
 

@@ -55,6 +55,7 @@ constexpr int kAdjThreads = kAdjTP * kAdjTQ / 4;
 constexpr int kGaussRadius = 8;  // r is evaluated within +-8 fine px of c_k
 constexpr size_t kMaxLds = 160 * 1024;
 
+int device_cus();  // compute units of the current device
 size_t fwd_lds_bytes(int s, int Tmax);
 size_t adj_lds_bytes(int Ar_max, int Bpad_max);
 

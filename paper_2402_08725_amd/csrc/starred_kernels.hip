@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kFwdThreads) void k_fwd_direct(
 
 size_t fwd_lds_bytes(int s, int Tmax) { return (size_t)(s * (kFwdTP - 1) + kFwdCA) * s * (kFwdTQ + Tmax) * 4; }
 
-static int device_cus()
+int device_cus()
 {
     static int n = 0;
     if (n <= 0) {

@@ -125,7 +125,7 @@ struct starred_plan {
     std::vector<FrameFft> ffr;
     std::vector<int> fcls;        // class of each frame
     std::vector<int> cls_frames;  // frames in class order
-    std::vector<int> cls_fits;    // per class: the one-launch forward fits in LDS (1: two planes, 2: one in place)
+    std::vector<int> cls_fits;    // per class: the one-launch forward fits in LDS (1: with room for a second plane, 2: alone)
     double *d_part_chi_fft = nullptr;  // chi-square partials: FFT groups, then direct tiles
     int n_fft_chi = 0;
     // launch shapes of the FFT path: work groups aimed at by the spectral adjoint
@@ -521,11 +521,12 @@ static bool smooth235(int v)
     return v == 1;
 }
 
-// smallest P >= need with P a multiple of 2s and P = 2^a 3^b 5^c
+// smallest P >= need with P a multiple of 2s and P = 2^a 3^b 5^c, and with Q = P/s among
+// the lengths of the one-launch forward unless it is above them
 static int good_size(int need, int s)
 {
     for (int P = need;; ++P)
-        if (P % (2 * s) == 0 && smooth235(P)) return P;
+        if (P % (2 * s) == 0 && smooth235(P) && (P / s > kFrameMaxQ || frame_body_frames(P / s, s))) return P;
 }
 
 static FftLen make_len(int L, std::map<int, long long> &tw_offsets, long long &tw_total)
@@ -599,12 +600,10 @@ static int build_fft(starred_plan *p)
     // classes whose Q-grid planes fit in LDS may take the one-launch forward
     p->cls_fits.clear();
     for (auto &c : p->cls) {
-        // the one-launch forward: two LDS planes (1), one plane in place (2), or none (0)
+        // (reported as 1 where a second plane would fit beside it, else 2)
         int fit = 0;
-        if (fused_lds_bytes(c.Q, c.n, c.P, p->M, 2) <= kFusedLdsMax) fit = 1;
-        else if (c.Q > 64 && fft_ip_length(c.Q) && !(p->M > 4 && p->M <= 8) &&
-                 fused_lds_bytes(c.Q, c.n, c.P, p->M, 1) <= kFusedLdsMax)
-            fit = 2;  // (5-8 sources: the source factors take the registers the in-place form needs)
+        if (frame_body_frames(c.Q, s) && frame_lds_bytes(c.Q, c.P, p->M, 1) <= kFusedLdsMax)
+            fit = frame_lds_bytes(c.Q, c.P, p->M, 2) <= kFusedLdsMax ? 1 : 2;
         p->cls_fits.push_back(fit);
         c.fused = fit ? 1 : 0;
         c.direct = 0;
@@ -737,40 +736,52 @@ static int build_fft_lists(starred_plan *p)
         if ((rc = p->alloc_list(&dst, sp.size()))) return rc;
         if (!sp.empty()) HIP_TRY(hipMemcpy(dst, sp.data(), sizeof(SpecItem) * sp.size(), hipMemcpyHostToDevice));
     }
-    // frames of the one-launch forward, largest transforms first
+    // frames of the one-launch forward, largest transforms first, in work groups of one frame,
+    // or of several where frames outnumber the compute units (one group runs per unit at a
+    // time, and its time grows slower than its frames)
     {
-        std::vector<int> fi;
-        size_t lds = 0;
-        for (int i = 0; i < E; ++i)
-            if (!is_direct(fcls[i]) && p->cls[fcls[i]].fused) {
-                fi.push_back(i);
-                const ClassFft &cl = p->cls[fcls[i]];
-                lds = std::max(lds, fused_lds_bytes(cl.Q, cl.n, cl.P, M, p->cls_fits[fcls[i]] == 2 ? 1 : 2));
+        int total = 0, nchi = 0;
+        for (int c = 0; c < (int)p->cls.size(); ++c)
+            if (!is_direct(c) && p->cls[c].fused) total += p->cls[c].ncf;
+        const bool many = total > device_cus();
+        std::vector<FrameItem> fr;
+        size_t flds = 0;
+        for (int c = 0; c < (int)p->cls.size(); ++c) {
+            const ClassFft &cl = p->cls[c];
+            if (is_direct(c) || !cl.fused) continue;
+            const int most = frame_body_frames(cl.Q, p->s);
+            const int *cf = cls_frames.data() + cl.cf_off;
+            const int per = many && frame_lds_bytes(cl.Q, cl.P, M, most) <= kFusedLdsMax ? most : 1;
+            flds = std::max(flds, frame_lds_bytes(cl.Q, cl.P, M, per));
+            for (int f0 = 0; f0 < cl.ncf; f0 += per) {
+                FrameItem it{};
+                it.nf = std::min(per, cl.ncf - f0);
+                it.per = per;
+                it.Q = cl.Q;
+                it.n = cl.n;
+                it.tw_off = cl.fQ.tw_off;
+                it.tab_off = cl.tab_off;
+                it.hh_off = cl.hh_off;
+                for (int q = 0; q < it.nf; ++q) {
+                    const FrameFft &f = p->ffr[cf[f0 + q]];
+                    it.frame[q] = cf[f0 + q];
+                    it.chi[q] = nchi++;
+                    it.s_off[q] = f.s_off;
+                    it.data_off[q] = f.data_off;
+                    it.r_off[q] = f.r_off;
+                }
+                fr.push_back(it);
             }
-        std::stable_sort(fi.begin(), fi.end(), [&](int a, int b) { return p->cls[fcls[a]].Q > p->cls[fcls[b]].Q; });
-        std::vector<FusedItem> fu;
-        for (int i : fi) {
-            const ClassFft &cl = p->cls[fcls[i]];
-            const FrameFft &f = p->ffr[i];
-            FusedItem it{};
-            it.frame = i;
-            it.cls = fcls[i];
-            it.P = cl.P;
-            it.Q = cl.Q;
-            it.n = cl.n;
-            it.inplace = p->cls_fits[fcls[i]] == 2 ? 1 : 0;
-            it.tw_off = cl.fQ.tw_off;
-            it.s_off = f.s_off;
-            it.data_off = f.data_off;
-            it.r_off = f.r_off;
-            it.tab_off = cl.tab_off;
-            it.hh_off = cl.hh_off;
-            fu.push_back(it);
         }
-        d.n_fused = (int)fu.size();
-        d.fused_lds = lds;
-        if ((rc = p->alloc_list(&d.fused, std::max<size_t>(1, fu.size())))) return rc;
-        if (!fu.empty()) HIP_TRY(hipMemcpy(d.fused, fu.data(), sizeof(FusedItem) * fu.size(), hipMemcpyHostToDevice));
+        std::stable_sort(fr.begin(), fr.end(), [](const FrameItem &a, const FrameItem &b) {
+            return a.nf * a.Q * a.Q > b.nf * b.Q * b.Q;
+        });
+        d.n_frame_items = (int)fr.size();
+        d.n_fused = nchi;
+        d.frame_lds = flds;
+        if ((rc = p->alloc_list(&d.frame_items, std::max<size_t>(1, fr.size())))) return rc;
+        if (!fr.empty())
+            HIP_TRY(hipMemcpy(d.frame_items, fr.data(), sizeof(FrameItem) * fr.size(), hipMemcpyHostToDevice));
     }
     // frequency-domain adjoint: items over chunks of p->adj_fc frames x ranges of
     // rows of the P half spectrum, about p->adj_blocks of them per launch (chunks of
@@ -1515,7 +1526,7 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
             }
             e1 = p->prof_start(sf);
             HIP_TRY(fft_fused_fwd(sf, p->fd, params, p->N, p->E, p->M, p->s, p->data, p->invvar,
-                                  p->d_part_chi_fft + n_rows, ride ? &pc : nullptr));
+                                  p->d_part_chi_fft + n_rows, ride ? &pc : nullptr, grad != nullptr));
             p->prof_stop(STARRED_STAGE_FFT_FUSED, e1, sf);
             if (split) HIP_TRY(hipEventRecord(p->ev_join3, p->st3));
         }
@@ -1526,8 +1537,8 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
         HIP_TRY(fused ? fft_model_cols_lg(p->st, p->fd) : fft_model_cols(p->st, p->fd));
         p->prof_stop(STARRED_STAGE_FFT_MCOLS, e1);
         e1 = p->prof_start();
-        HIP_TRY(fused ? fft_model_rows_lg(p->st, p->fd, p->data, p->invvar, p->d_part_chi_fft)
-                      : fft_model_rows(p->st, p->fd, p->data, p->invvar, p->d_part_chi_fft, nullptr));
+        HIP_TRY(fused ? fft_model_rows_lg(p->st, p->fd, p->data, p->invvar, p->d_part_chi_fft, grad != nullptr)
+                      : fft_model_rows(p->st, p->fd, p->data, p->invvar, p->d_part_chi_fft, nullptr, grad != nullptr));
         p->prof_stop(STARRED_STAGE_FFT_MROWS, e1);
         p->prof_stop(STARRED_STAGE_CONV_FWD, e0);
         n_chi = n_rows + (fused ? p->fd.n_fused : 0);
