@@ -18,9 +18,10 @@
 //   B  c_j = M_j T_j           (columns, j >= 1)
 //   C  alpha_j, z_j, the L1 share, and U_j = (D Y_j D) M_j^T, Y_j = z_j - z_{j-1}
 //      (rows; U_0 = z_0)
-//   D  out = U_0 + sum_{j >= 1} D^-1 (M_j U_j) D^-1   (columns)
-// The job bodies take the work-group index as an argument so that other
-// launches can carry them as extra work groups.
+//   D  T_j = D^-1 (M_j U_j) D^-1 (columns, j >= 1); the reader sums U_0 + sum_j T_j
+// The job bodies take the work-group index as an argument: other launches carry them as
+// extra work groups, where four passes of independent jobs cost next to nothing. (On their
+// own the passes of starred_scales.h are faster.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -43,8 +44,7 @@ struct DenseStar {
     const float *W = nullptr;    // weights: per pixel [J][N][N] (w_stride != 0) or per scale [J]
     int w_stride = 0;
     float lam0 = 0.f, lam1 = 0.f;  // image 0's and image 1's weight
-    const float *zin = nullptr;  // given coefficients' subgradient (adjoint alone): z [B][J][N][N]
-    float *out = nullptr;        // [B][N][N]
+    bool want_grad = false;      // build U_j and T_j
     double *part_l1 = nullptr;   // [B][J][rows jobs]
 
     // half width of level j's composite filter, 2^{j+1} - 2; its 2 bw + 1 taps
@@ -59,7 +59,6 @@ struct DenseStar {
     __host__ __device__ int jobs_a() const { return B * (J - 1) * xjobs(); }
     __host__ __device__ int jobs_b() const { return B * (J - 1) * tiles() * tiles(); }
     __host__ __device__ int jobs_c() const { return B * J * xjobs(); }
-    __host__ __device__ int jobs_d() const { return B * tiles() * tiles(); }
     __host__ __device__ int jobs_d1() const { return B * (J - 1) * tiles() * tiles(); }
     __host__ __device__ int l1_slots() const { return B * J * xjobs(); }
     __host__ __device__ const float *image(int b) const { return b ? img1 : img; }
@@ -272,11 +271,10 @@ __device__ __forceinline__ double dense_alpha(const DenseStar &d, int b, int j, 
     return cj - cn;
 }
 
-// z_j at (y, k): lambda W_j sgn(alpha_j) (FP32 product), or the given subgradient
+// z_j at (y, k): lambda W_j sgn(alpha_j) (FP32 product)
 __device__ __forceinline__ float dense_z(const DenseStar &d, int b, int j, int y, int k, float lam)
 {
     const long long pix = (long long)y * d.N + k, NN = (long long)d.N * d.N;
-    if (d.zin) return d.zin[((long long)b * d.J + j) * NN + pix];
     const float w = d.w_stride ? d.W[j * NN + pix] : d.W[j];
     return lam * w * dsgn(dense_alpha(d, b, j, y, k));
 }
@@ -290,7 +288,7 @@ __device__ __forceinline__ void dense_job_c(const DenseStar &d, int job, double 
     const long long NN = (long long)N * N;
     const float lam = b ? d.lam1 : d.lam0;
     double l1 = 0.0;
-    if (!d.zin) {
+    {
         // the level's L1 share over this job's rows
         for (int e = threadIdx.x; e < ny * N; e += blockDim.x) {
             const int y = y0 + e / N, k = e % N;
@@ -300,7 +298,7 @@ __device__ __forceinline__ void dense_job_c(const DenseStar &d, int job, double 
         }
     }
     double *U = d.U + d.plane(b, j);
-    if (!d.out) {
+    if (!d.want_grad) {
         // the loss alone: no subgradient image
     } else if (j == 0) {
         for (int e = threadIdx.x; e < ny * N; e += blockDim.x) {
@@ -320,35 +318,6 @@ __device__ __forceinline__ void dense_job_c(const DenseStar &d, int job, double 
         const double s = dense_block_sum(l1, red);
         if (threadIdx.x == 0) d.part_l1[(b * d.J + j) * xj + (y0 / d.rx)] = s;
     }
-}
-
-// ---- pass D: out = U_0 + sum_j D^-1 (M_j U_j) D^-1 ----
-// lds holds every level's strip at once (dense_d_lds doubles).
-__device__ __forceinline__ void dense_job_d(const DenseStar &d, int job, double *lds)
-{
-    const int nt = d.tiles(), per_b = nt * nt;
-    const int b = job / per_b, tile = job % per_b, N = d.N;
-    const int y0 = (tile / nt) * kDenseTile, x0 = (tile % nt) * kDenseTile;
-    // every level's strip in one batched staging pass (levels one after the other)
-    int total = 0;
-    for (int j = 1; j < d.J; ++j) total += (kDenseTile + 2 * d.bw(j)) * kDenseTile;
-    dense_stage(lds, total, kDenseYTail, [&](int e) {
-        int j = 1, off = 0;
-        while (e >= off + (kDenseTile + 2 * d.bw(j)) * kDenseTile) off += (kDenseTile + 2 * d.bw(j++)) * kDenseTile;
-        const double *U = d.U + d.plane(b, j);
-        return dense_strip_at(d, j, y0, x0, e - off, [&](int y, int x) { return U[y * N + x]; });
-    });
-    __syncthreads();
-    int off = 0;
-    const int ty = threadIdx.x / kDenseTile, tx = threadIdx.x % kDenseTile, y = y0 + ty, x = x0 + tx;
-    if (threadIdx.x >= kDenseTile * kDenseTile || y >= N || x >= N) return;
-    double acc = 0.0;
-    for (int j = 1; j < d.J; ++j) {
-        acc += dense_ysum(d, j, lds + off, ty, tx);
-        off += (kDenseTile + 2 * d.bw(j)) * kDenseTile;
-    }
-    const long long pix = (long long)y * N + x;
-    d.out[(long long)b * N * N + pix] = (float)(d.U[d.plane(b, 0) + pix] + acc / (dend(y, N) * dend(x, N)));
 }
 
 // ---- pass D1: level j's term D^-1 (M_j U_j) D^-1 alone, into plane j of T ----
@@ -384,7 +353,7 @@ namespace starred {
 // kDenseThreads threads and dense_piece_lds bytes of dynamic LDS).
 struct DensePiece {
     DenseStar d;
-    int pass = -1;  // 0..3: A..D, 4: D1; -1: none
+    int pass = -1;  // 0..2: A..C, 4: D1; -1: none
     int first = 0;
     int jobs = 0;
 };
@@ -399,7 +368,6 @@ __device__ __forceinline__ bool dense_piece_run(const DensePiece &p, void *lds_r
     case 0: dense_job_a(p.d, job, lds); break;
     case 1: dense_job_b(p.d, job, lds); break;
     case 2: dense_job_c(p.d, job, lds, red); break;
-    case 3: dense_job_d(p.d, job, lds); break;
     default: dense_job_d1(p.d, job, lds); break;
     }
     return true;

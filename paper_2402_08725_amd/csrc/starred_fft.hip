@@ -1277,7 +1277,7 @@ static size_t piece_lds(const DensePiece &p)
 {
     if (p.pass < 0) return 0;
     if (p.pass == 0 || p.pass == 2) return dense_lds_xr(p.d.N, p.d.J, p.d.rx);
-    return p.pass == 3 ? dense_lds_d(p.d.J) : dense_lds_y(p.d.J);
+    return dense_lds_y(p.d.J);
 }
 
 // n_main work groups of line groups (and extras), then the carried pass's jobs

@@ -133,14 +133,12 @@ hipError_t launch_finalize_small(hipStream_t st, int E, int M, int n_chi, const 
 hipError_t launch_copy_probe(hipStream_t st, const float *src, float *dst, long long n);
 hipError_t launch_idle(hipStream_t st, int iters);
 
-// partial L1 slots the forward transform writes for an N x N image and J planes
-int starlet_l1_slots(int N, int J);
-hipError_t launch_starlet_fwd(hipStream_t st, int N, int J, const float *img, float *coeffs,
-                              float *z, const float *W, int w_stride, float lam, float *c_a,
-                              float *c_b, float *tmp, double *part_l1, int *n_l1);
-hipError_t launch_starlet_prior(hipStream_t st, int N, int J, int B, const float *img, float *z, const float *W,
-                                int w_stride, float lam0, float lam1, float *c_a, float *c_b, double *part_l1,
-                                int *n_l1);
+// Starlet transform (starred_scales.h, starred_starlet.hip)
+struct StarArgs;
+bool star_fp64(int N, int J);                // whether one or two images are transformed in FP64
+int star_l1_slots(const StarArgs &a);        // FP64 L1 partials per image
+hipError_t launch_star_forward(hipStream_t st, const StarArgs &a);
+hipError_t launch_star_adjoint(hipStream_t st, const StarArgs &a);
 // Starlet prior through the per-scale composite filters (starred_starlet.hip)
 struct DenseStar;
 constexpr int kDenseMaxN = 256;
@@ -153,15 +151,6 @@ void dense_taps(int J, double *out);  // host: the composite filters of levels 1
 size_t dense_lds_x(int N, int J);
 size_t dense_lds_xr(int N, int J, int rx);  // rx rows per job
 size_t dense_lds_y(int J);
-size_t dense_lds_d(int J);
-// L1 partials (part_l1, if set) and, with out set, the subgradient's image
-hipError_t launch_dense_prior(hipStream_t st, const DenseStar &d);
-// coefficients alpha [B][J][N][N] of d.img
-hipError_t launch_dense_coeffs(hipStream_t st, const DenseStar &d, float *coeffs);
-// out = Phi zin
-hipError_t launch_dense_adjoint(hipStream_t st, const DenseStar &d);
-hipError_t launch_starlet_adj_batch(hipStream_t st, int N, int J, int B, const float *z, float *out, float *v_a,
-                                    float *v_b);
 hipError_t launch_pts_render(hipStream_t st, int N, int E, int M, float sigma, const float *params, float *h_out,
                              float *P_out);
 hipError_t launch_pts_dots(hipStream_t st, int N, int E, int M, float sigma, const float *params, const float *q,
@@ -169,12 +158,6 @@ hipError_t launch_pts_dots(hipStream_t st, int N, int E, int M, float sigma, con
 hipError_t launch_pts_images(hipStream_t st, int N, int E, int M, float sigma, const float *params, float *out);
 hipError_t launch_pts_sums(hipStream_t st, int B, int n, const double *part, int N, int E, int M, const float *params,
                            double *out);
-hipError_t launch_starlet_fwd_batch(hipStream_t st, int N, int J, int B, const float *img, float *coeffs,
-                                    float *c_a, float *c_b, const float *wzero);
-hipError_t launch_starlet_adj(hipStream_t st, int N, int J, const float *z, float *out,
-                              float *v_a, float *v_b, float *tmp);
-
-
 hipError_t launch_adam(hipStream_t st, long long P, const long long *seg_end, const float *lr,
                        float *params, const float *grad, float *m, float *v, int *d_t, float beta1,
                        float beta2, float eps, int rule = 0, float eps_root = 0.f);

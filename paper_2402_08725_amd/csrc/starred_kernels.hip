@@ -18,14 +18,6 @@ namespace starred {
 // helpers
 // --------------------------------------------------------------------------
 
-__device__ __forceinline__ int mirror_idx(int i, int N)
-{
-    i = i < 0 ? -i : i;
-    return i > N - 1 ? 2 * (N - 1) - i : i;
-}
-
-__device__ __forceinline__ int floordiv(int a, int b) { return (a >= 0) ? a / b : -((-a + b - 1) / b); }
-
 // Deterministic block sum of one double per thread; result valid in thread 0.
 template <int NT>
 __device__ __forceinline__ double block_sum_d(double v, double *sh)
@@ -893,368 +885,6 @@ hipError_t launch_finalize_small(hipStream_t st, int E, int M, int n_chi, const 
     fa.pts = pts;
     hipLaunchKernelGGL(k_finalize_small, dim3(1 + hblocks), dim3(kFinThreads), 0, st, fa, classes, ncls, hcls, prior,
                        psum ? *psum : DenseStar());
-    return hipGetLastError();
-}
-
-// --------------------------------------------------------------------------
-// a6 + a7: starlet forward (B3 a-trous, mirror boundary) with the weighted L1
-// term and its subgradient fused into the column pass.
-// --------------------------------------------------------------------------
-
-__constant__ float kB3[5] = {1.f / 16, 4.f / 16, 6.f / 16, 4.f / 16, 1.f / 16};
-constexpr int kStarThreads = 256;
-
-__device__ __forceinline__ float sgnf(float v) { return (float)((v > 0.f) - (v < 0.f)); }
-
-// One smoothing level j (spacing d = 2^j) of the forward transform per launch,
-// on kStarTile x kStarTile output tiles: the row filter R_j is applied to every
-// (virtual) row the column taps of the tile reach and kept in LDS, then the
-// column filter C_j gives c_{j+1}; alpha_j = c_j - c_{j+1}, with the weighted L1
-// term and its subgradient (and, on the last level, the coarse plane as well).
-// Virtual row v maps to image row mirror(v); 2d < N keeps one reflection enough.
-constexpr int kStarTile = 16;
-static_assert(kStarTile * kStarTile == kStarThreads, "one output pixel per thread");
-// The lines a level's second 1-D pass reads for a tile: the kStarTile + 4d contiguous
-// ones while the five taps' sets overlap (d <= kStarTile), otherwise only the five sets
-// of kStarTile lines (line kStarTile t' + l, t' = t + 2, holds the tile's line l moved
-// by t d), so the staged work stops growing with the hole size.
-__host__ __device__ constexpr int star_lines(int d) { return d > kStarTile ? 5 * kStarTile : kStarTile + 4 * d; }
-static size_t star_lds(int d) { return sizeof(float) * (size_t)star_lines(d) * kStarTile; }
-
-__global__ __launch_bounds__(kStarThreads) void k_star_level(
-    const float *__restrict__ cj, float *__restrict__ cnext, float *__restrict__ coeffs, float *__restrict__ z,
-    const float *__restrict__ W, int w_stride, float lam, int N, int d, int j, int last,
-    double *__restrict__ part_l1, long long img_stride, long long co_stride, float lam1, long long l1_stride)
-{
-    extern __shared__ float tmp[];  // star_lines(d) rows x kStarTile
-    __shared__ double red[kStarThreads / 64];
-    // a batch of images along blockIdx.z: image b's planes, subgradient and L1
-    // partials sit b strides further; image 1 takes the weight lam1
-    cj += blockIdx.z * img_stride;
-    cnext += blockIdx.z * img_stride;
-    if (coeffs) coeffs += blockIdx.z * co_stride;
-    if (z) z += blockIdx.z * co_stride;
-    if (part_l1) part_l1 += blockIdx.z * l1_stride;
-    if (blockIdx.z == 1) lam = lam1;
-    const int x0 = blockIdx.x * kStarTile, y0 = blockIdx.y * kStarTile;
-    const bool gath = d > kStarTile;  // the five taps' row sets apart: stage only those
-    const int R = star_lines(d), vy0 = y0 - 2 * d;
-    const int vmax = min(y0 + kStarTile, N) - 1 + 2 * d;  // last virtual row a tap reaches
-    for (int e = threadIdx.x; e < R * kStarTile; e += kStarThreads) {
-        const int r = e / kStarTile, x = x0 + (e % kStarTile);
-        // virtual row of staged row r, and whether an output row of the tile reads it
-        const int rl = r % kStarTile;
-        const int vy = gath ? y0 + rl + (r / kStarTile - 2) * d : vy0 + r;
-        const bool need = gath ? y0 + rl < N : vy <= vmax;
-        float acc = 0.f;
-        if (x < N && need) {
-            const float *row = cj + (long long)mirror_idx(vy, N) * N;
-            #pragma unroll
-            for (int t = -2; t <= 2; ++t) acc = fmaf(kB3[t + 2], row[mirror_idx(x + t * d, N)], acc);
-        }
-        tmp[e] = acc;
-    }
-    __syncthreads();
-    const int yl = threadIdx.x / kStarTile, xl = threadIdx.x % kStarTile;
-    const int y = y0 + yl, x = x0 + xl;
-    const long long NN = (long long)N * N;
-    double l1 = 0.0;
-    if (y < N && x < N) {
-        const long long pix = (long long)y * N + x;
-        float acc = 0.f;
-        #pragma unroll
-        for (int t = -2; t <= 2; ++t) {
-            const int r = gath ? (t + 2) * kStarTile + yl : yl + 2 * d + t * d;
-            acc = fmaf(kB3[t + 2], tmp[r * kStarTile + xl], acc);
-        }
-        cnext[pix] = acc;
-        const float al = cj[pix] - acc;
-        const float wj = w_stride ? W[j * NN + pix] : W[j];
-        if (coeffs) coeffs[j * NN + pix] = al;
-        if (z) z[j * NN + pix] = lam * wj * sgnf(al);
-        l1 += (double)lam * (double)wj * (double)fabsf(al);
-        if (last) {
-            const float wl = w_stride ? W[(j + 1) * NN + pix] : W[j + 1];
-            if (coeffs) coeffs[(j + 1) * NN + pix] = acc;
-            if (z) z[(j + 1) * NN + pix] = lam * wl * sgnf(acc);
-            l1 += (double)lam * (double)wl * (double)fabsf(acc);
-        }
-    }
-    const double s = block_sum_d<kStarThreads>(l1, red);
-    if (threadIdx.x == 0 && part_l1) part_l1[blockIdx.y * gridDim.x + blockIdx.x] = s;
-}
-
-static int star_tiles(int N) { return (N + kStarTile - 1) / kStarTile; }
-
-int starlet_l1_slots(int N, int J)
-{
-    const int plane = (int)(((long long)N * N + kStarThreads - 1) / kStarThreads);
-    const int tiles = star_tiles(N) * star_tiles(N);
-    return std::max(1, J - 1) * std::max(plane, tiles);
-}
-
-// J == 1: the only plane is the image itself.
-__global__ __launch_bounds__(kStarThreads) void k_star_plane(
-    const float *__restrict__ img, float *__restrict__ coeffs, float *__restrict__ z,
-    const float *__restrict__ W, int w_stride, float lam, int N, double *__restrict__ part_l1)
-{
-    __shared__ double red[kStarThreads / 64];
-    const int pix = blockIdx.x * blockDim.x + threadIdx.x;
-    double l1 = 0.0;
-    if (pix < N * N) {
-        const float al = img[pix];
-        const float wj = w_stride ? W[pix] : W[0];
-        if (coeffs) coeffs[pix] = al;
-        if (z) z[pix] = lam * wj * sgnf(al);
-        l1 = (double)lam * (double)wj * (double)fabsf(al);
-    }
-    const double s = block_sum_d<kStarThreads>(l1, red);
-    if (threadIdx.x == 0 && part_l1) part_l1[blockIdx.x] = s;
-}
-
-hipError_t launch_starlet_fwd(hipStream_t st, int N, int J, const float *img, float *coeffs,
-                              float *z, const float *W, int w_stride, float lam, float *c_a,
-                              float *c_b, float *, double *part_l1, int *n_l1)
-{
-    const int nb = (N * N + kStarThreads - 1) / kStarThreads;
-    if (J == 1) {
-        hipLaunchKernelGGL(k_star_plane, dim3(nb), dim3(kStarThreads), 0, st, img, coeffs, z, W,
-                           w_stride, lam, N, part_l1);
-        if (n_l1) *n_l1 = nb;
-        return hipGetLastError();
-    }
-    const int nt = star_tiles(N);
-    const float *cur = img;
-    for (int j = 0; j < J - 1; ++j) {
-        float *nxt = (j % 2 == 0) ? c_a : c_b;
-        const int d = 1 << j;
-        const size_t lds = star_lds(d);
-        hipLaunchKernelGGL(k_star_level, dim3(nt, nt), dim3(kStarThreads), lds, st, cur, nxt, coeffs, z, W,
-                           w_stride, lam, N, d, j, (int)(j == J - 2),
-                           part_l1 ? part_l1 + (long long)j * nt * nt : nullptr, 0LL, 0LL, lam, 0LL);
-        cur = nxt;
-    }
-    if (n_l1) *n_l1 = (J - 1) * nt * nt;
-    return hipGetLastError();
-}
-
-// --------------------------------------------------------------------------
-// a8: starlet adjoint Phi z:  v = z_{J-1};  v = z_j + H_j^T (v - z_j), j = J-2..0.
-// H_j^T = R_j^T C_j^T; each 1-D transpose gathers the taps that the mirror
-// boundary folded onto the target pixel.
-// --------------------------------------------------------------------------
-
-__device__ __forceinline__ float mirrorT_gather(const float *__restrict__ u, long long stride, int i,
-                                                int N, int d, const float *__restrict__ zsub,
-                                                bool sub)
-{
-    // sum over taps t of w_t * u'(y) for every y with mirror(y + t d) == i,
-    // where u' = u - zsub (if sub).
-    float acc = 0.f;
-    #pragma unroll
-    for (int t = -2; t <= 2; ++t) {
-        const float w = kB3[t + 2];
-        int y = i - t * d;
-        if (y >= 0 && y < N) acc = fmaf(w, u[y * stride] - (sub ? zsub[y * stride] : 0.f), acc);
-        if (i > 0) {
-            y = -i - t * d;
-            if (y >= 0 && y < N) acc = fmaf(w, u[y * stride] - (sub ? zsub[y * stride] : 0.f), acc);
-        }
-        if (i < N - 1) {
-            y = 2 * (N - 1) - i - t * d;
-            if (y >= 0 && y < N) acc = fmaf(w, u[y * stride] - (sub ? zsub[y * stride] : 0.f), acc);
-        }
-    }
-    return acc;
-}
-
-// One level of the adjoint per launch on output tiles: u = v - z_j, the
-// column transpose C_j^T u on the tile's rows for every column the row
-// transpose reaches (kept in LDS), then vout = z_j + R_j^T of it.
-__global__ __launch_bounds__(kStarThreads) void k_star_levelT(const float *__restrict__ v,
-                                                              const float *__restrict__ zj,
-                                                              float *__restrict__ vout, int N, int d,
-                                                              long long v_stride, long long out_stride,
-                                                              long long z_stride)
-{
-    extern __shared__ float tmp[];  // kStarTile rows x (kStarTile + 4d) columns, or [5][tile] (d > kStarTile)
-    // a batch of images along blockIdx.z
-    v += blockIdx.z * v_stride;
-    vout += blockIdx.z * out_stride;
-    zj += blockIdx.z * z_stride;
-    const int x0 = blockIdx.x * kStarTile, y0 = blockIdx.y * kStarTile;
-    const int yl = threadIdx.x / kStarTile, xl = threadIdx.x % kStarTile;
-    const int y = y0 + yl, x = x0 + xl;
-    if (d > kStarTile) {
-        // the taps' column sets apart: stage, per tap t and output (y, x), the column
-        // transpose summed over the columns the row transpose gathers for that tap
-        // (x - t d and its mirror images; one of them away from the edges)
-        constexpr int TT = kStarTile * kStarTile;
-        for (int e = threadIdx.x; e < 5 * TT; e += kStarThreads) {
-            const int t = e / TT - 2, rem = e % TT, y2 = y0 + rem / kStarTile, x2 = x0 + rem % kStarTile;
-            float acc = 0.f;
-            if (y2 < N && x2 < N) {
-                int xc = x2 - t * d;
-                if (xc >= 0 && xc < N) acc += mirrorT_gather(v + xc, N, y2, N, d, zj + xc, true);
-                if (x2 > 0) {
-                    xc = -x2 - t * d;
-                    if (xc >= 0 && xc < N) acc += mirrorT_gather(v + xc, N, y2, N, d, zj + xc, true);
-                }
-                if (x2 < N - 1) {
-                    xc = 2 * (N - 1) - x2 - t * d;
-                    if (xc >= 0 && xc < N) acc += mirrorT_gather(v + xc, N, y2, N, d, zj + xc, true);
-                }
-            }
-            tmp[e] = acc;
-        }
-        __syncthreads();
-        if (y >= N || x >= N) return;
-        float acc = 0.f;
-        #pragma unroll
-        for (int t = -2; t <= 2; ++t) acc = fmaf(kB3[t + 2], tmp[(t + 2) * TT + yl * kStarTile + xl], acc);
-        const long long pix = (long long)y * N + x;
-        vout[pix] = zj[pix] + acc;
-        return;
-    }
-    const int C = kStarTile + 4 * d, cx0 = x0 - 2 * d;
-    for (int e = threadIdx.x; e < kStarTile * C; e += kStarThreads) {
-        const int yl2 = e / C, c = e - yl2 * C;
-        const int y2 = y0 + yl2, xc = cx0 + c;
-        float acc = 0.f;
-        if (y2 < N && xc >= 0 && xc < N) acc = mirrorT_gather(v + xc, N, y2, N, d, zj + xc, true);
-        tmp[e] = acc;
-    }
-    __syncthreads();
-    if (y >= N || x >= N) return;
-    // the row transpose gathers tmp at every column xc with mirror(xc + t d) == x;
-    // all of them lie in [x0 - 2d, x0 + kStarTile + 2d)
-    const float *row = tmp + yl * C - cx0;  // indexed by image column
-    float acc = 0.f;
-    #pragma unroll
-    for (int t = -2; t <= 2; ++t) {
-        const float w = kB3[t + 2];
-        int xc = x - t * d;
-        if (xc >= 0 && xc < N) acc = fmaf(w, row[xc], acc);
-        if (x > 0) {
-            xc = -x - t * d;
-            if (xc >= 0 && xc < N) acc = fmaf(w, row[xc], acc);
-        }
-        if (x < N - 1) {
-            xc = 2 * (N - 1) - x - t * d;
-            if (xc >= 0 && xc < N) acc = fmaf(w, row[xc], acc);
-        }
-    }
-    const long long pix = (long long)y * N + x;
-    vout[pix] = zj[pix] + acc;
-}
-
-__global__ void k_copy(const float *__restrict__ a, float *__restrict__ b, long long n)
-{
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = a[i];
-}
-
-// The prior of B (1 or 2) images img [B][N][N] at once: subgradients z [B][J][N][N]
-// and L1 partials (image b's at part_l1 + b (J-1) tiles), image 0 weighted by
-// lam0 and image 1 by lam1; c_a and c_b hold B images each.
-hipError_t launch_starlet_prior(hipStream_t st, int N, int J, int B, const float *img, float *z, const float *W,
-                                int w_stride, float lam0, float lam1, float *c_a, float *c_b, double *part_l1,
-                                int *n_l1)
-{
-    const long long NN = (long long)N * N;
-    if (J == 1) {
-        int nl = 0;
-        for (int b = 0; b < B; ++b) {
-            hipError_t e = launch_starlet_fwd(st, N, J, img + b * NN, nullptr, z ? z + b * NN : nullptr, W, w_stride,
-                                              b ? lam1 : lam0, c_a, c_b, nullptr, part_l1 ? part_l1 + nl : nullptr,
-                                              n_l1);
-            if (e != hipSuccess) return e;
-            nl += n_l1 ? *n_l1 : 0;
-        }
-        if (n_l1) *n_l1 = nl;
-        return hipSuccess;
-    }
-    const int nt = star_tiles(N);
-    const long long l1s = (long long)(J - 1) * nt * nt;
-    const float *cur = img;
-    for (int j = 0; j < J - 1; ++j) {
-        float *nxt = (j % 2 == 0) ? c_a : c_b;
-        const int d = 1 << j;
-        const size_t lds = star_lds(d);
-        hipLaunchKernelGGL(k_star_level, dim3(nt, nt, B), dim3(kStarThreads), lds, st, cur, nxt, nullptr, z, W,
-                           w_stride, lam0, N, d, j, (int)(j == J - 2),
-                           part_l1 ? part_l1 + (long long)j * nt * nt : nullptr, NN, (long long)J * NN, lam1, l1s);
-        cur = nxt;
-    }
-    if (n_l1) *n_l1 = (int)(B * l1s);
-    return hipGetLastError();
-}
-
-// Coefficients of B images (img [B][N][N] -> coeffs [B][J][N][N]); c_a and c_b
-// hold B images each. J = 1 is not handled here (the coefficients are the image).
-hipError_t launch_starlet_fwd_batch(hipStream_t st, int N, int J, int B, const float *img, float *coeffs,
-                                    float *c_a, float *c_b, const float *wzero)
-{
-    const long long NN = (long long)N * N;
-    const int nt = star_tiles(N);
-    const float *cur = img;
-    for (int j = 0; j < J - 1; ++j) {
-        float *nxt = (j % 2 == 0) ? c_a : c_b;
-        const int d = 1 << j;
-        const size_t lds = star_lds(d);
-        hipLaunchKernelGGL(k_star_level, dim3(nt, nt, B), dim3(kStarThreads), lds, st, cur, nxt, coeffs,
-                           nullptr, wzero, 0, 0.f, N, d, j, (int)(j == J - 2), nullptr, NN, (long long)J * NN,
-                           0.f, 0LL);
-        cur = nxt;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_starlet_adj(hipStream_t st, int N, int J, const float *z, float *out,
-                              float *v_a, float *v_b, float *)
-{
-    const long long NN = (long long)N * N;
-    const int nb = (int)((NN + kStarThreads - 1) / kStarThreads);
-    if (J == 1) {
-        hipLaunchKernelGGL(k_copy, dim3(nb), dim3(kStarThreads), 0, st, z, out, NN);
-        return hipGetLastError();
-    }
-    const int nt = star_tiles(N);
-    const float *v = z + (J - 1) * NN;
-    for (int j = J - 2; j >= 0; --j) {
-        float *vn = (j == 0) ? out : ((j % 2 == 0) ? v_a : v_b);
-        const int d = 1 << j;
-        const size_t lds = star_lds(d);
-        hipLaunchKernelGGL(k_star_levelT, dim3(nt, nt), dim3(kStarThreads), lds, st, v, z + j * NN, vn, N, d, 0LL,
-                           0LL, 0LL);
-        v = vn;
-    }
-    return hipGetLastError();
-}
-
-// Adjoint of B images at once: z [B][J][N][N] -> out [B][N][N]; v_a, v_b hold B images.
-hipError_t launch_starlet_adj_batch(hipStream_t st, int N, int J, int B, const float *z, float *out, float *v_a,
-                                    float *v_b)
-{
-    const long long NN = (long long)N * N;
-    if (J == 1) {
-        for (int b = 0; b < B; ++b) {
-            hipError_t e = launch_starlet_adj(st, N, J, z + b * NN, out + b * NN, v_a, v_b, nullptr);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
-    }
-    const int nt = star_tiles(N);
-    const float *v = z + (J - 1) * NN;
-    for (int j = J - 2; j >= 0; --j) {
-        float *vn = (j == 0) ? out : ((j % 2 == 0) ? v_a : v_b);
-        const int d = 1 << j;
-        const size_t lds = star_lds(d);
-        // the first level reads plane J-1 of each image's z: stride J N^2 for it, N^2 after
-        hipLaunchKernelGGL(k_star_levelT, dim3(nt, nt, B), dim3(kStarThreads), lds, st, v, z + j * NN, vn, N, d,
-                           (j == J - 2) ? (long long)J * NN : NN, NN, (long long)J * NN);
-        v = vn;
-    }
     return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 #include "starred_fft.h"
 #include "starred_finalize.h"
 #include "starred_internal.h"
+#include "starred_scales.h"
 
 #include <hip/hip_runtime.h>
 
@@ -89,7 +90,8 @@ struct starred_plan {
     float *d_kf = nullptr, *d_ka = nullptr;
     float *d_scene = nullptr, *d_rho = nullptr, *d_g = nullptr;
     double *d_part_chi = nullptr, *d_part_l1 = nullptr, *d_fsum = nullptr;
-    float *d_z = nullptr, *d_ca = nullptr, *d_cb = nullptr, *d_tmp = nullptr, *d_prior = nullptr;
+    float *d_z = nullptr, *d_prior = nullptr;
+    double *d_ca = nullptr, *d_cb = nullptr;  // starlet planes between the passes
     // Eq. 11, third term: weight, [h | P] images, shares of dL/da and dL/dc (3M)
     double lam_pts = 0.0;
     float *d_pair = nullptr;
@@ -99,11 +101,9 @@ struct starred_plan {
     float *est_img = nullptr;
     double *est_part = nullptr, *est_out = nullptr;
     float *d_grad = nullptr;
-    float *d_wzero = nullptr;
     // the prior through the per-scale composite filters (when they fit): taps and
-    // the row-filtered, smoothed and adjoint planes, for up to dense_b images
+    // the row-filtered, smoothed and adjoint planes
     bool dense = false;
-    int dense_b = 0;
     double *d_dense_taps = nullptr, *d_dense_T = nullptr, *d_dense_C = nullptr, *d_dense_U = nullptr;
     float *d_hpart = nullptr;
     int hpart_chunks = 0;  // partial planes d_hpart holds
@@ -331,14 +331,32 @@ static int validate(const starred_desc *d)
     return STARRED_OK;
 }
 
-// The composite-filter prior: taps and planes for up to B images, when the
-// grid and the scale count fit it (else the prior runs the cascade).
-static int dense_setup(starred_plan *p, int B)
+// The starlet transform of B images (image 0 at img, the others at d_pair + N^2) with the
+// plan's weights: which outputs it has is the caller's to set.
+static StarArgs star_args(const starred_plan *p, int B, const float *img)
+{
+    StarArgs a;
+    a.N = p->N;
+    a.J = p->J;
+    a.B = B;
+    a.fp64 = star_fp64(p->N, p->J);
+    a.img = img;
+    a.img1 = p->d_pair ? p->d_pair + (size_t)p->N * p->N : nullptr;
+    a.w_stride = p->w_stride;
+    a.lam0 = (float)p->lam;
+    a.lam1 = (float)p->lam_pts;
+    a.ca = p->d_ca;
+    a.cb = p->d_cb;
+    return a;
+}
+
+// The composite-filter prior, whose passes ride in the step's launches: taps and planes,
+// when the grid and the scale count fit it.
+static int dense_setup(starred_plan *p)
 {
     p->dense = dense_fits(p->N, p->J);
     if (!p->dense) return STARRED_OK;
-    p->dense_b = B;
-    const size_t planes = (size_t)B * p->J * p->N * p->N;
+    const size_t planes = (size_t)p->J * p->N * p->N;
     int rc;
     if ((rc = p->alloc(&p->d_dense_taps, (size_t)dense_num_taps(p->J)))) return rc;
     if ((rc = p->alloc(&p->d_dense_T, planes))) return rc;
@@ -350,12 +368,12 @@ static int dense_setup(starred_plan *p, int B)
     return STARRED_OK;
 }
 
-static DenseStar dense_desc(const starred_plan *p, int B, const float *img)
+static DenseStar dense_desc(const starred_plan *p, const float *img)
 {
     DenseStar d;
     d.N = p->N;
     d.J = p->J;
-    d.B = B;
+    d.B = 1;
     d.rx = dense_rows_per_job(p->N);
     d.taps = p->d_dense_taps;
     d.img = img;
@@ -364,13 +382,8 @@ static DenseStar dense_desc(const starred_plan *p, int B, const float *img)
     d.U = p->d_dense_U;
     d.W = p->W;
     d.w_stride = p->w_stride;
-    d.lam0 = d.lam1 = (float)p->lam;
+    d.lam0 = (float)p->lam;
     return d;
-}
-
-static size_t dense_l1_slots(const starred_plan *p)
-{
-    return p->dense ? (size_t)dense_desc(p, p->dense_b, nullptr).l1_slots() : 0;
 }
 
 static int build_deconv(starred_plan *p)
@@ -424,9 +437,10 @@ static int build_deconv(starred_plan *p)
     if ((rc = p->alloc(&p->d_scene, p->nfine))) return rc;
     if ((rc = p->alloc(&p->d_rho, p->ndata))) return rc;
     if ((rc = p->alloc(&p->d_g, p->nfine))) return rc;
-    if ((rc = dense_setup(p, 2))) return rc;
-    if ((rc = p->alloc(&p->d_part_l1, std::max((size_t)2 * starlet_l1_slots(p->N, p->J), dense_l1_slots(p)))))
-        return rc;
+    if ((rc = dense_setup(p))) return rc;
+    size_t l1 = (size_t)2 * star_l1_slots(star_args(p, 2, nullptr));
+    if (p->dense) l1 = std::max(l1, (size_t)dense_desc(p, nullptr).l1_slots());
+    if ((rc = p->alloc(&p->d_part_l1, l1))) return rc;
     if ((rc = p->alloc(&p->d_fsum, (size_t)E * (1 + 3 * p->M)))) return rc;
     // two images (h and the point-source image P of Eq. 11) for the prior buffers
     if ((rc = p->alloc(&p->d_z, (size_t)2 * p->J * NN))) return rc;
@@ -434,15 +448,12 @@ static int build_deconv(starred_plan *p)
     if ((rc = p->alloc(&p->d_cb, 2 * NN))) return rc;
     if ((rc = p->alloc(&p->d_pair, 2 * NN))) return rc;
     if ((rc = p->alloc(&p->d_pts, (size_t)3 * std::max(1, p->M)))) return rc;
-    if ((rc = p->alloc(&p->d_tmp, NN))) return rc;
     if ((rc = p->alloc(&p->d_prior, 2 * NN))) return rc;
     p->hpart_chunks = finalize_h_chunks(E);
     if ((rc = p->alloc(&p->d_hpart, (size_t)p->hpart_chunks * NN))) return rc;
     if ((rc = p->alloc(&p->d_gxfp, (size_t)xf_grad_parts(E)))) return rc;
     if ((rc = p->alloc(&p->d_hdir, NN))) return rc;
     if ((rc = p->alloc(&p->d_grad, p->nparams))) return rc;
-    if ((rc = p->alloc(&p->d_wzero, (size_t)p->J * NN))) return rc;
-    HIP_TRY(hipMemset(p->d_wzero, 0, sizeof(float) * p->J * NN));
     return STARRED_OK;
 }
 
@@ -963,16 +974,12 @@ static int build_psf(starred_plan *p)
     if ((rc = p->alloc(&p->d_rho, p->ndata))) return rc;
     if ((rc = p->alloc(&p->d_part_chi, (size_t)S * psf_fwd_tiles(n) * 4))) return rc;
     if ((rc = p->alloc(&p->d_part_eta, (size_t)psf_adj_tiles(N) * 5))) return rc;
-    if ((rc = dense_setup(p, 1))) return rc;
-    if ((rc = p->alloc(&p->d_part_l1, std::max((size_t)starlet_l1_slots(p->N, p->J), dense_l1_slots(p))))) return rc;
+    if ((rc = p->alloc(&p->d_part_l1, (size_t)star_l1_slots(star_args(p, 1, nullptr))))) return rc;
     if ((rc = p->alloc(&p->d_z, (size_t)p->J * NN))) return rc;
     if ((rc = p->alloc(&p->d_ca, NN))) return rc;
     if ((rc = p->alloc(&p->d_cb, NN))) return rc;
-    if ((rc = p->alloc(&p->d_tmp, NN))) return rc;
     if ((rc = p->alloc(&p->d_prior, NN))) return rc;
     if ((rc = p->alloc(&p->d_grad, p->nparams))) return rc;
-    if ((rc = p->alloc(&p->d_wzero, (size_t)p->J * NN))) return rc;
-    HIP_TRY(hipMemset(p->d_wzero, 0, sizeof(float) * p->J * NN));
     return STARRED_OK;
 }
 
@@ -1343,27 +1350,19 @@ int starred_convolve_subsample_adj(starred_plan *p, const float *resid, float *g
 int starred_starlet_fwd(starred_plan *p, const float *img, float *coeffs)
 {
     if (!p || !img || !coeffs) return fail(STARRED_EINVAL, "NULL argument");
-    if (p->dense) {
-        HIP_TRY(launch_dense_coeffs(p->st, dense_desc(p, 1, img), coeffs));
-        return STARRED_OK;
-    }
-    // the transform alone: zero weights, no L1 partials, no subgradient
-    HIP_TRY(launch_starlet_fwd(p->st, p->N, p->J, img, coeffs, nullptr, p->d_wzero, 0, 0.f,
-                               p->d_ca, p->d_cb, p->d_tmp, nullptr, nullptr));
+    StarArgs a = star_args(p, 1, img);
+    a.coeffs = coeffs;  // the transform alone: no weights
+    HIP_TRY(launch_star_forward(p->st, a));
     return STARRED_OK;
 }
 
 int starred_starlet_adj(starred_plan *p, const float *coeffs, float *img)
 {
     if (!p || !coeffs || !img) return fail(STARRED_EINVAL, "NULL argument");
-    if (p->dense) {
-        DenseStar d = dense_desc(p, 1, nullptr);
-        d.zin = coeffs;
-        d.out = img;
-        HIP_TRY(launch_dense_adjoint(p->st, d));
-        return STARRED_OK;
-    }
-    HIP_TRY(launch_starlet_adj(p->st, p->N, p->J, coeffs, img, p->d_ca, p->d_cb, p->d_tmp));
+    StarArgs a = star_args(p, 1, nullptr);
+    a.z = const_cast<float *>(coeffs);  // (only read)
+    a.out = img;
+    HIP_TRY(launch_star_adjoint(p->st, a));
     return STARRED_OK;
 }
 
@@ -1376,37 +1375,19 @@ int starred_starlet_adj(starred_plan *p, const float *coeffs, float *img)
 // gradient's shares of dL/da and dL/dc land in d_pts.
 static int prior_launches(starred_plan *p, hipStream_t st, const float *img, bool want_grad, int *n_l1)
 {
-    if (p->dense) {
-        // every scale from the image(s) directly: four passes over all scales
-        const bool pts = p->mode == STARRED_DECONV && p->lam_pts != 0.0;
-        const long long NN = (long long)p->N * p->N;
-        if (pts) HIP_TRY(launch_pts_render(st, p->N, p->E, p->M, p->sigma, img, nullptr, p->d_pair + NN));
-        DenseStar d = dense_desc(p, pts ? 2 : 1, img);
-        if (pts) {
-            d.img1 = p->d_pair + NN;  // the point-source image
-            d.lam1 = (float)p->lam_pts;
-        }
-        d.part_l1 = p->d_part_l1;
-        d.out = want_grad ? p->d_prior : nullptr;
-        HIP_TRY(launch_dense_prior(st, d));
-        *n_l1 = d.l1_slots();
-        if (pts && want_grad) HIP_TRY(launch_pts_dots(st, p->N, p->E, p->M, p->sigma, img, p->d_prior + NN, p->d_pts));
-        return STARRED_OK;
-    }
-    if (p->mode == STARRED_DECONV && p->lam_pts != 0.0) {
-        const long long NN = (long long)p->N * p->N;
-        HIP_TRY(launch_pts_render(st, p->N, p->E, p->M, p->sigma, img, p->d_pair, p->d_pair + NN));
-        HIP_TRY(launch_starlet_prior(st, p->N, p->J, 2, p->d_pair, want_grad ? p->d_z : nullptr, p->W, p->w_stride,
-                                     (float)p->lam, (float)p->lam_pts, p->d_ca, p->d_cb, p->d_part_l1, n_l1));
-        if (want_grad) {
-            HIP_TRY(launch_starlet_adj_batch(st, p->N, p->J, 2, p->d_z, p->d_prior, p->d_ca, p->d_cb));
-            HIP_TRY(launch_pts_dots(st, p->N, p->E, p->M, p->sigma, img, p->d_prior + NN, p->d_pts));
-        }
-        return STARRED_OK;
-    }
-    HIP_TRY(launch_starlet_fwd(st, p->N, p->J, img, nullptr, want_grad ? p->d_z : nullptr, p->W, p->w_stride,
-                               (float)p->lam, p->d_ca, p->d_cb, p->d_tmp, p->d_part_l1, n_l1));
-    if (want_grad) HIP_TRY(launch_starlet_adj(st, p->N, p->J, p->d_z, p->d_prior, p->d_ca, p->d_cb, p->d_tmp));
+    const bool pts = p->mode == STARRED_DECONV && p->lam_pts != 0.0;
+    const long long NN = (long long)p->N * p->N;
+    if (pts) HIP_TRY(launch_pts_render(st, p->N, p->E, p->M, p->sigma, img, nullptr, p->d_pair + NN));
+    StarArgs a = star_args(p, pts ? 2 : 1, img);
+    a.W = p->W;
+    a.part_l1 = p->d_part_l1;
+    a.z = want_grad ? p->d_z : nullptr;
+    a.out = p->d_prior;
+    HIP_TRY(launch_star_forward(st, a));
+    *n_l1 = a.B * star_l1_slots(a);
+    if (!want_grad) return STARRED_OK;
+    HIP_TRY(launch_star_adjoint(st, a));
+    if (pts) HIP_TRY(launch_pts_dots(st, p->N, p->E, p->M, p->sigma, img, p->d_prior + NN, p->d_pts));
     return STARRED_OK;
 }
 
@@ -1472,9 +1453,9 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
     DensePiece pa, pb, pc, pd;
     DenseStar dd;
     if (ride) {
-        dd = dense_desc(p, 1, params);
+        dd = dense_desc(p, params);
         dd.part_l1 = p->d_part_l1;
-        dd.out = grad ? p->d_prior : nullptr;  // (pass C builds U_j only when set)
+        dd.want_grad = grad != nullptr;
         pa.d = pb.d = pd.d = dd;
         pc.d = dd;
         pc.d.rx = dense_rows_for(p->N, kFusedThreads);  // the forward's work groups are wider
@@ -1859,14 +1840,14 @@ static int psf_loss_grad_impl(starred_plan *p, const float *params, float *grad,
 {
     const int S = p->E, n = p->psf_n, N = p->N;
     int n_l1 = 0;
-    // the prior's branch first: its chain is about as long as the stars' (render, forward,
-    // adjoint), and launching it ahead of them measured faster than after the render
+    // the prior's branch forks here and is launched after the render (see starlet_fork)
     int rc = starlet_fork(p);
-    if (!rc) rc = starlet_launch(p, params + 5, grad != nullptr, &n_l1);
     if (rc) return rc;
     hipEvent_t e0 = p->prof_start();
     HIP_TRY(launch_psf_render64(p->st, N, params, p->d_s64, grad ? p->d_dm : nullptr, tick));
     p->prof_stop(STARRED_STAGE_RENDER, e0);
+    rc = starlet_launch(p, params + 5, grad != nullptr, &n_l1);
+    if (rc) return rc;
     e0 = p->prof_start();
     HIP_TRY(launch_psf_fwd(p->st, S, n, p->s, N, p->sigma, params, p->d_s64, p->data, p->invvar, p->d_rho,
                            p->d_part_chi));
@@ -2192,7 +2173,11 @@ int starred_estimate_lambda_pts(starred_plan *p, const float *params, double *la
     if (!p->frames_set) return fail(STARRED_ESTATE, "set_frames has not been called");
     if (p->M < 1) return fail(STARRED_EUNSUPPORTED, "no point sources");
     const long long NN = (long long)p->N * p->N;
-    const int B = p->M + 2, slots = starlet_l1_slots(p->N, p->J);
+    StarArgs sa = star_args(p, 1, nullptr);
+    sa.W = p->W;
+    sa.lam0 = 1.f;
+    sa.fp64 = false;
+    const int B = p->M + 2, slots = star_l1_slots(sa);
     if (!p->est_img) {
         int rc = p->alloc(&p->est_img, (size_t)B * NN);
         if (!rc) rc = p->alloc(&p->est_part, (size_t)B * slots);
@@ -2201,9 +2186,11 @@ int starred_estimate_lambda_pts(starred_plan *p, const float *params, double *la
     }
     HIP_TRY(launch_fill_d(p->st, p->est_part, (long long)B * slots));
     HIP_TRY(launch_pts_images(p->st, p->N, p->E, p->M, p->sigma, params, p->est_img));
-    for (int b = 0; b < B; ++b)
-        HIP_TRY(launch_starlet_fwd(p->st, p->N, p->J, p->est_img + b * NN, nullptr, nullptr, p->W, p->w_stride, 1.f,
-                                   p->d_ca, p->d_cb, p->d_tmp, p->est_part + (long long)b * slots, nullptr));
+    for (int b = 0; b < B; ++b) {
+        sa.img = p->est_img + b * NN;
+        sa.part_l1 = p->est_part + (long long)b * slots;
+        HIP_TRY(launch_star_forward(p->st, sa));
+    }
     HIP_TRY(launch_pts_sums(p->st, B, slots, p->est_part, p->N, p->E, p->M, params, p->est_out));
     std::vector<double> h(B + p->M);
     HIP_TRY(hipMemcpyAsync(h.data(), p->est_out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, p->st));
@@ -2291,12 +2278,13 @@ int starred_noise_weights(starred_plan *p, int32_t frame, const float *sigma2_da
         int rc = starred_convolve_subsample_adj(p->noise_aux, p->nz_delta, p->nz_g);
         if (rc) return rc;
         HIP_TRY(launch_noise_embed(p->st, B, F, N, o, p->nz_g, p->nz_img));
-        if (J == 1) {
-            HIP_TRY(hipMemcpyAsync(p->nz_coef, p->nz_img, sizeof(float) * B * NN, hipMemcpyDeviceToDevice, p->st));
-        } else {
-            HIP_TRY(launch_starlet_fwd_batch(p->st, N, J, nb, p->nz_img, p->nz_coef, p->nz_ca, p->nz_cb,
-                                             p->d_wzero));
-        }
+        StarArgs a = star_args(p, nb, p->nz_img);
+        a.fp64 = false;  // as the fields are
+        a.img1 = p->nz_img + NN;
+        a.coeffs = p->nz_coef;
+        a.ca = p->nz_ca;
+        a.cb = p->nz_cb;
+        HIP_TRY(launch_star_forward(p->st, a));
         HIP_TRY(launch_noise_moments(p->st, nb, (long long)J * NN, p->nz_coef, p->nz_s1, p->nz_s2));
     }
     HIP_TRY(launch_noise_finish(p->st, J, NN, n_real, per_pixel, p->nz_s1, p->nz_s2, W_out));

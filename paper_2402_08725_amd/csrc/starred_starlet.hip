@@ -1,8 +1,8 @@
-// Starlet prior through the per-scale composite filters (starred_dense.h):
-// standalone launches of the four passes, the coefficient and adjoint forms,
-// and the host-side construction of the composite taps.
+// Launches of the starlet passes (starred_scales.h), and the host side of the
+// composite-filter passes that ride in other launches (starred_dense.h).
 #include "starred_dense.h"
 #include "starred_internal.h"
+#include "starred_scales.h"
 
 #include <hip/hip_runtime.h>
 
@@ -10,41 +10,101 @@
 
 namespace starred {
 
-__global__ __launch_bounds__(kDenseThreads) void k_dense_a(DenseStar d)
+template <class V, int L, int T, int NT>
+__global__ __launch_bounds__(NT) void k_star_forward(StarArgs a, int g)
 {
     extern __shared__ double lds[];
-    dense_job_a(d, blockIdx.x, lds);
+    __shared__ double red[NT / 64];
+    star_forward<V, L, T, NT>(a, g, blockIdx.x, (V *)lds, red);
 }
 
-__global__ __launch_bounds__(kDenseThreads) void k_dense_b(DenseStar d)
+template <class V, int L, int T, int NT>
+__global__ __launch_bounds__(NT) void k_star_adjoint(StarArgs a, int g)
 {
     extern __shared__ double lds[];
-    dense_job_b(d, blockIdx.x, lds);
+    star_adjoint<V, L, T, NT>(a, g, blockIdx.x, (V *)lds);
 }
 
-__global__ __launch_bounds__(kDenseThreads) void k_dense_c(DenseStar d)
+// J = 1: the only plane is the image itself.
+__global__ __launch_bounds__(256) void k_star_plane(StarArgs a)
 {
-    extern __shared__ double lds[];
-    __shared__ double red[kDenseThreads / 64];
-    dense_job_c(d, blockIdx.x, lds, red);
+    __shared__ double red[256 / 64];
+    const long long NN = (long long)a.N * a.N, pix = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int b = blockIdx.y;
+    const float lam = b ? a.lam1 : a.lam0;
+    double l1 = 0.0;
+    if (pix < NN) {
+        const float al = a.image(b)[pix];
+        if (a.coeffs) a.coeffs[b * NN + pix] = al;
+        if (a.W) {
+            const float w = a.w_stride ? a.W[pix] : a.W[0];
+            if (a.z) a.z[b * NN + pix] = lam * w * (float)((al > 0.f) - (al < 0.f));
+            l1 = (double)lam * (double)w * (double)fabsf(al);
+        }
+    }
+    if (a.part_l1) {
+        const double s = star_block_sum(l1, red);
+        if (threadIdx.x == 0) a.part_l1[(long long)b * gridDim.x + blockIdx.x] = s;
+    }
 }
 
-__global__ __launch_bounds__(kDenseThreads) void k_dense_d(DenseStar d)
+__global__ void k_copy(const float *__restrict__ a, float *__restrict__ b, long long n)
 {
-    extern __shared__ double lds[];
-    dense_job_d(d, blockIdx.x, lds);
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) b[i] = a[i];
 }
 
-// alpha_j (FP32) of every scale: [B][J][N][N]
-__global__ void k_dense_coeffs(DenseStar d, float *coeffs)
+bool star_fp64(int N, int J) { return N <= kStarSmall && J <= kStarFewPlanes; }
+
+int star_l1_slots(const StarArgs &a)
 {
-    const long long NN = (long long)d.N * d.N, n = (long long)d.B * d.J * NN;
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    const int b = (int)(e / (d.J * NN)), j = (int)((e / NN) % d.J);
-    const long long pix = e % NN;
-    coeffs[e] = (float)dense_alpha(d, b, j, (int)(pix / d.N), (int)(pix % d.N));
+    return a.J == 1 ? (int)(((long long)a.N * a.N + 255) / 256) : a.l1_slots();
 }
+
+// tiles of 16 on 512 threads (two waves per SIMD hide more than one), of 32 on 1024
+#define STAR_LAUNCH_L(KERNEL, V, L)                                                                             \
+    if (q.T == kStarTile)                                                                                       \
+        hipLaunchKernelGGL((KERNEL<V, L, kStarTile, 512>), grid, dim3(512), q.lds(), st, a, g);                 \
+    else                                                                                                        \
+        hipLaunchKernelGGL((KERNEL<float, L, kStarTileLarge, 1024>), grid, dim3(1024), q.lds(), st, a, g)
+#define STAR_LAUNCH(KERNEL)                                          \
+    do {                                                             \
+        const StarArgs::Group q = a.group(g);                        \
+        const dim3 grid(a.B * q.jobs());                             \
+        switch (q.L + (a.fp64 ? 8 : 0)) {                            \
+        case 1: STAR_LAUNCH_L(KERNEL, float, 1); break;              \
+        case 2: STAR_LAUNCH_L(KERNEL, float, 2); break;              \
+        case 3: STAR_LAUNCH_L(KERNEL, float, 3); break;              \
+        case 4: STAR_LAUNCH_L(KERNEL, float, 4); break;              \
+        case 9: STAR_LAUNCH_L(KERNEL, double, 1); break;             \
+        case 10: STAR_LAUNCH_L(KERNEL, double, 2); break;            \
+        case 11: STAR_LAUNCH_L(KERNEL, double, 3); break;            \
+        default: return hipErrorInvalidValue;                        \
+        }                                                            \
+    } while (0)
+
+hipError_t launch_star_forward(hipStream_t st, const StarArgs &a)
+{
+    if (a.J == 1) {
+        hipLaunchKernelGGL(k_star_plane, dim3(star_l1_slots(a), a.B), dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
+    for (int g = 0; g < star_num_groups(a.J); ++g) STAR_LAUNCH(k_star_forward);
+    return hipGetLastError();
+}
+
+hipError_t launch_star_adjoint(hipStream_t st, const StarArgs &a)
+{
+    const long long n = (long long)a.B * a.N * a.N;
+    if (a.J == 1) {
+        hipLaunchKernelGGL(k_copy, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a.z, a.out, n);
+        return hipGetLastError();
+    }
+    for (int g = star_num_groups(a.J) - 1; g >= 0; --g) STAR_LAUNCH(k_star_adjoint);
+    return hipGetLastError();
+}
+
+// ---- composite filters: LDS, shapes and taps ----
 
 size_t dense_lds_xr(int N, int J, int rx)
 {
@@ -58,13 +118,6 @@ size_t dense_lds_y(int J)
     return sizeof(double) * (kDenseTile * (size_t)(kDenseTile + 2 * DenseStar::bw(J - 1)) + kDenseYTail);
 }
 
-size_t dense_lds_d(int J)
-{
-    size_t n = kDenseYTail;
-    for (int j = 1; j < J; ++j) n += (size_t)(kDenseTile + 2 * DenseStar::bw(j)) * kDenseTile;
-    return sizeof(double) * n;
-}
-
 int dense_rows_for(int N, int threads) { return N >= threads ? 1 : threads / N; }
 
 int dense_rows_per_job(int N) { return dense_rows_for(N, kDenseThreads); }
@@ -72,7 +125,7 @@ int dense_rows_per_job(int N) { return dense_rows_for(N, kDenseThreads); }
 bool dense_fits(int N, int J)
 {
     return J >= 2 && J <= kDenseMaxJ - 1 && N <= kDenseMaxN && DenseStar::bw(J - 1) <= N - 1 &&
-           dense_lds_d(J) <= kDenseMaxLds && dense_lds_x(N, J) <= kDenseMaxLds;
+           dense_lds_y(J) <= kDenseMaxLds && dense_lds_x(N, J) <= kDenseMaxLds;
 }
 
 int dense_num_taps(int J) { return J >= 2 ? DenseStar::toff(J) : 0; }
@@ -90,41 +143,6 @@ void dense_taps(int J, double *out)
         a.swap(n);
         for (int i = 0; i < DenseStar::plen(j); ++i) out[DenseStar::toff(j) + i] = i < (int)a.size() ? a[i] : 0.0;
     }
-}
-
-static hipError_t dense_launch(void (*k)(DenseStar), int jobs, size_t lds, hipStream_t st, const DenseStar &d)
-{
-    if (jobs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k, dim3(jobs), dim3(kDenseThreads), lds, st, d);
-    return hipGetLastError();
-}
-
-hipError_t launch_dense_prior(hipStream_t st, const DenseStar &d)
-{
-    hipError_t e;
-    if ((e = dense_launch(k_dense_a, d.jobs_a(), dense_lds_x(d.N, d.J), st, d)) != hipSuccess) return e;
-    if ((e = dense_launch(k_dense_b, d.jobs_b(), dense_lds_y(d.J), st, d)) != hipSuccess) return e;
-    if ((e = dense_launch(k_dense_c, d.jobs_c(), dense_lds_x(d.N, d.J), st, d)) != hipSuccess) return e;
-    if (!d.out) return hipSuccess;
-    return dense_launch(k_dense_d, d.jobs_d(), dense_lds_d(d.J), st, d);
-}
-
-hipError_t launch_dense_coeffs(hipStream_t st, const DenseStar &d, float *coeffs)
-{
-    hipError_t e;
-    if ((e = dense_launch(k_dense_a, d.jobs_a(), dense_lds_x(d.N, d.J), st, d)) != hipSuccess) return e;
-    if ((e = dense_launch(k_dense_b, d.jobs_b(), dense_lds_y(d.J), st, d)) != hipSuccess) return e;
-    const long long n = (long long)d.B * d.J * d.N * d.N;
-    hipLaunchKernelGGL(k_dense_coeffs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d, coeffs);
-    return hipGetLastError();
-}
-
-hipError_t launch_dense_adjoint(hipStream_t st, const DenseStar &d)
-{
-    if (!d.zin || !d.out) return hipErrorInvalidValue;
-    hipError_t e;
-    if ((e = dense_launch(k_dense_c, d.jobs_c(), dense_lds_x(d.N, d.J), st, d)) != hipSuccess) return e;
-    return dense_launch(k_dense_d, d.jobs_d(), dense_lds_d(d.J), st, d);
 }
 
 }  // namespace starred

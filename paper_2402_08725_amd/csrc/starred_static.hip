@@ -5,6 +5,7 @@
 // is looked up once per device; inputs and outputs are the caller's.
 #include "starred.h"
 #include "starred_internal.h"
+#include "starred_scales.h"
 
 #include <hip/hip_runtime.h>
 
@@ -16,23 +17,16 @@ using namespace starred;
 
 namespace {
 
-// Two smoothed planes c_a, c_b of the cascade (N^2 floats each, N <= kStaticMaxSide)
-// followed by the J per-scale weights the transform-only launch reads (zero).
+// The planes between the transform's passes (two of N^2 floats, N <= kStaticMaxSide).
 constexpr int kStaticMaxSide = 512;
 constexpr int kStaticMaxScales = 16;
-constexpr size_t kScratchFloats = 2 * (size_t)kStaticMaxSide * kStaticMaxSide + kStaticMaxScales;
+constexpr size_t kScratchFloats = 2 * (size_t)kStaticMaxSide * kStaticMaxSide + 16;
 
 static __device__ __align__(256) float scratch[kScratchFloats];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
 float *g_ptr[kMaxDevices] = {};
-
-__global__ void k_zero(float *p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.f;
-}
 
 }  // namespace
 
@@ -68,14 +62,16 @@ extern "C" int starred_starlet_fwd_noalloc(int32_t N, int32_t J, const float *im
         base = g_ptr[dev];
     }
     hipStream_t st = (hipStream_t)stream;
-    const size_t NN = (size_t)N * N;
-    float *c_a = base, *c_b = base + NN, *wz = base + 2 * NN;
-    // the weights the transform-only launch reads must be zero: a fill kernel
-    // (every call, since calls share the array)
-    hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, wz, J);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = launch_starlet_fwd(st, N, J, img, coeffs, nullptr, wz, 0, 0.f, c_a, c_b, nullptr,
-                                                nullptr, nullptr);
+    StarArgs a;
+    a.N = N;
+    a.J = J;
+    a.B = 1;
+    a.fp64 = false;  // the working planes are FP32
+    a.img = img;
+    a.coeffs = coeffs;
+    a.ca = base;
+    a.cb = base + (size_t)N * N;
+    e = launch_star_forward(st, a);
     if (e != hipSuccess) return starred_set_error(STARRED_EHIP, hipGetErrorString(e));
     return STARRED_OK;
 }
