@@ -182,14 +182,12 @@ struct FftPlanDev {
     float2 *tw = nullptr;
     float2 *S = nullptr, *T = nullptr, *T2 = nullptr, *Rh = nullptr, *T3 = nullptr;
     float2 *Th = nullptr, *Hh = nullptr, *tab = nullptr;
-    LinePass hrows, hcols, krows, kcols, fcols, frows, rrows, rcols, acols, arows, srows, scols;
+    LinePass hrows, hcols, krows, kcols, fcols, frows, rcols;
+    // operators on given scenes and residuals (rows in pairs; fold: columns of the Q grid)
+    LinePass srows, rrows, arows, fold;
     SpecItem *spec = nullptr;
     int n_spec = 0;
     int *cls_frames = nullptr;
-    // per-frame sums of g from the adjoint row pass: partial per line group and,
-    // for each frame, the list of its groups (CSR)
-    double *gpart = nullptr;
-    int *gcsr_off = nullptr, *gcsr_item = nullptr;
     // frequency-domain adjoint
     int n_frames = 0;
     AdjItem *aspec = nullptr;
@@ -211,9 +209,8 @@ struct FftPlanDev {
     size_t frame_lds = 0;
     LinePass fcols_lg, frows_lg, rcols_lg;
     // every frame, whatever its class runs: the per-frame convolution of rendered
-    // scenes (frames with per-frame transforms), and its per-group sums of g
-    LinePass srows_x, scols_x, fcols_x, frows_x, rcols_x, acols_x, arows_x;
-    double *gpart_x = nullptr;
+    // scenes (frames with per-frame transforms)
+    LinePass srows_x, fold_x, frows_x, arows_x;
 };
 
 // Deterministic block sum of one double per thread (NT threads); thread 0 holds it.
@@ -245,10 +242,7 @@ hipError_t fft_model_cols(hipStream_t st, const FftPlanDev &d);
 hipError_t fft_model_rows(hipStream_t st, const FftPlanDev &d, const float *data, const float *invvar,
                           double *part_chi, float *model, bool want_rho = true);
 hipError_t fft_rho_cols(hipStream_t st, const FftPlanDev &d);
-hipError_t fft_adj_cols(hipStream_t st, const FftPlanDev &d);
-hipError_t fft_adj_rows(hipStream_t st, const FftPlanDev &d, float *g);
-hipError_t fft_resid_rows(hipStream_t st, const FftPlanDev &d, const float *resid);
-hipError_t fft_adjoint(hipStream_t st, const FftPlanDev &d, float *g);
+hipError_t fft_scene_adjoint(hipStream_t st, const FftPlanDev &d, const float *resid, int s, float *g);
 hipError_t fft_spec_adj(hipStream_t st, const FftPlanDev &d, int M, int s);
 hipError_t fft_adj_sums(hipStream_t st, const FftPlanDev &d, int M, double *fsum);
 struct FinalArgs;
@@ -283,10 +277,11 @@ hipError_t fft_grad_h_inverse(hipStream_t st, const FftPlanDev &d, DensePiece *p
 hipError_t fft_scene_model(hipStream_t st, const FftPlanDev &d, const float *scene, int s, float *model);
 // Frames with per-frame transforms: S_i and D of each frame's rendered scene (fine
 // grid, per-frame layout) through its own spectrum, the weighted residual and its
-// chi-square partials (one per row group of frows_x), rho_hat kept for the adjoint.
+// chi-square partials (one per row group of frows_x), the residuals' row spectra kept for
+// the adjoint.
 hipError_t fft_xf_forward(hipStream_t st, const FftPlanDev &d, const float *scene, int s, const float *data,
                           const float *invvar, double *part_chi);
 // ... and D^T S_i^T of those residuals into g (fine grid, per-frame layout).
-hipError_t fft_xf_adjoint(hipStream_t st, const FftPlanDev &d, float *g);
+hipError_t fft_xf_adjoint(hipStream_t st, const FftPlanDev &d, int s, float *g);
 
 }  // namespace starred

@@ -305,20 +305,52 @@ __global__ __launch_bounds__(kFftThreads) void k_lines(const LineItem *__restric
     }
     __syncthreads();
     float2 *r = lds_fft_any<Op::inverse>(a, b, it.nl, f, tw + f.tw_off);
-    double acc = 0.0;
     for (int e = threadIdx.x; e < tot; e += blockDim.x) {
         int l, j;
         if (Op::col) { l = e % it.nl; j = e / it.nl; }
         else { l = e / f.L; j = e - l * f.L; }
-        if constexpr (Op::rowsum)
-            acc += (double)op.store(cl, it.frame, it.line0 + l, j, r[l * Ls + j]);
-        else
-            op.store(cl, it.frame, it.line0 + l, j, r[l * Ls + j]);
+        op.store(cl, it.frame, it.line0 + l, j, r[l * Ls + j]);
     }
-    if constexpr (Op::rowsum) {
-        __shared__ double red[kFftThreads / 64];
-        const double tot_sum = block_sum_d_fft(acc, red);
-        if (threadIdx.x == 0) op.gpart[blockIdx.x] = tot_sum;
+}
+
+// Row passes of the per-frame operators, two real rows per complex transform (line p of an
+// item is the pair 2p, 2p + 1; a missing second row is zero): half the transforms of a row
+// each. Forward: the pair's spectrum Z is split, X0 = (Z(k) + conj Z(-k)) / 2 and
+// X1 = (Z(k) - conj Z(-k)) / 2i; inverse: Z = X0 + i X1 gives both rows at once.
+template <class Op>
+__global__ __launch_bounds__(kFftThreads) void k_row_pairs(const LineItem *__restrict__ items,
+                                                           const ClassFft *__restrict__ classes,
+                                                           const float2 *__restrict__ tw, Op op)
+{
+    extern __shared__ float2 sm[];
+    const LineItem it = items[blockIdx.x];
+    const ClassFft &cl = classes[it.cls];
+    const FftLen &f = op.len(cl);
+    const int L = f.L, Ls = L + 1, H = L / 2 + 1, rows = op.rows(cl);
+    float2 *a = sm, *b = sm + it.nl * Ls;
+    for (int e = threadIdx.x; e < it.nl * L; e += kFftThreads) {
+        const int l = e / L, j = e - l * L, y = 2 * (it.line0 + l);
+        if constexpr (Op::inverse) {
+            const float2 x0 = op.load(cl, it.frame, y, j), x1 = y + 1 < rows ? op.load(cl, it.frame, y + 1, j) : make_float2(0.f, 0.f);
+            a[l * Ls + j] = make_float2(x0.x - x1.y, x0.y + x1.x);
+        } else {
+            a[l * Ls + j] = make_float2(op.load(cl, it.frame, y, j), y + 1 < rows ? op.load(cl, it.frame, y + 1, j) : 0.f);
+        }
+    }
+    __syncthreads();
+    const float2 *r = lds_fft_any<Op::inverse>(a, b, it.nl, f, tw + f.tw_off);
+    const int n = Op::inverse ? L : H;
+    for (int e = threadIdx.x; e < it.nl * n; e += kFftThreads) {
+        const int l = e / n, j = e - l * n, y = 2 * (it.line0 + l);
+        const float2 z = r[l * Ls + j];
+        if constexpr (Op::inverse) {
+            op.store(cl, it.frame, y, j, z.x);
+            if (y + 1 < rows) op.store(cl, it.frame, y + 1, j, z.y);
+        } else {
+            const float2 m = r[l * Ls + (j == 0 ? 0 : L - j)];
+            op.store(cl, it.frame, y, j, make_float2(0.5f * (z.x + m.x), 0.5f * (z.y - m.y)));
+            if (y + 1 < rows) op.store(cl, it.frame, y + 1, j, make_float2(0.5f * (z.y + m.y), 0.5f * (m.x - z.x)));
+        }
     }
 }
 
@@ -390,7 +422,6 @@ struct OpHRows {
                     blockDim.x * tb);
     }
     static constexpr bool col = false;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = false;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
     __device__ float2 load(const ClassFft &c, int, int y, int x) const
@@ -409,7 +440,6 @@ struct OpHCols {
     const float2 *Th;
     float2 *Hh;
     static constexpr bool col = true;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = false;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
     __device__ float2 load(const ClassFft &c, int, int kx, int y) const
@@ -430,7 +460,6 @@ struct OpKRows {
     int s;
     float2 *TS;
     static constexpr bool col = false;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = false;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
     __device__ float2 load(const ClassFft &c, int i, int y, int x) const
@@ -461,7 +490,6 @@ struct OpKCols {
     const float2 *TS;
     float2 *S;
     static constexpr bool col = true;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = false;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
     __device__ float2 load(const ClassFft &c, int i, int kx, int y) const
@@ -475,34 +503,105 @@ struct OpKCols {
     }
 };
 
-// ---- pass D: forward spectral product + alias fold + inverse along ky ----
-struct OpFwdCols {
-    const FrameFft *fr;
-    const float2 *S;
-    int s;
-    float2 *T;
-    const float2 *scene_spec;  // per-frame scene spectra [P][P/2+1]
-    static constexpr bool col = true;
-    static constexpr bool rowsum = false;
-    static constexpr bool inverse = true;
-    __device__ const FftLen &len(const ClassFft &c) const { return c.fQ; }
-    __device__ float2 load(const ClassFft &c, int i, int kx, int ky) const
-    {
-        const FrameFft &f = fr[i];
-        const int P = c.P, Q = c.Q;
-        const float2 *Si = S + f.s_off + (ky * (Q / 2 + 1) + kx) * s * s;
-        float2 acc = make_float2(0.f, 0.f);
-        for (int al = 0; al < s; ++al)
-            for (int be = 0; be < s; ++be)
-                acc = cadd(acc, cmul(Si[be * s + al], half_get(scene_spec + f.t3_off, P, ky + al * Q, kx + be * Q)));
-        return acc;
+// ---- per-frame operators on given scenes and residuals: the column passes ----
+// A line is a column kx of the Q grid with the s columns Kx = kx + bQ of the P grid that fold
+// onto it (Kx > P/2: the column P - Kx, mirrored and conjugated; the half plane's columns
+// are each used once, up to kx = 0 and Q/2). The P-point transforms, the product with S'' and
+// the Q-point transform run on one line in LDS: no spectrum of the P or Q grid goes through
+// memory between them.
+// LDS: two planes of nl lines of P + 1 (transform and scratch) and nl lines of Q + 1.
+
+// rows of scene spectra [F][P/2+1] -> rows of model spectra [n][Q/2+1]
+template <int S>
+__global__ __launch_bounds__(kFftThreads) void k_fold(const LineItem *__restrict__ items,
+                                                      const ClassFft *__restrict__ classes,
+                                                      const FrameFft *__restrict__ fr, const float2 *__restrict__ tw,
+                                                      const float2 *__restrict__ rowspec,
+                                                      const float2 *__restrict__ Sp, float2 *__restrict__ T)
+{
+    extern __shared__ float2 sm[];
+    const LineItem it = items[blockIdx.x];
+    const ClassFft &c = classes[it.cls];
+    const FrameFft &f = fr[it.frame];
+    const int P = c.P, Q = c.Q, HP = P / 2 + 1, HQ = Q / 2 + 1, nl = it.nl, Ls = P + 1;
+    float2 *a = sm, *b = sm + nl * Ls, *m = sm + 2 * nl * Ls;
+    const float2 *X = rowspec + f.t3_off, *Si = Sp + f.s_off;
+    for (int be = 0; be < S; ++be) {
+        for (int e = threadIdx.x; e < nl * P; e += kFftThreads) {
+            const int y = e / nl, l = e - y * nl, Kx = it.line0 + l + be * Q;
+            a[l * Ls + y] = y < c.F ? X[y * HP + (2 * Kx <= P ? Kx : P - Kx)] : make_float2(0.f, 0.f);
+        }
+        __syncthreads();
+        const float2 *r = lds_fft_any<false>(a, b, nl, c.fP, tw + c.fP.tw_off);
+        for (int e = threadIdx.x; e < nl * Q; e += kFftThreads) {
+            const int ky = e / nl, l = e - ky * nl, kx = it.line0 + l;
+            const bool lo = 2 * (kx + be * Q) <= P;
+            float2 sk[S], acc = be ? m[l * (Q + 1) + ky] : make_float2(0.f, 0.f);
+            alias_load<S>(Si, ((ky * HQ + kx) * S + be) * S, sk);
+            #pragma unroll
+            for (int al = 0; al < S; ++al) {
+                const int Ky = ky + al * Q;
+                float2 v = r[l * Ls + (lo || Ky == 0 ? Ky : P - Ky)];
+                v.y = lo ? v.y : -v.y;
+                acc = cadd(acc, cmul(sk[al], v));
+            }
+            m[l * (Q + 1) + ky] = acc;
+        }
+        __syncthreads();
     }
-    __device__ void store(const ClassFft &c, int i, int kx, int y, float2 v) const
-    {
-        const int H = c.Q / 2 + 1;
-        if (y < c.n) T[fr[i].t_off + (long long)y * H + kx] = v;
+    const float2 *r = lds_fft_any<true>(m, a, nl, c.fQ, tw + c.fQ.tw_off);
+    for (int e = threadIdx.x; e < nl * c.n; e += kFftThreads) {
+        const int y = e / nl, l = e - y * nl;
+        T[f.t_off + (long long)y * HQ + it.line0 + l] = r[l * (Q + 1) + y];
     }
-};
+}
+
+// rows of residual spectra [n][Q/2+1] -> rows of adjoint spectra [F][P/2+1]
+template <int S>
+__global__ __launch_bounds__(kFftThreads) void k_unfold(const LineItem *__restrict__ items,
+                                                        const ClassFft *__restrict__ classes,
+                                                        const FrameFft *__restrict__ fr, const float2 *__restrict__ tw,
+                                                        const float2 *__restrict__ T2, const float2 *__restrict__ Sp,
+                                                        float2 *__restrict__ rowspec)
+{
+    extern __shared__ float2 sm[];
+    const LineItem it = items[blockIdx.x];
+    const ClassFft &c = classes[it.cls];
+    const FrameFft &f = fr[it.frame];
+    const int P = c.P, Q = c.Q, HP = P / 2 + 1, HQ = Q / 2 + 1, nl = it.nl, Ls = P + 1;
+    float2 *a = sm, *b = sm + nl * Ls, *m = sm + 2 * nl * Ls;
+    for (int e = threadIdx.x; e < nl * Q; e += kFftThreads) {
+        const int y = e / nl, l = e - y * nl;
+        m[l * (Q + 1) + y] = y < c.n ? T2[f.t_off + (long long)y * HQ + it.line0 + l] : make_float2(0.f, 0.f);
+    }
+    __syncthreads();
+    const float2 *rho = lds_fft_any<false>(m, a, nl, c.fQ, tw + c.fQ.tw_off);
+    if (rho != m) {  // (the transform ended in the other buffer)
+        for (int e = threadIdx.x; e < nl * (Q + 1); e += kFftThreads) m[e] = rho[e];
+        __syncthreads();
+    }
+    float2 *X = rowspec + f.t3_off;
+    const float2 *Si = Sp + f.s_off;
+    for (int be = 0; be < S; ++be) {
+        for (int e = threadIdx.x; e < nl * Q; e += kFftThreads) {
+            const int ky = e / nl, l = e - ky * nl, kx = it.line0 + l;
+            float2 sk[S];
+            alias_load<S>(Si, ((ky * HQ + kx) * S + be) * S, sk);
+            const float2 v = m[l * (Q + 1) + ky];
+            #pragma unroll
+            for (int al = 0; al < S; ++al) a[l * Ls + ky + al * Q] = cmulc(v, sk[al]);
+        }
+        __syncthreads();
+        const float2 *r = lds_fft_any<true>(a, b, nl, c.fP, tw + c.fP.tw_off);
+        for (int e = threadIdx.x; e < nl * c.F; e += kFftThreads) {
+            const int y = e / nl, l = e - y * nl, kx = it.line0 + l, Kx = kx + be * Q;
+            const float2 v = r[l * Ls + y];
+            if (2 * Kx <= P) X[y * HP + Kx] = v;
+            else if (kx > 0 && 2 * kx < Q) X[y * HP + P - Kx] = conjf2(v);  // (else another column's own)
+        }
+        __syncthreads();
+    }
+}
 
 // ---- forward spectral product: M_hat_i(k) = sum over the s^2 aliases of
 // S''_i(K) F_i(K), F_i = H + Gamma_i w x w + sum_k a_ik gy_k x gx_k (Eq. 9).
@@ -654,7 +753,6 @@ struct OpMCols {
     const float2 *Mh;
     float2 *T;
     static constexpr bool col = true;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = true;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fQ; }
     __device__ float2 load(const ClassFft &c, int i, int kx, int ky) const
@@ -675,7 +773,6 @@ struct OpRhoCols {
     const float2 *T2;
     float2 *Rh;
     static constexpr bool col = true;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = false;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fQ; }
     __device__ float2 load(const ClassFft &c, int i, int kx, int y) const
@@ -690,112 +787,57 @@ struct OpRhoCols {
     }
 };
 
-// ---- pass G: conj(S'') * rho_hat(K mod Q), inverse along Ky, crop rows < F ----
-struct OpAdjCols {
-    const FrameFft *fr;
-    const float2 *S;
-    const float2 *Rh;
-    float2 *T3;
-    static constexpr bool col = true;
-    static constexpr bool rowsum = false;
-    static constexpr bool inverse = true;
-    __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
-    __device__ float2 load(const ClassFft &c, int i, int Kx, int Ky) const
-    {
-        const FrameFft &f = fr[i];
-        const int P = c.P, Q = c.Q;
-        const float2 sv = alias_get(S + f.s_off, P, Q, Ky, Kx);
-        const int ky = Ky % Q, kx = Kx % Q;
-        const float2 rv = half_get(Rh + f.r_off, Q, ky, kx);
-        return cmulc(rv, sv);
-    }
-    __device__ void store(const ClassFft &c, int i, int Kx, int y, float2 v) const
-    {
-        const int H = c.P / 2 + 1;
-        if (y < c.F) T3[fr[i].t3_off + (long long)y * H + Kx] = v;
-    }
-};
-
-// ---- pass H: rows, Hermitian extension, inverse, crop x < F -> g_i ----
-struct OpAdjRows {
+// ---- their row passes ----
+struct OpAdjRows {  // adjoint spectra -> g
     const FrameFft *fr;
     const float2 *T3;
     float *g;
-    double *gpart;  // one partial sum of g per work group
-    static constexpr bool col = false;
-    static constexpr bool rowsum = true;  // per-group sum of g: the frame sums for Gamma
     static constexpr bool inverse = true;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
+    __device__ int rows(const ClassFft &c) const { return c.F; }
     __device__ float2 load(const ClassFft &c, int i, int y, int Kx) const
     {
         const int P = c.P, H = P / 2 + 1;
         const float2 *row = T3 + fr[i].t3_off + (long long)y * H;
         return Kx < H ? row[Kx] : conjf2(row[P - Kx]);
     }
-    __device__ float store(const ClassFft &c, int i, int y, int x, float2 v) const
+    __device__ void store(const ClassFft &c, int i, int y, int x, float v) const
     {
-        if (x >= c.F) return 0.f;
-        g[fr[i].fine_off + (long long)y * c.F + x] = v.x;
-        return v.x;
+        if (x < c.F) g[fr[i].fine_off + (long long)y * c.F + x] = v;
     }
 };
 
-// ---- standalone adjoint: rows of a given residual -> T2 ----
-struct OpResidRows {
+struct OpResidRows {  // a given residual -> T2
     const FrameFft *fr;
     const float *resid;
     float2 *T2;
-    static constexpr bool col = false;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = false;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fQ; }
-    __device__ float2 load(const ClassFft &c, int i, int y, int x) const
+    __device__ int rows(const ClassFft &c) const { return c.n; }
+    __device__ float load(const ClassFft &c, int i, int y, int x) const
     {
-        return make_float2(x < c.n ? resid[fr[i].data_off + (long long)y * c.n + x] : 0.f, 0.f);
+        return x < c.n ? resid[fr[i].data_off + (long long)y * c.n + x] : 0.f;
     }
     __device__ void store(const ClassFft &c, int i, int y, int kx, float2 v) const
     {
-        const int H = c.Q / 2 + 1;
-        if (kx < H) T2[fr[i].t_off + (long long)y * H + kx] = v;
+        T2[fr[i].t_off + (long long)y * (c.Q / 2 + 1) + kx] = v;
     }
 };
 
-// ---- standalone forward: spectrum of a given scene, rows then columns in place ----
-struct OpSceneRows {
+struct OpSceneRows {  // a given scene -> T3
     const FrameFft *fr;
     const float *scene;
     float2 *T3;
-    static constexpr bool col = false;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = false;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
-    __device__ float2 load(const ClassFft &c, int i, int y, int x) const
+    __device__ int rows(const ClassFft &c) const { return c.F; }
+    __device__ float load(const ClassFft &c, int i, int y, int x) const
     {
-        return make_float2(x < c.F ? scene[fr[i].fine_off + (long long)y * c.F + x] : 0.f, 0.f);
+        return x < c.F ? scene[fr[i].fine_off + (long long)y * c.F + x] : 0.f;
     }
     __device__ void store(const ClassFft &c, int i, int y, int kx, float2 v) const
     {
-        const int H = c.P / 2 + 1;
-        if (kx < H) T3[fr[i].t3_off + (long long)y * H + kx] = v;
-    }
-};
-
-struct OpSceneCols {  // every column is read and written by the same work group
-    const FrameFft *fr;
-    float2 *T3;
-    static constexpr bool col = true;
-    static constexpr bool rowsum = false;
-    static constexpr bool inverse = false;
-    __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
-    __device__ float2 load(const ClassFft &c, int i, int kx, int y) const
-    {
-        const int H = c.P / 2 + 1;
-        return y < c.F ? T3[fr[i].t3_off + (long long)y * H + kx] : make_float2(0.f, 0.f);
-    }
-    __device__ void store(const ClassFft &c, int i, int kx, int ky, float2 v) const
-    {
-        const int H = c.P / 2 + 1;
-        T3[fr[i].t3_off + (long long)ky * H + kx] = v;
+        T3[fr[i].t3_off + (long long)y * (c.P / 2 + 1) + kx] = v;
     }
 };
 
@@ -1199,7 +1241,6 @@ struct OpGCols {
     const float2 *Gp;
     float2 *Th;
     static constexpr bool col = true;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = true;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
     __device__ float2 load(const ClassFft &c, int, int Kx, int Ky) const
@@ -1217,7 +1258,6 @@ struct OpGRows {
     const float2 *Th;
     float *hcls;
     static constexpr bool col = false;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = true;
     __device__ const FftLen &len(const ClassFft &c) const { return c.fP; }
     __device__ float2 load(const ClassFft &c, int, int y, int Kx) const
@@ -1244,7 +1284,6 @@ struct OpGRowsFin {
     DenseStar psum;  // with psum.U set, the prior's gradient is summed from its per-level planes here
     static constexpr bool extra = true;
     static constexpr bool col = false;
-    static constexpr bool rowsum = false;
     static constexpr bool inverse = true;
     __device__ void run_extra(int xb, const ClassFft *, const float2 *) const
     {
@@ -1351,50 +1390,68 @@ hipError_t fft_model_rows(hipStream_t st, const FftPlanDev &d, const float *data
     return hipGetLastError();
 }
 
+template <class Op>
+static hipError_t run_row_pairs(hipStream_t st, const LinePass &lp, const FftPlanDev &d, const Op &op)
+{
+    if (lp.n_items <= 0) return hipSuccess;
+    hipLaunchKernelGGL((k_row_pairs<Op>), dim3(lp.n_items), dim3(kFftThreads), lp.lds_bytes, st, lp.items, d.classes,
+                       d.tw, op);
+    return hipGetLastError();
+}
+
+#define FOLD_LAUNCH(KERNEL, LP, ...)                                                                             \
+    do {                                                                                                         \
+        if ((LP).n_items <= 0) break;                                                                            \
+        const dim3 g_((LP).n_items), b_(kFftThreads);                                                            \
+        if (s == 1) hipLaunchKernelGGL(KERNEL<1>, g_, b_, (LP).lds_bytes, st, (LP).items, d.classes, __VA_ARGS__); \
+        else if (s == 2) hipLaunchKernelGGL(KERNEL<2>, g_, b_, (LP).lds_bytes, st, (LP).items, d.classes, __VA_ARGS__); \
+        else hipLaunchKernelGGL(KERNEL<3>, g_, b_, (LP).lds_bytes, st, (LP).items, d.classes, __VA_ARGS__);        \
+    } while (0)
+
+// S_i and D of given scenes: the model alone (model), or the residual's chi-square
+// partials and its row spectra
+static hipError_t scene_forward(hipStream_t st, const FftPlanDev &d, const LinePass &srows, const LinePass &fold,
+                                const LinePass &frows, const float *scene, int s, const float *data,
+                                const float *invvar, float *model, double *part_chi)
+{
+    hipError_t e = run_row_pairs(st, srows, d, OpSceneRows{d.frames, scene, d.T3});
+    if (e != hipSuccess) return e;
+    FOLD_LAUNCH(k_fold, fold, d.frames, d.tw, d.T3, d.S, d.T);
+    if (frows.n_items > 0)
+        hipLaunchKernelGGL(k_fwd_rows, dim3(frows.n_items), dim3(kFftThreads), frows.lds_bytes, st, frows.items,
+                           d.classes, d.frames, d.tw, d.T, data, invvar, d.T2, model, part_chi);
+    return hipGetLastError();
+}
+
+// D^T and S_i^T of residuals given by their row spectra
+static hipError_t resid_adjoint(hipStream_t st, const FftPlanDev &d, const LinePass &unfold, const LinePass &arows,
+                                int s, float *g)
+{
+    FOLD_LAUNCH(k_unfold, unfold, d.frames, d.tw, d.T2, d.S, d.T3);
+    hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : run_row_pairs(st, arows, d, OpAdjRows{d.frames, d.T3, g});
+}
+
 hipError_t fft_scene_model(hipStream_t st, const FftPlanDev &d, const float *scene, int s, float *model)
 {
-    // the kernel spectra are indexed like the row passes over P lines
-    hipError_t e = run_lines(st, d.srows, d.classes, d.tw, OpSceneRows{d.frames, scene, d.T3});
-    if (e != hipSuccess) return e;
-    e = run_lines(st, d.scols, d.classes, d.tw, OpSceneCols{d.frames, d.T3});
-    if (e != hipSuccess) return e;
-    e = run_lines(st, d.fcols, d.classes, d.tw,
-                  OpFwdCols{d.frames, d.S, s, d.T, d.T3});
-    if (e != hipSuccess) return e;
-    if (d.frows.n_items > 0) {
-        hipLaunchKernelGGL(k_fwd_rows, dim3(d.frows.n_items), dim3(kFftThreads), d.frows.lds_bytes, st,
-                           d.frows.items, d.classes, d.frames, d.tw, d.T, nullptr, nullptr, d.T2, model,
-                           nullptr);
-        e = hipGetLastError();
-    }
-    return e;
+    return scene_forward(st, d, d.srows, d.fold, d.frows, scene, s, nullptr, nullptr, model, nullptr);
+}
+
+hipError_t fft_scene_adjoint(hipStream_t st, const FftPlanDev &d, const float *resid, int s, float *g)
+{
+    const hipError_t e = run_row_pairs(st, d.rrows, d, OpResidRows{d.frames, resid, d.T2});
+    return e != hipSuccess ? e : resid_adjoint(st, d, d.fold, d.arows, s, g);
 }
 
 hipError_t fft_xf_forward(hipStream_t st, const FftPlanDev &d, const float *scene, int s, const float *data,
                           const float *invvar, double *part_chi)
 {
-    hipError_t e = run_lines(st, d.srows_x, d.classes, d.tw, OpSceneRows{d.frames, scene, d.T3});
-    if (e != hipSuccess) return e;
-    e = run_lines(st, d.scols_x, d.classes, d.tw, OpSceneCols{d.frames, d.T3});
-    if (e != hipSuccess) return e;
-    e = run_lines(st, d.fcols_x, d.classes, d.tw, OpFwdCols{d.frames, d.S, s, d.T, d.T3});
-    if (e != hipSuccess || d.frows_x.n_items <= 0) return e;
-    hipLaunchKernelGGL(k_fwd_rows, dim3(d.frows_x.n_items), dim3(kFftThreads), d.frows_x.lds_bytes, st,
-                       d.frows_x.items, d.classes, d.frames, d.tw, d.T, data, invvar, d.T2, nullptr, part_chi);
-    return hipGetLastError();
+    return scene_forward(st, d, d.srows_x, d.fold_x, d.frows_x, scene, s, data, invvar, nullptr, part_chi);
 }
 
-hipError_t fft_xf_adjoint(hipStream_t st, const FftPlanDev &d, float *g)
+hipError_t fft_xf_adjoint(hipStream_t st, const FftPlanDev &d, int s, float *g)
 {
-    hipError_t e = run_lines(st, d.rcols_x, d.classes, d.tw, OpRhoCols{d.frames, d.T2, d.Rh});
-    if (e == hipSuccess) e = run_lines(st, d.acols_x, d.classes, d.tw, OpAdjCols{d.frames, d.S, d.Rh, d.T3});
-    if (e == hipSuccess) e = run_lines(st, d.arows_x, d.classes, d.tw, OpAdjRows{d.frames, d.T3, g, d.gpart_x});
-    return e;
-}
-
-hipError_t fft_resid_rows(hipStream_t st, const FftPlanDev &d, const float *resid)
-{
-    return run_lines(st, d.rrows, d.classes, d.tw, OpResidRows{d.frames, resid, d.T2});
+    return resid_adjoint(st, d, d.fold_x, d.arows_x, s, g);
 }
 
 hipError_t fft_fused_fwd(hipStream_t st, const FftPlanDev &d, const float *params, int N, int E, int M, int s,
@@ -1447,16 +1504,6 @@ hipError_t fft_rho_cols_lg(hipStream_t st, const FftPlanDev &d)
 hipError_t fft_rho_cols(hipStream_t st, const FftPlanDev &d)
 {
     return run_lines(st, d.rcols, d.classes, d.tw, OpRhoCols{d.frames, d.T2, d.Rh});
-}
-
-hipError_t fft_adj_cols(hipStream_t st, const FftPlanDev &d)
-{
-    return run_lines(st, d.acols, d.classes, d.tw, OpAdjCols{d.frames, d.S, d.Rh, d.T3});
-}
-
-hipError_t fft_adj_rows(hipStream_t st, const FftPlanDev &d, float *g)
-{
-    return run_lines(st, d.arows, d.classes, d.tw, OpAdjRows{d.frames, d.T3, g, d.gpart});
 }
 
 template <int S>
@@ -1523,14 +1570,6 @@ hipError_t fft_grad_h_inverse(hipStream_t st, const FftPlanDev &d, DensePiece *p
     hipError_t e = run_lines(st, d.gcols, d.classes, d.tw, OpGCols{d.Gp, d.Th}, -1, pd);
     if (e != hipSuccess) return e;
     return run_lines(st, d.grows, d.classes, d.tw, OpGRows{d.Th, d.hcls});
-}
-
-hipError_t fft_adjoint(hipStream_t st, const FftPlanDev &d, float *g)
-{
-    hipError_t e = fft_rho_cols(st, d);
-    if (e == hipSuccess) e = fft_adj_cols(st, d);
-    if (e == hipSuccess) e = fft_adj_rows(st, d, g);
-    return e;
 }
 
 }  // namespace starred

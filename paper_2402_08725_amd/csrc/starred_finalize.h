@@ -15,8 +15,6 @@ struct FinalArgs {
     const float *params = nullptr;
     float *grad = nullptr;
     double *loss = nullptr;
-    const int *gcsr_off = nullptr, *gcsr_item = nullptr;  // optional CSR of dL/dGamma partials
-    const double *gpart = nullptr;
     int *tick = nullptr;           // step counter advanced here (null: none)
     AdamDev adam;                  // update of Gamma, a, c (params null: none)
     const double *pts = nullptr;   // point-source prior's shares (3M) or null
@@ -117,15 +115,7 @@ __device__ void finalize_small_body(const FinalArgs &a)
     }
     if (!a.grad) return;
     float *gG = a.grad + NN, *ga = gG + E;
-    for (int i = threadIdx.x; i < E; i += NT) {
-        if (a.gcsr_off) {
-            double acc = 0.0;
-            for (int q = a.gcsr_off[i]; q < a.gcsr_off[i + 1]; ++q) acc += a.gpart[a.gcsr_item[q]];
-            gG[i] = (float)acc;
-        } else {
-            gG[i] = (float)a.fsum[(long long)i * stride];
-        }
-    }
+    for (int i = threadIdx.x; i < E; i += NT) gG[i] = (float)a.fsum[(long long)i * stride];
     for (long long e = threadIdx.x; e < (long long)E * M; e += NT) {
         const long long i = e / M, k = e - i * M;
         ga[e] = (float)(a.fsum[i * stride + 1 + k] + (a.pts ? a.pts[3 * k] : 0.0));

@@ -124,9 +124,7 @@ struct DenseStar;
 hipError_t launch_finalize_small(hipStream_t st, int E, int M, int n_chi, const double *part_chi,
                                  int n_l1, const double *part_l1, double lambda,
                                  const double *fsum, const float *params, int N,
-                                 float *grad, double *loss, const int *gcsr_off = nullptr,
-                                 const int *gcsr_item = nullptr, const double *gpart = nullptr,
-                                 int *tick = nullptr, const ClassFft *classes = nullptr, int ncls = 0,
+                                 float *grad, double *loss, int *tick = nullptr, const ClassFft *classes = nullptr, int ncls = 0,
                                  const float *hcls = nullptr, const float *prior = nullptr,
                                  const AdamDev &adam = AdamDev(), const double *pts = nullptr,
                                  const DenseStar *psum = nullptr);

@@ -100,6 +100,7 @@ hipError_t launch_prep_kernels(hipStream_t st, const FrameDev *fr_dev, const Fra
 // reach hundreds of pixels.
 struct FrameMap {
     double cs, sn, C, dx, dy;
+    FrameMap() = default;
     __device__ FrameMap(const float *xf, int i, int N)
     {
         dx = (double)xf[3 * i];
@@ -143,6 +144,11 @@ __global__ void k_render(const FrameDev *__restrict__ frames, int E, int frame0,
     const int i = flist ? flist[blockIdx.y] : frame0 + blockIdx.y;
     const FrameDev fr = frames[i];
     const int pix = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ FrameMap fm;  // (FP64 sine and cosine once per block, not per pixel)
+    if (xf) {
+        if (threadIdx.x == 0) fm = FrameMap(xf, i, N);
+        __syncthreads();
+    }
     if (pix >= fr.F * fr.F) return;
     const int y = pix / fr.F, x = pix % fr.F;
     const int Y = y + fr.o, X = x + fr.o;
@@ -152,7 +158,6 @@ __global__ void k_render(const FrameDev *__restrict__ frames, int E, int frame0,
     double ux = (double)X, uy = (double)Y;
     float v;
     if (xf) {
-        FrameMap fm(xf, i, N);
         fm.map((double)X, (double)Y, ux, uy);
         v = params[(long long)N * N + i] + bilerp(h, N, ux, uy, nullptr, nullptr);
     } else {
@@ -534,7 +539,9 @@ __device__ void frame_sums_xf(const FrameDev &fr, int i, int by, int E, int N, i
     const float inv2s2 = 1.0f / (2.0f * sigma * sigma);
     const float invs2 = 1.0f / (sigma * sigma);
     const float norm = 1.0f / (2.0f * 3.14159265358979f * sigma * sigma);
-    const FrameMap fm(xf, i, N);
+    __shared__ FrameMap fm;
+    if (threadIdx.x == 0) fm = FrameMap(xf, i, N);
+    __syncthreads();
     if (by == 0) {
         double acc = 0.0;
         for (int p = threadIdx.x; p < tot; p += NT) acc += (double)gi[p];
@@ -730,10 +737,8 @@ constexpr int kFinChunkXf = 4;  // the same for frames under transforms (25 cand
 // g_i(X) times the weight with which frame pixel X read h there, over the frame
 // pixels whose transformed position lies within one pixel of (PX, PY) on both axes
 // (a gather in a fixed order: the candidates around the preimage of the pixel).
-__device__ float transpose_bilerp(const FrameDev &fr, int i, int N, const float *__restrict__ xf,
-                                  const float *__restrict__ g, int PX, int PY)
+__device__ float transpose_bilerp(const FrameDev &fr, const FrameMap &fm, const float *__restrict__ g, int PX, int PY)
 {
-    const FrameMap fm(xf, i, N);
     const double ex = (double)PX - fm.C - fm.dx, ey = (double)PY - fm.C - fm.dy;
     const double px = fm.cs * ex + fm.sn * ey + fm.C, py = -fm.sn * ex + fm.cs * ey + fm.C;
     // a frame pixel X reads (PX, PY) when its image u lies in [PX - 1, PX + 1) on both
@@ -769,15 +774,20 @@ __global__ void k_finalize_h_part(const FrameDev *__restrict__ frames, int E, in
                                   const int *__restrict__ flist, const float *__restrict__ xf)
 {
     const int pix = blockIdx.x * blockDim.x + threadIdx.x;
-    if (pix >= N * N) return;
-    const int Y = pix / N, X = pix % N;
     const int chunk = xf ? kFinChunkXf : kFinChunk;
     const int i0 = blockIdx.y * chunk, i1 = min(E, i0 + chunk);
+    __shared__ FrameMap fm[kFinChunkXf];
+    if (xf) {
+        if ((int)threadIdx.x < i1 - i0) fm[threadIdx.x] = FrameMap(xf, flist ? flist[i0 + threadIdx.x] : i0 + threadIdx.x, N);
+        __syncthreads();
+    }
+    if (pix >= N * N) return;
+    const int Y = pix / N, X = pix % N;
     float acc = 0.f;
     if (xf) {
         for (int q = i0; q < i1; ++q) {
             const int i = flist ? flist[q] : q;
-            acc += transpose_bilerp(frames[i], i, N, xf, g, X, Y);
+            acc += transpose_bilerp(frames[i], fm[q - i0], g, X, Y);
         }
         part[(long long)blockIdx.y * N * N + pix] = acc;
         return;
@@ -856,8 +866,7 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize_small(FinalArgs fa, co
 hipError_t launch_finalize_small(hipStream_t st, int E, int M, int n_chi, const double *part_chi,
                                  int n_l1, const double *part_l1, double,
                                  const double *fsum, const float *params, int N,
-                                 float *grad, double *loss, const int *gcsr_off, const int *gcsr_item,
-                                 const double *gpart, int *tick, const ClassFft *classes, int ncls,
+                                 float *grad, double *loss, int *tick, const ClassFft *classes, int ncls,
                                  const float *hcls, const float *prior, const AdamDev &adam, const double *pts,
                                  const DenseStar *psum)
 {
@@ -877,9 +886,6 @@ hipError_t launch_finalize_small(hipStream_t st, int E, int M, int n_chi, const 
     fa.params = params;
     fa.grad = grad;
     fa.loss = loss;
-    fa.gcsr_off = gcsr_off;
-    fa.gcsr_item = gcsr_item;
-    fa.gpart = gpart;
     fa.tick = tick;
     fa.adam = adam;
     fa.pts = pts;

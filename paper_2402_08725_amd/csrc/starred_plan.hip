@@ -863,10 +863,9 @@ static int build_fft_lists(starred_plan *p)
     HIP_TRY(hipMemcpy(d.classes, p->cls.data(), sizeof(ClassFft) * p->cls.size(), hipMemcpyHostToDevice));
 
     // line passes: groups of lines of one frame (or class), longest transforms first
-    std::vector<LineItem> last_items;
     // all: every frame, whatever its class runs (the kernel-spectrum passes of set_frames)
     auto make_pass = [&](LinePass &lp, bool per_class, auto lines_of, auto len_of, bool skip_fused = false,
-                         bool all = false) -> int {
+                         bool all = false, int min_lines = 1) -> int {
         struct G { int L; LineItem it; };
         std::vector<G> g;
         const int nunits = per_class ? (int)p->cls.size() : E;
@@ -881,7 +880,7 @@ static int build_fft_lists(starred_plan *p)
         // lines per work group: about kFftTargetElems elements, fewer when the
         // pass is small so that every compute unit gets work
         const long long want_groups = p->line_groups;
-        const int cap = (int)std::max(1LL, total_lines / want_groups);
+        const int cap = (int)std::max((long long)min_lines, total_lines / want_groups);
         int maxL = 1;
         for (int u = 0; u < nunits; ++u) {
             if (skip(u)) continue;
@@ -897,7 +896,6 @@ static int build_fft_lists(starred_plan *p)
         std::stable_sort(g.begin(), g.end(), [](const G &a, const G &b) { return a.L > b.L; });
         std::vector<LineItem> items;
         for (auto &x : g) items.push_back(x.it);
-        last_items = items;
         lp.n_items = (int)items.size();
         lp.lds_bytes = (size_t)2 * maxL * sizeof(float2);
         int rc2 = p->alloc_list(&lp.items, std::max<size_t>(1, items.size()));
@@ -916,39 +914,28 @@ static int build_fft_lists(starred_plan *p)
     if ((rc = make_pass(d.kcols, false, [](const ClassFft &c) { return c.P / 2 + 1; }, LP, false, true))) return rc;
     if ((rc = make_pass(d.fcols, false, [](const ClassFft &c) { return c.Q / 2 + 1; }, LQ))) return rc;
     if ((rc = make_pass(d.frows, false, [](const ClassFft &c) { return c.n; }, LQ))) return rc;
-    if ((rc = make_pass(d.rrows, false, [](const ClassFft &c) { return c.n; }, LQ))) return rc;
     if ((rc = make_pass(d.rcols, false, [](const ClassFft &c) { return c.Q / 2 + 1; }, LQ))) return rc;
     if ((rc = make_pass(d.fcols_lg, false, [](const ClassFft &c) { return c.Q / 2 + 1; }, LQ, true))) return rc;
     if ((rc = make_pass(d.frows_lg, false, [](const ClassFft &c) { return c.n; }, LQ, true))) return rc;
     if ((rc = make_pass(d.rcols_lg, false, [](const ClassFft &c) { return c.Q / 2 + 1; }, LQ, true))) return rc;
-    if ((rc = make_pass(d.acols, false, [](const ClassFft &c) { return c.P / 2 + 1; }, LP))) return rc;
-    if ((rc = make_pass(d.arows, false, [](const ClassFft &c) { return c.F; }, LP))) return rc;
-    {
-        std::vector<int> off(E + 1, 0), item;
-        for (const LineItem &li : last_items) off[li.frame + 1]++;
-        for (int i = 0; i < E; ++i) off[i + 1] += off[i];
-        item.resize(last_items.size());
-        std::vector<int> fill(off.begin(), off.end() - 1);
-        for (int q = 0; q < (int)last_items.size(); ++q) item[fill[last_items[q].frame]++] = q;
-        if ((rc = p->alloc_list(&d.gpart, std::max<size_t>(1, last_items.size())))) return rc;
-        if ((rc = p->alloc_list(&d.gcsr_off, E + 1))) return rc;
-        if ((rc = p->alloc_list(&d.gcsr_item, std::max<size_t>(1, item.size())))) return rc;
-        HIP_TRY(hipMemcpy(d.gcsr_off, off.data(), sizeof(int) * (E + 1), hipMemcpyHostToDevice));
-        if (!item.empty()) HIP_TRY(hipMemcpy(d.gcsr_item, item.data(), sizeof(int) * item.size(), hipMemcpyHostToDevice));
-    }
-    if ((rc = make_pass(d.srows, false, [](const ClassFft &c) { return c.F; }, LP))) return rc;
-    if ((rc = make_pass(d.scols, false, [](const ClassFft &c) { return c.P / 2 + 1; }, LP))) return rc;
     if ((rc = make_pass(d.gcols, true, [](const ClassFft &c) { return c.P / 2 + 1; }, LP))) return rc;
     if ((rc = make_pass(d.grows, true, [](const ClassFft &c) { return c.F; }, LP))) return rc;
+    // operators on given scenes and residuals: rows in pairs, and columns of the Q grid with
+    // their P-point lines (k_fold: two planes of P + 1 and one of Q + 1 per line; four lines at
+    // least, whose columns share memory sectors)
+    auto pairsF = [](const ClassFft &c) { return (c.F + 1) / 2; };
+    auto pairsn = [](const ClassFft &c) { return (c.n + 1) / 2; };
+    auto colsQ = [](const ClassFft &c) { return c.Q / 2 + 1; };
+    auto LF = [](const ClassFft &c) { return c.P + 1 + (c.Q + 1) / 2; };
+    if ((rc = make_pass(d.srows, false, pairsF, LP))) return rc;
+    if ((rc = make_pass(d.rrows, false, pairsn, LQ))) return rc;
+    if ((rc = make_pass(d.arows, false, pairsF, LP))) return rc;
+    if ((rc = make_pass(d.fold, false, colsQ, LF, false, false, 4))) return rc;
     // every frame: the per-frame convolution of the rendered scenes (frame transforms)
-    if ((rc = make_pass(d.srows_x, false, [](const ClassFft &c) { return c.F; }, LP, false, true))) return rc;
-    if ((rc = make_pass(d.scols_x, false, [](const ClassFft &c) { return c.P / 2 + 1; }, LP, false, true))) return rc;
-    if ((rc = make_pass(d.fcols_x, false, [](const ClassFft &c) { return c.Q / 2 + 1; }, LQ, false, true))) return rc;
+    if ((rc = make_pass(d.srows_x, false, pairsF, LP, false, true))) return rc;
+    if ((rc = make_pass(d.fold_x, false, colsQ, LF, false, true, 4))) return rc;
     if ((rc = make_pass(d.frows_x, false, [](const ClassFft &c) { return c.n; }, LQ, false, true))) return rc;
-    if ((rc = make_pass(d.rcols_x, false, [](const ClassFft &c) { return c.Q / 2 + 1; }, LQ, false, true))) return rc;
-    if ((rc = make_pass(d.acols_x, false, [](const ClassFft &c) { return c.P / 2 + 1; }, LP, false, true))) return rc;
-    if ((rc = make_pass(d.arows_x, false, [](const ClassFft &c) { return c.F; }, LP, false, true))) return rc;
-    if ((rc = p->alloc_list(&d.gpart_x, std::max<size_t>(1, (size_t)d.arows_x.n_items)))) return rc;
+    if ((rc = make_pass(d.arows_x, false, pairsF, LP, false, true))) return rc;
     // the direct path's lists for the frames of the direct classes
     if ((rc = build_direct_lists(p))) return rc;
     // chi-square partials: the FFT line-pass row groups (or, with the one-launch
@@ -1339,8 +1326,7 @@ int starred_convolve_subsample_adj(starred_plan *p, const float *resid, float *g
     if (p->mode == STARRED_PSF) return fail(STARRED_EUNSUPPORTED, "deconvolution-mode operator called on a PSF-mode plan");
     if (!p->frames_set) return fail(STARRED_ESTATE, "set_frames has not been called");
     if (p->algo == STARRED_CONV_FFT) {
-        HIP_TRY(fft_resid_rows(p->st, p->fd, resid));
-        HIP_TRY(fft_adjoint(p->st, p->fd, grad_scene));
+        HIP_TRY(fft_scene_adjoint(p->st, p->fd, resid, p->s, grad_scene));
     }
     HIP_TRY(launch_adj_direct(p->st, p->s, p->d_fr, p->d_adj_items, (int)p->adj_items.size(), p->Ardir,
                               p->Bpdir, resid, p->d_ka, grad_scene, p->adj_groups));
@@ -1584,7 +1570,7 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
         if (dir) {
             hipEvent_t e1 = p->prof_start();
             if (xf_fft)
-                HIP_TRY(fft_xf_adjoint(p->st, p->fd, p->d_g));
+                HIP_TRY(fft_xf_adjoint(p->st, p->fd, p->s, p->d_g));
             else
                 HIP_TRY(launch_adj_direct(p->st, p->s, p->d_fr, p->d_adj_items, (int)p->adj_items.size(), p->Ardir,
                                           p->Bpdir, p->d_rho, p->d_ka, p->d_g, p->adj_groups));
@@ -1629,7 +1615,7 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
         HIP_TRY(launch_finalize_h(p->st, p->d_fr, p->E, p->N, p->d_g, p->d_prior, fft ? p->d_hdir : grad,
                                   p->d_hpart, fft ? p->d_fdir : nullptr, (int)p->fdir.size(), p->xf));
     HIP_TRY(launch_finalize_small(p->st, p->E, p->M, n_chi, part_chi, n_l1, p->d_part_l1, p->lam, p->d_fsum,
-                                  params, p->N, grad, loss_out, nullptr, nullptr, nullptr,
+                                  params, p->N, grad, loss_out,
                                   (fft && adam) ? nullptr : tick, fft ? p->fd.classes : nullptr, p->fd.n_classes,
                                   p->fd.hcls, ride ? nullptr : ((fft && dir) ? p->d_hdir : p->d_prior),
                                   (fft && adam) ? *adam : AdamDev(),
@@ -1978,7 +1964,7 @@ int starred_loss_grad_plain(starred_plan *p, const float *params, float *grad, d
     if (rc) return rc;
     if (grad) HIP_TRY(launch_finalize_h(p->st, p->d_fr, p->E, p->N, p->d_g, p->d_prior, grad, p->d_hpart));
     HIP_TRY(launch_finalize_small(p->st, p->E, p->M, p->n_pchi, p->d_pchi, n_l1, p->d_part_l1, p->lam, p->d_fsum,
-                                  params, p->N, grad, loss_out, nullptr, nullptr, nullptr, nullptr, nullptr, 0,
+                                  params, p->N, grad, loss_out, nullptr, nullptr, 0,
                                   nullptr, nullptr, AdamDev(), (p->lam_pts != 0.0 && grad) ? p->d_pts : nullptr));
     return STARRED_OK;
 }
@@ -2525,7 +2511,7 @@ int starred_time_stage(starred_plan *p, const float *params, int32_t stage, int3
         case STARRED_STAGE_DIRECT_ADJ:
             if (p->fdir.empty()) break;
             if (p->xf && p->xf_fft) {
-                HIP_TRY(fft_xf_adjoint(p->st, p->fd, p->d_g));
+                HIP_TRY(fft_xf_adjoint(p->st, p->fd, p->s, p->d_g));
                 return STARRED_OK;
             }
             HIP_TRY(launch_adj_direct(p->st, p->s, p->d_fr, p->d_adj_items, (int)p->adj_items.size(), p->Ardir,
