@@ -752,18 +752,17 @@ __device__ float transpose_bilerp(const FrameDev &fr, const FrameMap &fm, const 
     for (int Y = ylo; Y <= yhi; ++Y) {
         const int y = Y - fr.o;
         if (y < 0 || y >= fr.F) continue;
-        for (int X = xlo; X <= xhi; ++X) {
+        // distances of the row's candidates from the pixel: a step in X moves them by (cos, sin)
+        double dx, dy;
+        fm.map((double)xlo, (double)Y, dx, dy);
+        dx -= (double)PX;
+        dy -= (double)PY;
+        for (int X = xlo; X <= xhi; ++X, dx += fm.cs, dy += fm.sn) {
             const int x = X - fr.o;
-            if (x < 0 || x >= fr.F) continue;
-            double ux, uy;
-            fm.map((double)X, (double)Y, ux, uy);
-            // the same corner weights as the read: (1 - t) towards the lower corner
-            const double fx = floor(ux), fy = floor(uy);
-            const int X0 = (int)fx, Y0 = (int)fy;
-            if ((PX != X0 && PX != X0 + 1) || (PY != Y0 && PY != Y0 + 1)) continue;
-            const float tx = (float)(ux - fx), ty = (float)(uy - fy);
-            const float wx = PX == X0 ? 1.f - tx : tx, wy = PY == Y0 ? 1.f - ty : ty;
-            acc += gi[(long long)y * fr.F + x] * (wx * wy);
+            // the corner weights of the read: 1 - distance, nothing from a pixel away on
+            const double wx = 1.0 - fabs(dx), wy = 1.0 - fabs(dy);
+            if (x < 0 || x >= fr.F || !(wx > 0.0) || !(wy > 0.0)) continue;
+            acc += gi[(long long)y * fr.F + x] * ((float)wx * (float)wy);
         }
     }
     return acc;
@@ -808,6 +807,7 @@ __global__ void k_finalize_h_sum(int nchunk, int N, const float *__restrict__ pa
     const int pix = blockIdx.x * blockDim.x + threadIdx.x;
     if (pix >= N * N) return;
     float acc = prior ? prior[pix] : 0.f;
+    #pragma unroll 8
     for (int c = 0; c < nchunk; ++c) acc += part[(long long)c * N * N + pix];
     grad_h[pix] = acc;
 }

@@ -94,6 +94,7 @@ __global__ void k_noise_moments(int nb, long long count, const float *__restrict
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= count) return;
     double a = s1[q], b2 = s2[q];
+    #pragma unroll 8
     for (int b = 0; b < nb; ++b) {
         const double c = coeffs[(long long)b * count + q];
         a += c;

@@ -43,8 +43,11 @@ int fail_hip(hipError_t e, const char *where)
 
 // s_sleep periods of the idle lead-in that stage timing puts before each call
 constexpr int kProfIdleIters = 300;
-// noise propagation: realizations per batch
-constexpr int kNoiseBatch = 32;
+// noise propagation: realizations per batch, as many as kNoiseValues coefficients hold (a
+// batch is ten launches whatever its size; 64 realizations of 128^2 with six planes, 206 us
+// in batches of 32)
+constexpr int kNoiseBatch = 64;
+constexpr long long kNoiseValues = 64LL << 20;
 
 #define HIP_TRY(expr)                                     \
     do {                                                  \
@@ -2208,7 +2211,7 @@ int starred_noise_weights(starred_plan *p, int32_t frame, const float *sigma2_da
     const int n = p->n[frame], K = p->K[frame], s = p->s, F = s * n, N = p->N, J = p->J;
     const int o = (N - F) / 2;
     const long long FF = (long long)F * F, NN = (long long)N * N;
-    const int B = std::min(n_real, kNoiseBatch);
+    const int B = (int)std::max(1LL, std::min((long long)std::min(n_real, kNoiseBatch), std::max(32LL, kNoiseValues / (J * NN))));
     if (!p->noise_aux || p->noise_frame != frame || p->noise_B < B) {
         if (p->noise_aux) {
             (void)starred_plan_destroy(p->noise_aux);
@@ -2263,10 +2266,12 @@ int starred_noise_weights(starred_plan *p, int32_t frame, const float *sigma2_da
                                   p->nz_delta));
         int rc = starred_convolve_subsample_adj(p->noise_aux, p->nz_delta, p->nz_g);
         if (rc) return rc;
-        HIP_TRY(launch_noise_embed(p->st, B, F, N, o, p->nz_g, p->nz_img));
-        StarArgs a = star_args(p, nb, p->nz_img);
+        // (a window that is the whole grid needs no embedding)
+        const float *img = F == N ? p->nz_g : p->nz_img;
+        if (F != N) HIP_TRY(launch_noise_embed(p->st, B, F, N, o, p->nz_g, p->nz_img));
+        StarArgs a = star_args(p, nb, img);
         a.fp64 = false;  // as the fields are
-        a.img1 = p->nz_img + NN;
+        a.img1 = img + NN;
         a.coeffs = p->nz_coef;
         a.ca = p->nz_ca;
         a.cb = p->nz_cb;
