@@ -135,6 +135,7 @@ hipError_t launch_idle(hipStream_t st, int iters);
 struct StarArgs;
 bool star_fp64(int N, int J);                // whether one or two images are transformed in FP64
 int star_l1_slots(const StarArgs &a);        // FP64 L1 partials per image
+bool star_rides(const StarArgs &a);          // the passes may ride in other launches
 hipError_t launch_star_forward(hipStream_t st, const StarArgs &a);
 hipError_t launch_star_adjoint(hipStream_t st, const StarArgs &a);
 // Starlet prior through the per-scale composite filters (starred_starlet.hip)
@@ -200,18 +201,23 @@ hipError_t launch_history(hipStream_t st, long long n, const float *xn, float *x
 hipError_t launch_psf_render(hipStream_t st, int N, const float *params, float *s_out);
 // dm (or null): the Moffat derivatives per pixel, [5][N^2]; tick (or null): the step
 // counter, advanced by this launch
+// star (or null): a pass of the starlet prior carried by the launch; in finalize the last
+// pass, whose pixels are the prior's gradient (else read from prior)
+struct StarPiece;
 hipError_t launch_psf_render64(hipStream_t st, int N, const float *params, double *s64, float *dm,
-                               int *tick = nullptr);
+                               int *tick = nullptr, const StarPiece *star = nullptr);
 // model (or null): the star models alone into model (S x n^2; data, invvar, rho and part unused)
 hipError_t launch_psf_fwd(hipStream_t st, int S, int n, int ss, int N, float sigma, const float *params,
                           const double *s64, const float *data, const float *invvar, float *rho, double *part,
-                          float *model = nullptr);
+                          float *model = nullptr, const StarPiece *star = nullptr);
 hipError_t launch_psf_adjsum(hipStream_t st, int S, int n, int ss, int N, float sigma, const float *params,
-                             const float *rho, const float *dm, float *grad, double *part_eta);
+                             const float *rho, const float *dm, float *grad, double *part_eta,
+                             const StarPiece *star = nullptr);
 // the loss, the gradient's small blocks, grad_b += prior, and (adam.params non-null) the update
 hipError_t launch_psf_finalize(hipStream_t st, int S, int N, int tiles, const double *part, int n_l1,
                                const double *part_l1, int n_eta, const double *part_eta, const float *params,
-                               const float *prior, float *grad, double *loss, const AdamDev &adam = AdamDev());
+                               const float *prior, float *grad, double *loss, const AdamDev &adam = AdamDev(),
+                               const StarPiece *star = nullptr);
 int psf_fwd_tiles(int n);   // forward tiles per star (four FP64 partials each)
 int psf_adj_tiles(int N);   // adjoint tiles (five FP64 partials each)
 size_t psf_fwd_lds(int s);

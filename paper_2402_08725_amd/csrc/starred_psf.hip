@@ -13,6 +13,8 @@
 // of stars still fill the chip; every reduction runs in a fixed order.
 #include "starred_internal.h"
 #include "starred_fft.h"
+#include "starred_finalize.h"
+#include "starred_scales.h"
 
 #include <hip/hip_runtime.h>
 
@@ -115,9 +117,12 @@ __device__ __forceinline__ void psf_taps(float c, int s, float sigma, int T, flo
 // dm (or null): the Moffat derivatives dm/deta per pixel, [5][N^2], for the adjoint.
 // tick (or null): the step counter, advanced here (the step's first launch) for the
 // update at its end.
-__global__ void k_psf_render64(int N, const float *__restrict__ params, double *__restrict__ s64,
-                               float *__restrict__ dm, int *__restrict__ tick)
+__global__ __launch_bounds__(256) void k_psf_render64(int N, const float *__restrict__ params, double *__restrict__ s64,
+                               float *__restrict__ dm, int *__restrict__ tick, StarPiece star)
 {
+    extern __shared__ double slds[];
+    __shared__ double sred[256 / 64];
+    if (star_piece_run<256>(star, slds, sred)) return;  // a pass of the starlet prior carried by this launch
     const int pix = blockIdx.x * blockDim.x + threadIdx.x;
     const long long NN = (long long)N * N;
     if (pix >= NN) return;
@@ -132,9 +137,23 @@ __global__ void k_psf_render64(int N, const float *__restrict__ params, double *
     }
 }
 
-hipError_t launch_psf_render64(hipStream_t st, int N, const float *params, double *s64, float *dm, int *tick)
+// the carried pass behind a launch's `main` work groups, and its LDS
+static StarPiece psf_piece(const StarPiece *star, int main, size_t *lds)
 {
-    hipLaunchKernelGGL(k_psf_render64, dim3((N * N + 255) / 256), dim3(256), 0, st, N, params, s64, dm, tick);
+    StarPiece p;
+    if (star) p = *star;
+    p.first = main;
+    *lds = std::max(*lds, p.lds());
+    return p;
+}
+
+hipError_t launch_psf_render64(hipStream_t st, int N, const float *params, double *s64, float *dm, int *tick,
+                               const StarPiece *star)
+{
+    const int main = (N * N + 255) / 256;
+    size_t lds = 0;
+    const StarPiece p = psf_piece(star, main, &lds);
+    hipLaunchKernelGGL(k_psf_render64, dim3(main + p.jobs), dim3(256), lds, st, N, params, s64, dm, tick, p);
     return hipGetLastError();
 }
 
@@ -186,16 +205,19 @@ template <int SS>
 __global__ __launch_bounds__(kPsfThreads) void k_psf_fwd(
     int S, int n, int N, float sigma, const float *__restrict__ params,
     const double *__restrict__ s64, const float *__restrict__ data, const float *__restrict__ invvar,
-    float *__restrict__ rho, double *__restrict__ part, float *__restrict__ model)
+    float *__restrict__ rho, double *__restrict__ part, float *__restrict__ model, int tp, int tq, StarPiece star)
 {
     using Win = PsfFwdWin<SS>;
     constexpr int T = Win::T, RM = Win::RM, CM = Win::CM, QT = kPsfColTile;
     extern __shared__ double smd[];
     __shared__ double G[2][kPsfMaxT], dG[2][kPsfMaxT];
     __shared__ double red[kPsfThreads / 64][4];
-    const int k = blockIdx.z;
+    __shared__ double sred[kPsfThreads / 64];
+    if (star_piece_run<kPsfThreads>(star, smd, sred)) return;  // a pass of the starlet prior
+    // work groups: tile rows fastest, then tile columns (tp x tq tiles), then stars
+    const int k = blockIdx.x / (tp * tq), bq = blockIdx.x / tp % tq, bp = blockIdx.x % tp;
     const long long NN = (long long)N * N;
-    const int p0 = blockIdx.x * kPsfRowChunk, q0 = blockIdx.y * QT;
+    const int p0 = bp * kPsfRowChunk, q0 = bq * QT;
     // this thread's data pixel, loaded first: it does not depend on the star's centre
     const int pl = threadIdx.x / QT, ql = threadIdx.x % QT;
     const bool own = p0 + pl < n && q0 + ql < n;
@@ -287,7 +309,7 @@ __global__ __launch_bounds__(kPsfThreads) void k_psf_fwd(
     }
     block_sum_vec<kPsfThreads, 4>(sums, red);
     if (threadIdx.x == 0 && part) {
-        double *o = part + ((long long)k * gridDim.x * gridDim.y + (long long)blockIdx.y * gridDim.x + blockIdx.x) * 4;
+        double *o = part + ((long long)k * tp * tq + (long long)bq * tp + bp) * 4;
 #pragma unroll
         for (int j = 0; j < 4; ++j) o[j] = sums[j];
     }
@@ -337,11 +359,11 @@ __global__ __launch_bounds__(kPsfAdjThreads) void k_psf_adjsum(int S, int n, int
                                                                const float *__restrict__ rho,
                                                                const float *__restrict__ dm,
                                                                float *__restrict__ grad,
-                                                               double *__restrict__ part_eta)
+                                                               double *__restrict__ part_eta, int tx, StarPiece star)
 {
     using Win = PsfAdjWin<SS>;
     constexpr int T = Win::T, PR = Win::PR, QC = Win::QC, KT = Win::KT, TX = kPsfAdjTx;
-    extern __shared__ float sm[];
+    extern __shared__ __align__(16) float sm[];
     __shared__ double red[kPsfAdjThreads / 64][5];
     int *sp = (int *)sm;                    // per star: first residual row, first column, floor(cx), floor(cy)
     float *sa = sm + 4 * kb;                // a_k
@@ -350,7 +372,9 @@ __global__ __launch_bounds__(kPsfAdjThreads) void k_psf_adjsum(int S, int n, int
     float *Rt = Gt + 2 * kb * T;            // residual windows [kb][PR][QC]
     float *U = Rt + (size_t)kb * PR * QC;   // [kb][PR][TX]
     const long long NN = (long long)N * N;
-    const int X0 = blockIdx.x * TX, Y0 = blockIdx.y * kPsfAdjTy;
+    __shared__ double sred[kPsfAdjThreads / 64];
+    if (star_piece_run<kPsfAdjThreads>(star, sm, sred)) return;  // a pass of the starlet prior
+    const int X0 = blockIdx.x % tx * TX, Y0 = blockIdx.x / tx * kPsfAdjTy;
     const int pix_l = threadIdx.x % kPsfAdjPix, grp = threadIdx.x / kPsfAdjPix;
     const int xl = pix_l % TX, yl = pix_l / TX;
     const int xp = X0 + xl, yp = Y0 + yl;
@@ -477,7 +501,7 @@ __global__ __launch_bounds__(kPsfAdjThreads) void k_psf_adjsum(int S, int n, int
     }
     block_sum_vec<kPsfAdjThreads, 5>(de, red);
     if (threadIdx.x == 0) {
-        const long long tile = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+        const long long tile = blockIdx.x;
 #pragma unroll
         for (int e = 0; e < 5; ++e) part_eta[tile * 5 + e] = de[e];
     }
@@ -497,23 +521,32 @@ __global__ __launch_bounds__(256) void k_psf_finalize(int S, int N, int tiles, c
                                                       const float *params,  // updated through ad.params
                                                       const float *__restrict__ prior,
                                                       float *__restrict__ grad, double *__restrict__ loss,
-                                                      AdamDev ad)
+                                                      AdamDev ad, StarPiece star)
 {
     if (blockIdx.x > 0) {
         const long long NN = (long long)N * N;
+        float bc1, bc2;
+        adam_bias(ad, bc1, bc2);
+        auto pixel = [&](long long i, float pg) {
+            const float g = grad[5 + i] + pg;
+            grad[5 + i] = g;
+            if (ad.params) {
+                float pi = ad.params[5 + i], mi = ad.m[5 + i], vi = ad.v[5 + i];
+                adam_update(pi, mi, vi, g, ad.lr[1], ad.beta1, ad.beta2, bc1, bc2, ad.eps, ad.rule == 1, ad.eps_root);
+                ad.m[5 + i] = mi;
+                ad.v[5 + i] = vi;
+                ad.params[5 + i] = pi;
+            }
+        };
+        if (star.group >= 0) {
+            // the prior's last pass, tile by tile: its pixels go straight into the gradient
+            extern __shared__ double slds[];
+            star_piece_adjoint<256>(star, blockIdx.x - 1, slds, pixel);
+            return;
+        }
         const long long i = (long long)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
         if (!grad || i >= NN) return;
-        const float g = grad[5 + i] + (prior ? prior[i] : 0.f);
-        grad[5 + i] = g;
-        if (ad.params) {
-            const float t = (float)(*ad.d_t);
-            const float bc1 = 1.f - powf(ad.beta1, t), bc2 = 1.f - powf(ad.beta2, t);
-            float pi = ad.params[5 + i], mi = ad.m[5 + i], vi = ad.v[5 + i];
-            adam_update(pi, mi, vi, g, ad.lr[1], ad.beta1, ad.beta2, bc1, bc2, ad.eps, ad.rule == 1, ad.eps_root);
-            ad.m[5 + i] = mi;
-            ad.v[5 + i] = vi;
-            ad.params[5 + i] = pi;
-        }
+        pixel(i, prior ? prior[i] : 0.f);
         return;
     }
     const long long NN = (long long)N * N;
@@ -604,34 +637,39 @@ __global__ __launch_bounds__(256) void k_psf_finalize(int S, int N, int tiles, c
 
 hipError_t launch_psf_fwd(hipStream_t st, int S, int n, int ss, int N, float sigma, const float *params,
                           const double *s64, const float *data, const float *invvar, float *rho, double *part,
-                          float *model)
+                          float *model, const StarPiece *star)
 {
-    const dim3 grid((n + kPsfRowChunk - 1) / kPsfRowChunk, (n + kPsfColTile - 1) / kPsfColTile, S);
+    const int tp = (n + kPsfRowChunk - 1) / kPsfRowChunk, tq = (n + kPsfColTile - 1) / kPsfColTile;
+    size_t lds = psf_fwd_lds(ss);
+    const StarPiece p = psf_piece(star, tp * tq * S, &lds);
     auto kern = ss == 1 ? k_psf_fwd<1> : ss == 2 ? k_psf_fwd<2> : k_psf_fwd<3>;
-    hipLaunchKernelGGL(kern, grid, dim3(kPsfThreads), psf_fwd_lds(ss), st, S, n, N, sigma, params, s64, data, invvar,
-                       rho, part, model);
+    hipLaunchKernelGGL(kern, dim3(tp * tq * S + p.jobs), dim3(kPsfThreads), lds, st, S, n, N, sigma, params, s64, data,
+                       invvar, rho, part, model, tp, tq, p);
     return hipGetLastError();
 }
 
 hipError_t launch_psf_adjsum(hipStream_t st, int S, int n, int ss, int N, float sigma, const float *params,
-                             const float *rho, const float *dm, float *grad, double *part_eta)
+                             const float *rho, const float *dm, float *grad, double *part_eta, const StarPiece *star)
 {
-    const int kb = psf_adj_batch(ss, S);
-    const dim3 grid((N + kPsfAdjTx - 1) / kPsfAdjTx, (N + kPsfAdjTy - 1) / kPsfAdjTy);
+    const int kb = psf_adj_batch(ss, S), tx = (N + kPsfAdjTx - 1) / kPsfAdjTx;
+    size_t lds = psf_adj_per_star(ss) * kb;
+    const StarPiece p = psf_piece(star, psf_adj_tiles(N), &lds);
     auto kern = ss == 1 ? k_psf_adjsum<1> : ss == 2 ? k_psf_adjsum<2> : k_psf_adjsum<3>;
-    hipLaunchKernelGGL(kern, grid, dim3(kPsfAdjThreads), psf_adj_per_star(ss) * kb, st, S, n, N, sigma, kb, params,
-                       rho, dm, grad, part_eta);
+    hipLaunchKernelGGL(kern, dim3(psf_adj_tiles(N) + p.jobs), dim3(kPsfAdjThreads), lds, st, S, n, N, sigma, kb, params,
+                       rho, dm, grad, part_eta, tx, p);
     return hipGetLastError();
 }
 
 hipError_t launch_psf_finalize(hipStream_t st, int S, int N, int tiles, const double *part, int n_l1,
                                const double *part_l1, int n_eta, const double *part_eta, const float *params,
-                               const float *prior, float *grad, double *loss, const AdamDev &adam)
+                               const float *prior, float *grad, double *loss, const AdamDev &adam, const StarPiece *star)
 {
     const long long NN = (long long)N * N;
-    const unsigned groups = grad ? 1 + (unsigned)((NN + 255) / 256) : 1;
-    hipLaunchKernelGGL(k_psf_finalize, dim3(groups), dim3(256), 0, st, S, N, tiles, part, n_l1, part_l1, n_eta,
-                       part_eta, params, prior, grad, loss, adam);
+    size_t lds = 0;
+    const StarPiece p = psf_piece(star, 1, &lds);
+    const unsigned groups = grad ? 1 + (p.group >= 0 ? (unsigned)p.jobs : (unsigned)((NN + 255) / 256)) : 1;
+    hipLaunchKernelGGL(k_psf_finalize, dim3(groups), dim3(256), lds, st, S, N, tiles, part, n_l1, part_l1, n_eta,
+                       part_eta, params, prior, grad, loss, adam, p);
     return hipGetLastError();
 }
 

@@ -302,27 +302,33 @@ __device__ __forceinline__ void star_forward(const StarArgs &a, int g, int job, 
 }
 
 // ---- transposed pass (the last group first) ----
-template <class V, int L, int T, int NT, int l = L - 1>
+// out(pixel, value) takes the transpose's pixels as the first group's pass forms them
+struct StarStore {
+    float *out;
+    __device__ void operator()(long long pix, float v) const { out[pix] = v; }
+};
+
+template <class V, int L, int T, int NT, class Out, int l = L - 1>
 __device__ __forceinline__ void star_adjoint_level(const StarArgs &a, int g, const StarArgs::Group &q, const StarJob &j,
-                                                   const float *z, V *region, V *tmp)
+                                                   const float *z, V *region, V *tmp, Out out)
 {
     if constexpr (l >= 0) {
         constexpr int H = StarShape<L, T>::H, R = StarShape<L, T>::R;
         // (levels above this one took 2 (2^L - 2^(l+1)) pixels off each side)
-        constexpr int e = 1 << l, lo = 2 * ((1 << L) - (2 << l)), hi = R - lo, in = lo + 2 * e, out = hi - 2 * e;
+        constexpr int e = 1 << l, lo = 2 * ((1 << L) - (2 << l)), hi = R - lo, in = lo + 2 * e, end = hi - 2 * e;
         const int N = a.N;
         const long long NN = (long long)N * N;
         // what joins the filtered value: z_j, less the next level's (on its way during the rows)
-        float zl[StarCount<NT, in, out, in, out>::n][2];
-        star_each<NT, in, out, in, out>([&](int r, int c, int k, bool) {
+        float zl[StarCount<NT, in, end, in, end>::n][2];
+        star_each<NT, in, end, in, end>([&](int r, int c, int k, bool) {
             const int y = star_mirror(j.ry + q.D * (j.ty + r - H), N), x = star_mirror(j.rx + q.D * (j.tx + c - H), N);
             const float *p = z + (q.l0 + l) * NN + y * N + x;
             zl[k][0] = p[0];
             zl[k][1] = l > 0 ? p[-NN] : 0.f;
         });
-        star_filter<V, NT, lo, hi, in, out, R>(region, tmp, e);
+        star_filter<V, NT, lo, hi, in, end, R>(region, tmp, e);
         __syncthreads();
-        star_each<NT, in, out, in, out>([&](int r, int c, int k, bool) {
+        star_each<NT, in, end, in, end>([&](int r, int c, int k, bool) {
             const int y = j.ry + q.D * (j.ty + r - H), x = j.rx + q.D * (j.tx + c - H);
             const V s = star_end<V>(star_mirror(y, N), N) * star_end<V>(star_mirror(x, N), N);
             const V v = fma((V)zl[k][0] - (V)zl[k][1], s, star_b3(tmp + r * R + c, e * R));
@@ -331,16 +337,16 @@ __device__ __forceinline__ void star_adjoint_level(const StarArgs &a, int g, con
             } else if (y < N && x < N) {
                 const long long pix = (long long)y * N + x;
                 if (g > 0) ((V *)((g & 1) ? a.ca : a.cb))[j.b * NN + pix] = v;
-                else a.out[j.b * NN + pix] = (float)(v / s);
+                else out(j.b * NN + pix, (float)(v / s));
             }
         });
         __syncthreads();
-        star_adjoint_level<V, L, T, NT, l - 1>(a, g, q, j, z, region, tmp);
+        star_adjoint_level<V, L, T, NT, Out, l - 1>(a, g, q, j, z, region, tmp, out);
     }
 }
 
-template <class V, int L, int T, int NT>
-__device__ __forceinline__ void star_adjoint(const StarArgs &a, int g, int job, V *lds)
+template <class V, int L, int T, int NT, class Out>
+__device__ __forceinline__ void star_adjoint(const StarArgs &a, int g, int job, V *lds, Out out)
 {
     constexpr int R = StarShape<L, T>::R;
     const StarArgs::Group q = a.group(g);
@@ -366,7 +372,46 @@ __device__ __forceinline__ void star_adjoint(const StarArgs &a, int g, int job, 
         });
     }
     __syncthreads();
-    star_adjoint_level<V, L, T, NT>(a, g, q, j, z, region, tmp);
+    star_adjoint_level<V, L, T, NT>(a, g, q, j, z, region, tmp, out);
+}
+
+// One FP64 pass carried by another launch: its work groups first .. first+jobs-1 run the
+// pass's jobs (groups of up to three levels, lds() bytes of dynamic LDS).
+struct StarPiece {
+    StarArgs a;
+    int group = -1;  // -1: none
+    bool adjoint = false;
+    int first = 0, jobs = 0;
+    size_t lds() const { return group < 0 ? 0 : a.group(group).lds(); }
+};
+
+// Runs job `job` of a transposed pass, its pixels into out.
+template <int NT, class Out>
+__device__ __forceinline__ void star_piece_adjoint(const StarPiece &p, int job, void *lds, Out out)
+{
+    switch (p.a.group(p.group).L) {
+    case 1: star_adjoint<double, 1, kStarTile, NT>(p.a, p.group, job, (double *)lds, out); break;
+    case 2: star_adjoint<double, 2, kStarTile, NT>(p.a, p.group, job, (double *)lds, out); break;
+    default: star_adjoint<double, 3, kStarTile, NT>(p.a, p.group, job, (double *)lds, out); break;
+    }
+}
+
+// Runs this work group's job when it carries one; true if it did.
+template <int NT>
+__device__ __forceinline__ bool star_piece_run(const StarPiece &p, void *lds, double *red)
+{
+    const int job = (int)blockIdx.x - p.first;
+    if (p.group < 0 || job < 0 || job >= p.jobs) return false;
+    if (p.adjoint) {
+        star_piece_adjoint<NT>(p, job, lds, StarStore{p.a.out});
+        return true;
+    }
+    switch (p.a.group(p.group).L) {
+    case 1: star_forward<double, 1, kStarTile, NT>(p.a, p.group, job, (double *)lds, red); break;
+    case 2: star_forward<double, 2, kStarTile, NT>(p.a, p.group, job, (double *)lds, red); break;
+    default: star_forward<double, 3, kStarTile, NT>(p.a, p.group, job, (double *)lds, red); break;
+    }
+    return true;
 }
 
 }  // namespace starred

@@ -22,7 +22,7 @@ template <class V, int L, int T, int NT>
 __global__ __launch_bounds__(NT) void k_star_adjoint(StarArgs a, int g)
 {
     extern __shared__ double lds[];
-    star_adjoint<V, L, T, NT>(a, g, blockIdx.x, (V *)lds);
+    star_adjoint<V, L, T, NT>(a, g, blockIdx.x, (V *)lds, StarStore{a.out});
 }
 
 // J = 1: the only plane is the image itself.
@@ -82,6 +82,15 @@ int star_l1_slots(const StarArgs &a)
         default: return hipErrorInvalidValue;                        \
         }                                                            \
     } while (0)
+
+// the passes may be carried by other launches (StarPiece): at most four of them
+bool star_rides(const StarArgs &a)
+{
+    const int n = star_num_groups(a.J);
+    for (int g = 0; g < n; ++g)
+        if (a.group(g).L > 3) return false;
+    return a.fp64 && n > 0 && n <= 2;
+}
 
 hipError_t launch_star_forward(hipStream_t st, const StarArgs &a)
 {
