@@ -101,7 +101,7 @@ def fft_kernel_bytes(prob, fused_classes, keep=None):
 
 
 FFT_KERNEL_NAMES = {
-    "fft_fused": "k_frame_fwd (one-launch forward per frame: spectral product, inverse 2-D transform, "
+    "fft_fused": "k_frame (one-launch forward per frame: spectral product, inverse 2-D transform, "
                  "residual, chi-square, forward 2-D transform of rho)",
     "fft_spec": "k_spec_fwd (spectral product and alias fold)",
     "fft_mcols": "k_lines<OpMCols> (inverse columns of the model spectra)",
