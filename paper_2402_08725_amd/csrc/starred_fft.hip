@@ -510,6 +510,10 @@ struct OpKCols {
 // the Q-point transform run on one line in LDS: no spectrum of the P or Q grid goes through
 // memory between them.
 // LDS: two planes of nl lines of P + 1 (transform and scratch) and nl lines of Q + 1.
+// Bound by the LDS passes of the P-point transforms and by the row spectra's way through memory.
+// Models and back-projected residuals of 60 frames (64^2 and 90^2, s = 2): 205 us with a launch
+// per pass and whole spectra between them, 165 with these and the rows in pairs; loss and gradient
+// of 100 shifted frames of 64^2 265 -> 217.
 
 // rows of scene spectra [F][P/2+1] -> rows of model spectra [n][Q/2+1]
 template <int S>
@@ -1006,7 +1010,10 @@ __device__ void tables_part(const ClassFft &c, const float2 *__restrict__ tw, co
 // sources, otherwise), folds V with the x-tables and reduces the dot products once per
 // group of SB sources through LDS. Each pass reads the chunk's spectra again, so fewer,
 // wider passes save reads. The per-block partials are summed per frame (and the chunk
-// spectra over chunks) by k_adj_sums.
+// spectra over chunks) by k_adj_sums. One source, eight frames per chunk: bound by memory (1000
+// frames of 32^2 .. 128^2: 260 MB in 49 us, 5.3 TB/s, what a plain copy reaches; 61 us from half
+// spectra in row order, which took s^2 narrow loads and their index arithmetic per bin); many
+// sources: by the column sums' registers (12 frames of 256^2, 30 sources: 72 us).
 template <int S, int FC, int SB>
 __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restrict__ items,
                                                           const float2 *__restrict__ Sp,

@@ -736,7 +736,10 @@ constexpr int kFinChunkXf = 4;  // the same for frames under transforms (25 cand
 // Transpose of the bilinear read of frame i at grid pixel (PX, PY): the sum of
 // g_i(X) times the weight with which frame pixel X read h there, over the frame
 // pixels whose transformed position lies within one pixel of (PX, PY) on both axes
-// (a gather in a fixed order: the candidates around the preimage of the pixel).
+// (a gather in a fixed order: the candidates around the preimage of the pixel). Bound by the
+// candidates' arithmetic: the weights come from the distances, and a block's frame maps (a sine
+// and cosine each) are formed once in LDS; loss and gradient of 100 shifted frames of 64^2
+// 217 -> 197 us.
 __device__ float transpose_bilerp(const FrameDev &fr, const FrameMap &fm, const float *__restrict__ g, int PX, int PY)
 {
     const double ex = (double)PX - fm.C - fm.dx, ey = (double)PY - fm.C - fm.dy;
