@@ -1285,6 +1285,7 @@ int starred_set_frames(starred_plan *p, const float *data, const float *inv_var,
     p->invvar = inv_var;
     p->W = W;
     p->psf_bound = psf;
+    p->noise_frame = -1;  // (its plan holds a kernel of the frames bound before)
     if (p->plain_ready) {
         HIP_TRY(launch_prep_kernels(p->st, p->d_frp, p->frp.data(), p->E, 1, psf, p->d_pkf, p->d_pka));
     }
