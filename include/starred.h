@@ -413,8 +413,11 @@ int starred_profile_read(starred_plan *plan, double *ms_out, int64_t *count_out)
  * draw them on the device: draw k of realization r is the Box-Muller value of
  * Philox4x32-10 with counter (k/4, r, 0, 0) and key (seed low, seed high), words
  * mapped to ((w >> 8) + 1/2) / 2^24, pairs (0,1) and (2,3), cosine then sine.
- * n_real >= 2. The plan allocates its working memory on the first call (kept
- * until destroy); the call synchronises the plan's stream. */
+ * n_real >= 2. The plan allocates its working memory on the first call and keeps
+ * one set (until a frame of other sides or a larger n_real, up to a batch, replaces
+ * it, or until destroy); the psf kernels passed to starred_set_frames must stay valid
+ * (the frame's is read on its first call after each binding). The call synchronises
+ * the plan's stream. */
 int starred_noise_weights(starred_plan *plan, int32_t frame, const float *sigma2_data, int32_t n_real,
                           uint64_t seed, const float *normals, int32_t per_pixel, float *W_out);
 

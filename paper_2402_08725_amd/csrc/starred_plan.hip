@@ -64,8 +64,9 @@ int dev_alloc(T **p, size_t count)
     *p = nullptr;
     if (count == 0) count = 1;
     hipError_t e = hipMalloc((void **)p, count * sizeof(T));
-    if (e != hipSuccess) return fail_hip(e, "hipMalloc");
-    return STARRED_OK;
+    if (e == hipSuccess) return STARRED_OK;
+    (void)hipGetLastError();  // reported here: the next launch's check must not find it again
+    return fail_hip(e, "hipMalloc");
 }
 
 }  // namespace
@@ -112,9 +113,12 @@ struct starred_plan {
     int hpart_chunks = 0;  // partial planes d_hpart holds
     double *d_gxfp = nullptr;  // partials of the transforms' gradient
     std::vector<void *> owned;
-    // noise propagation: an s = 1 plan applying S_f^T to a batch of noise fields
+    // noise propagation: an s = 1 plan applying S_f^T to noise_B noise fields of side noise_n
+    // with a kernel of side noise_K, the buffers of such a batch, and the frame whose kernel the
+    // plan holds (-1: none)
     starred_plan *noise_aux = nullptr;
-    int noise_frame = -1, noise_B = 0;
+    int noise_n = 0, noise_K = 0, noise_B = 0, noise_frame = -1;
+    std::vector<void *> noise_owned;
     float *nz_kern = nullptr, *nz_zero = nullptr, *nz_one = nullptr, *nz_w = nullptr;
     float *nz_delta = nullptr, *nz_g = nullptr, *nz_img = nullptr, *nz_ca = nullptr, *nz_cb = nullptr;
     float *nz_coef = nullptr;
@@ -284,6 +288,22 @@ struct starred_plan {
     {
         for (void *q : list_owned) (void)hipFree(q);
         list_owned.clear();
+    }
+    template <typename T>
+    int alloc_noise(T **p, size_t count)
+    {
+        int rc = dev_alloc(p, count);
+        if (rc == STARRED_OK) noise_owned.push_back((void *)*p);
+        return rc;
+    }
+    void free_noise()
+    {
+        if (noise_aux) (void)starred_plan_destroy(noise_aux);
+        noise_aux = nullptr;
+        for (void *q : noise_owned) (void)hipFree(q);
+        noise_owned.clear();
+        noise_n = noise_K = noise_B = 0;
+        noise_frame = -1;
     }
 };
 
@@ -1083,7 +1103,7 @@ int starred_plan_create(const starred_desc *desc, void *stream, starred_plan **p
 
 starred_plan::~starred_plan()
 {
-    if (noise_aux) (void)starred_plan_destroy(noise_aux);
+    free_noise();
     destroy_members();
 }
 
@@ -2229,23 +2249,15 @@ int starred_set_graph_mode(starred_plan *p, int32_t enable)
     return STARRED_OK;
 }
 
-int starred_noise_weights(starred_plan *p, int32_t frame, const float *sigma2_data, int32_t n_real, uint64_t seed,
-                          const float *normals, int32_t per_pixel, float *W_out)
+// The noise plan and buffers for batches of B fields of one frame. What a call before left is
+// kept where it serves (the same sides, B fields or more; the same frame and binding: its kernel
+// too) and freed where it does not; after a failure nothing is held that the next call would use.
+static int noise_prepare(starred_plan *p, int frame, int B)
 {
-    if (!p || !sigma2_data || !W_out) return fail(STARRED_EINVAL, "NULL argument");
-    if (p->mode != STARRED_DECONV) return fail(STARRED_EUNSUPPORTED, "noise propagation needs deconvolution mode");
-    if (!p->frames_set) return fail(STARRED_ESTATE, "set_frames has not been called");
-    if (frame < 0 || frame >= p->E) return fail(STARRED_EINVAL, "frame out of range");
-    if (n_real < 2) return fail(STARRED_EINVAL, "n_real must be >= 2");
-    const int n = p->n[frame], K = p->K[frame], s = p->s, F = s * n, N = p->N, J = p->J;
-    const int o = (N - F) / 2;
-    const long long FF = (long long)F * F, NN = (long long)N * N;
-    const int B = (int)std::max(1LL, std::min((long long)std::min(n_real, kNoiseBatch), std::max(32LL, kNoiseValues / (J * NN))));
-    if (!p->noise_aux || p->noise_frame != frame || p->noise_B < B) {
-        if (p->noise_aux) {
-            (void)starred_plan_destroy(p->noise_aux);
-            p->noise_aux = nullptr;
-        }
+    const int K = p->K[frame], F = p->s * p->n[frame], N = p->N, J = p->J;
+    const long long FF = (long long)F * F, NN = (long long)N * N, kk = (long long)K * K;
+    if (!p->noise_aux || p->noise_n != F || p->noise_K != K || p->noise_B < B) {
+        p->free_noise();
         // S_f^T on the fine grid = the adjoint of an s = 1 plan with B copies of the frame
         std::vector<int32_t> sides(B, F), ks(B, K);
         starred_desc d{};
@@ -2262,39 +2274,60 @@ int starred_noise_weights(starred_plan *p, int32_t frame, const float *sigma2_da
         d.lambda = 0.0;
         d.gauss_fwhm = p->fwhm;
         int rc = starred_plan_create(&d, p->st, &p->noise_aux);
-        if (rc) return rc;
-        p->noise_frame = frame;
+        if (!rc) rc = p->alloc_noise(&p->nz_kern, (size_t)B * kk);
+        if (!rc) rc = p->alloc_noise(&p->nz_zero, (size_t)B * FF);
+        if (!rc) rc = p->alloc_noise(&p->nz_one, (size_t)B * FF);
+        if (!rc) rc = p->alloc_noise(&p->nz_w, (size_t)J);
+        if (!rc) rc = p->alloc_noise(&p->nz_delta, (size_t)B * FF);
+        if (!rc) rc = p->alloc_noise(&p->nz_g, (size_t)B * FF);
+        if (!rc) rc = p->alloc_noise(&p->nz_img, (size_t)B * NN);
+        if (!rc) rc = p->alloc_noise(&p->nz_ca, (size_t)B * NN);
+        if (!rc) rc = p->alloc_noise(&p->nz_cb, (size_t)B * NN);
+        if (!rc) rc = p->alloc_noise(&p->nz_coef, (size_t)B * J * NN);
+        if (!rc) rc = p->alloc_noise(&p->nz_s1, (size_t)J * NN);
+        if (!rc) rc = p->alloc_noise(&p->nz_s2, (size_t)J * NN);
+        if (rc) {
+            p->free_noise();
+            return rc;
+        }
+        p->noise_n = F;
+        p->noise_K = K;
         p->noise_B = B;
-        const long long kk = (long long)K * K;
-        if ((rc = p->alloc(&p->nz_kern, (size_t)B * kk))) return rc;
-        if ((rc = p->alloc(&p->nz_zero, (size_t)B * FF))) return rc;
-        if ((rc = p->alloc(&p->nz_one, (size_t)B * FF))) return rc;
-        if ((rc = p->alloc(&p->nz_w, (size_t)J))) return rc;
-        if ((rc = p->alloc(&p->nz_delta, (size_t)B * FF))) return rc;
-        if ((rc = p->alloc(&p->nz_g, (size_t)B * FF))) return rc;
-        if ((rc = p->alloc(&p->nz_img, (size_t)B * NN))) return rc;
-        if ((rc = p->alloc(&p->nz_ca, (size_t)B * NN))) return rc;
-        if ((rc = p->alloc(&p->nz_cb, (size_t)B * NN))) return rc;
-        if ((rc = p->alloc(&p->nz_coef, (size_t)B * J * NN))) return rc;
-        if ((rc = p->alloc(&p->nz_s1, (size_t)J * NN))) return rc;
-        if ((rc = p->alloc(&p->nz_s2, (size_t)J * NN))) return rc;
-        const float *kf = p->psf_bound + p->fr[frame].kern_off;
-        for (int b = 0; b < B; ++b)
-            HIP_TRY(hipMemcpyAsync(p->nz_kern + b * kk, kf, sizeof(float) * kk, hipMemcpyDeviceToDevice, p->st));
-        HIP_TRY(launch_fill(p->st, p->nz_zero, (long long)B * FF, 0.f));
-        HIP_TRY(launch_fill(p->st, p->nz_one, (long long)B * FF, 1.f));
-        HIP_TRY(launch_fill(p->st, p->nz_w, J, 0.f));
-        rc = starred_set_frames(p->noise_aux, p->nz_zero, p->nz_one, p->nz_kern, p->nz_w);
-        if (rc) return rc;
     }
+    if (p->noise_frame == frame) return STARRED_OK;
+    p->noise_frame = -1;  // (until the kernel is in place)
+    const float *kf = p->psf_bound + p->fr[frame].kern_off;
+    for (int b = 0; b < p->noise_B; ++b)
+        HIP_TRY(hipMemcpyAsync(p->nz_kern + b * kk, kf, sizeof(float) * kk, hipMemcpyDeviceToDevice, p->st));
+    HIP_TRY(launch_fill(p->st, p->nz_zero, p->noise_B * FF, 0.f));
+    HIP_TRY(launch_fill(p->st, p->nz_one, p->noise_B * FF, 1.f));
+    HIP_TRY(launch_fill(p->st, p->nz_w, J, 0.f));
+    const int rc = starred_set_frames(p->noise_aux, p->nz_zero, p->nz_one, p->nz_kern, p->nz_w);
+    if (!rc) p->noise_frame = frame;
+    return rc;
+}
+
+int starred_noise_weights(starred_plan *p, int32_t frame, const float *sigma2_data, int32_t n_real, uint64_t seed,
+                          const float *normals, int32_t per_pixel, float *W_out)
+{
+    if (!p || !sigma2_data || !W_out) return fail(STARRED_EINVAL, "NULL argument");
+    if (p->mode != STARRED_DECONV) return fail(STARRED_EUNSUPPORTED, "noise propagation needs deconvolution mode");
+    if (!p->frames_set) return fail(STARRED_ESTATE, "set_frames has not been called");
+    if (frame < 0 || frame >= p->E) return fail(STARRED_EINVAL, "frame out of range");
+    if (n_real < 2) return fail(STARRED_EINVAL, "n_real must be >= 2");
+    const int n = p->n[frame], s = p->s, F = s * n, N = p->N, J = p->J;
+    const int o = (N - F) / 2;
+    const long long NN = (long long)N * N;
+    const int B = (int)std::max(1LL, std::min((long long)std::min(n_real, kNoiseBatch), std::max(32LL, kNoiseValues / (J * NN))));
+    int rc = noise_prepare(p, frame, B);
+    if (rc) return rc;
     HIP_TRY(launch_fill_d(p->st, p->nz_s1, (long long)J * NN));
     HIP_TRY(launch_fill_d(p->st, p->nz_s2, (long long)J * NN));
     for (int r0 = 0; r0 < n_real; r0 += B) {
         const int nb = std::min(B, n_real - r0);
         HIP_TRY(launch_noise_draw(p->st, B, nb, r0, n, s, sigma2_data, normals, (unsigned long long)seed,
                                   p->nz_delta));
-        int rc = starred_convolve_subsample_adj(p->noise_aux, p->nz_delta, p->nz_g);
-        if (rc) return rc;
+        if ((rc = starred_convolve_subsample_adj(p->noise_aux, p->nz_delta, p->nz_g))) return rc;
         // (a window that is the whole grid needs no embedding)
         const float *img = F == N ? p->nz_g : p->nz_img;
         if (F != N) HIP_TRY(launch_noise_embed(p->st, B, F, N, o, p->nz_g, p->nz_img));

@@ -34,6 +34,59 @@ L.starred_plan_destroy(h)
 """)
 
 
+def test_a_loop_over_frames_holds_one_set_of_buffers(tmp_path):
+    """Frames of another shape replace the buffers, those of the same shape use them."""
+    fake_hip.run(tmp_path, SETUP + """
+assert weights(2) == st.OK
+small = hip.fake_live_bytes()
+assert weights(0) == st.OK
+held, mallocs = hip.fake_live_bytes(), hip.fake_mallocs()
+assert weights(1) == st.OK and reads(psf, 1) > 0
+assert weights(0, 20) == st.OK
+assert (hip.fake_live_bytes(), hip.fake_mallocs()) == (held, mallocs)
+for frame in (2, 0, 1, 2):
+    assert weights(frame) == st.OK
+    assert hip.fake_live_bytes() == (small if frame == 2 else held)
+L.starred_plan_destroy(h)
+assert hip.fake_live_count() == 0
+""")
+
+
+def test_out_of_memory_leaves_nothing_half_made(tmp_path):
+    """Each allocation in turn fails, of a first call and of one that asks for a larger batch:
+    the call says so, and the next one has every buffer."""
+    fake_hip.run(tmp_path, SETUP + """
+base = hip.fake_live_bytes()
+for first in (0, 20):
+    k = 0
+    while True:
+        L.starred_plan_destroy(h)
+        h = make_plan(sides, ks, s, N, M, J)
+        bind(psf)
+        if first:
+            assert weights(0, first) == st.OK
+        k += 1
+        m = hip.fake_mallocs()
+        hip.fake_fail_malloc_in(k)
+        rc = weights(0)
+        hip.fake_fail_malloc_in(-1)
+        if rc == st.OK:
+            assert hip.fake_mallocs() - m < k  # (no allocation was left to fail)
+            break
+        assert rc in (st.ENOMEM, st.EHIP)
+        assert hip.fake_live_bytes() == base
+        m = hip.fake_mallocs()
+        assert weights(0) == st.OK
+        made, held = hip.fake_mallocs() - m, hip.fake_live_bytes()
+        if k > 1:
+            assert (made, held) == last
+        last = (made, held)
+    assert k > 12
+L.starred_plan_destroy(h)
+assert hip.fake_live_count() == 0
+""")
+
+
 @pytest.mark.gpu
 def test_weights_after_a_new_binding_equal_a_fresh_plan():
     torch = pytest.importorskip("torch")
