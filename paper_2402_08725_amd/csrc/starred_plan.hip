@@ -2216,12 +2216,10 @@ int starred_estimate_lambda_pts(starred_plan *p, const float *params, double *la
     sa.lam0 = 1.f;
     sa.fp64 = false;
     const int B = p->M + 2, slots = star_l1_slots(sa);
-    if (!p->est_img) {
-        int rc = p->alloc(&p->est_img, (size_t)B * NN);
-        if (!rc) rc = p->alloc(&p->est_part, (size_t)B * slots);
-        if (!rc) rc = p->alloc(&p->est_out, (size_t)B + p->M);
-        if (rc) return rc;
-    }
+    int rc = p->est_img ? STARRED_OK : p->alloc(&p->est_img, (size_t)B * NN);
+    if (!rc && !p->est_part) rc = p->alloc(&p->est_part, (size_t)B * slots);
+    if (!rc && !p->est_out) rc = p->alloc(&p->est_out, (size_t)B + p->M);
+    if (rc) return rc;
     HIP_TRY(launch_fill_d(p->st, p->est_part, (long long)B * slots));
     HIP_TRY(launch_pts_images(p->st, p->N, p->E, p->M, p->sigma, params, p->est_img));
     for (int b = 0; b < B; ++b) {
