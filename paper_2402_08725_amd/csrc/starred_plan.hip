@@ -1267,6 +1267,15 @@ int starred_set_frame_transforms(starred_plan *p, const float *xf, float *grad_x
     if (xf && !p->direct_ok)
         return fail(STARRED_EUNSUPPORTED, "per-frame transforms run the direct algorithm, whose tiles these kernels exceed");
     p->drop_graphs();
+    if (xf && p->hpart_chunks < finalize_h_chunks(p->E, true)) {
+        // transformed frames are summed into dL/dh in smaller chunks: more partial planes
+        const int chunks = finalize_h_chunks(p->E, true);
+        float *part = nullptr;
+        int rc = p->alloc(&part, (size_t)chunks * p->N * p->N);
+        if (rc) return rc;
+        p->d_hpart = part;
+        p->hpart_chunks = chunks;
+    }
     if (xf && !p->xf) {
         // every class onto the direct algorithm (the FFT path assumes untransformed windows)
         p->xf_prev_choice.resize(p->cls.size());
@@ -1281,12 +1290,6 @@ int starred_set_frame_transforms(starred_plan *p, const float *xf, float *grad_x
     p->xf = xf;
     p->gxf = xf ? grad_xf : nullptr;
     if (!xf) return STARRED_OK;
-    if (p->hpart_chunks < finalize_h_chunks(p->E, true)) {
-        // transformed frames are summed into dL/dh in smaller chunks: more partial planes
-        p->hpart_chunks = finalize_h_chunks(p->E, true);
-        int rc = p->alloc(&p->d_hpart, (size_t)p->hpart_chunks * p->N * p->N);
-        if (rc) return rc;
-    }
     int rc = choose_xf_algo(p, algo);
     p->drop_graphs();
     return rc;

@@ -27,3 +27,25 @@ for k in (1, 2, 3):
     assert hip.fake_mallocs() - m == 4 - k
     L.starred_plan_destroy(h)
 """)
+
+
+def test_set_frame_transforms(tmp_path):
+    """The partial planes of transformed frames: no memory for them leaves the plan without
+    transforms and with the planes it had."""
+    fake_hip.run(tmp_path, SETUP + """
+sides, ks = [12] * 40, [7] * 40
+nd = 40 * 144
+h = fresh()
+xf = f32(3 * 40)
+before = hip.fake_live_bytes()
+algo = ctypes.c_int32(-1)
+def info():
+    assert L.starred_frame_transforms_info(h, ctypes.byref(algo), None) == st.OK
+    return algo.value
+hip.fake_fail_malloc_in(1)
+assert L.starred_set_frame_transforms(h, ptr(xf), None, st.CONV_FFT) == st.ENOMEM
+assert info() == 0 and hip.fake_live_bytes() == before
+assert L.starred_set_frame_transforms(h, ptr(xf), None, st.CONV_FFT) == st.OK
+assert info() == st.CONV_FFT
+L.starred_plan_destroy(h)
+""")
