@@ -302,7 +302,8 @@ __device__ __forceinline__ void star_forward(const StarArgs &a, int g, int job, 
 }
 
 // ---- transposed pass (the last group first) ----
-// out(pixel, value) takes the transpose's pixels as the first group's pass forms them
+// out(pixel, value) takes the transpose's pixels as the first group's pass forms them, each
+// pixel once (it may add to what is there)
 struct StarStore {
     float *out;
     __device__ void operator()(long long pix, float v) const { out[pix] = v; }
@@ -328,13 +329,13 @@ __device__ __forceinline__ void star_adjoint_level(const StarArgs &a, int g, con
         });
         star_filter<V, NT, lo, hi, in, end, R>(region, tmp, e);
         __syncthreads();
-        star_each<NT, in, end, in, end>([&](int r, int c, int k, bool) {
+        star_each<NT, in, end, in, end>([&](int r, int c, int k, bool ok) {
             const int y = j.ry + q.D * (j.ty + r - H), x = j.rx + q.D * (j.tx + c - H);
             const V s = star_end<V>(star_mirror(y, N), N) * star_end<V>(star_mirror(x, N), N);
             const V v = fma((V)zl[k][0] - (V)zl[k][1], s, star_b3(tmp + r * R + c, e * R));
             if (l > 0) {
                 region[r * R + c] = v;
-            } else if (y < N && x < N) {
+            } else if (ok && y < N && x < N) {
                 const long long pix = (long long)y * N + x;
                 if (g > 0) ((V *)((g & 1) ? a.ca : a.cb))[j.b * NN + pix] = v;
                 else out(j.b * NN + pix, (float)(v / s));
