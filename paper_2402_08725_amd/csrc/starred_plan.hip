@@ -555,12 +555,26 @@ static bool smooth235(int v)
     return v == 1;
 }
 
-// smallest P >= need with P a multiple of 2s and P = 2^a 3^b 5^c, and with Q = P/s among
-// the lengths of the one-launch forward unless it is above them
-static int good_size(int need, int s)
+// a class of these lengths has the one-launch forward
+static bool frame_fits(int P, int s, int M, int per = 1)
 {
-    for (int P = need;; ++P)
-        if (P % (2 * s) == 0 && smooth235(P) && (P / s > kFrameMaxQ || frame_body_frames(P / s, s))) return P;
+    return frame_body_frames(P / s, s) && frame_lds_bytes(P / s, P, M, per) <= kFusedLdsMax;
+}
+
+// smallest P >= need with P a multiple of 2s and P = 2^a 3^b 5^c; where that has no one-launch
+// forward, the next one that has, for s = 1 and 2 or up to Q = 18. Q = 162 becomes 180 so: 300
+// frames of 100^2 (s = 1, one source) 213 -> 123 us, of 130^2 (s = 2) 304 -> 218 us. It stays
+// where the sources' tables leave no room at 180 (s = 2, four sources: 347 us, 354 at 180 on the
+// line passes) and for s = 3, whose spectra grow the most (one source: 412 us, 425 at 180).
+// Shorter ones than 18: 3000 frames of 8^2 (s = 1) 199 -> 135 us, of 6^2 (s = 3) 216 -> 192 us.
+static int good_size(int need, int s, int M)
+{
+    const auto smooth = [&](int P) { return P % (2 * s) == 0 && smooth235(P); };
+    int P = need;
+    while (!smooth(P)) ++P;
+    for (int R = P; R <= (s < 3 ? kFrameMaxQ : 18) * s; ++R)
+        if (smooth(R) && frame_fits(R, s, M)) return R;
+    return P;
 }
 
 static FftLen make_len(int L, std::map<int, long long> &tw_offsets, long long &tw_total)
@@ -607,7 +621,7 @@ static int build_fft(starred_plan *p)
             c.F = s * c.n;
             c.K = p->K[i];
             c.o = (p->N - c.F) / 2;
-            c.P = good_size(c.F + c.K / 2, s);
+            c.P = good_size(c.F + c.K / 2, s, p->M);
             c.Q = c.P / s;
             if (c.P > 4096) return fail(STARRED_EUNSUPPORTED, "FFT size above 4096");
             c.fP = make_len(c.P, tw_off, tw_total);
@@ -636,8 +650,7 @@ static int build_fft(starred_plan *p)
     for (auto &c : p->cls) {
         // (reported as 1 where a second plane would fit beside it, else 2)
         int fit = 0;
-        if (frame_body_frames(c.Q, s) && frame_lds_bytes(c.Q, c.P, p->M, 1) <= kFusedLdsMax)
-            fit = frame_lds_bytes(c.Q, c.P, p->M, 2) <= kFusedLdsMax ? 1 : 2;
+        if (frame_fits(c.P, s, p->M)) fit = frame_fits(c.P, s, p->M, 2) ? 1 : 2;
         p->cls_fits.push_back(fit);
         c.fused = fit ? 1 : 0;
         c.direct = 0;
