@@ -2,12 +2,13 @@
 // memory, copies are copies, kernels do nothing, streams, events and graphs are empty. Built
 // as a shared library and loaded (RTLD_GLOBAL) before libstarred.so, whose undefined HIP
 // symbols then resolve to these. It counts the live allocations, can fail the n-th one to
-// come, and keeps the destinations and sources of device-to-device copies.
+// come, and keeps the sources of device-to-device copies and the names of the kernels launched.
 #include <cstddef>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <string>
 #include <vector>
 
 namespace {
@@ -15,6 +16,8 @@ std::map<void *, size_t> live;
 long long live_bytes = 0, fail_in = -1, mallocs = 0;
 int last_error = 0;
 std::vector<const void *> copy_src;
+std::map<const void *, std::string> kernels;
+std::string launches;
 struct Dim3 { uint32_t x, y, z; };
 struct { Dim3 grid, block; size_t shmem; void *stream; } call;
 }  // namespace
@@ -30,6 +33,13 @@ long long fake_copies_from(const void *src)
     long long n = 0;
     for (const void *s : copy_src) n += s == src;
     return n;
+}
+const char *fake_launches()  // since the last call: mangled names, a space after each
+{
+    static std::string out;
+    out.swap(launches);
+    launches.clear();
+    return out.c_str();
 }
 
 // ---- memory ----
@@ -72,7 +82,10 @@ int hipGetSymbolAddress(void **p, const void *)
 
 // ---- kernels ----
 void *__hipRegisterFatBinary(const void *) { static void *h; return &h; }
-void __hipRegisterFunction(void *, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+void __hipRegisterFunction(void *, const void *f, char *, const char *name, unsigned, void *, void *, void *, void *, int *)
+{
+    kernels[f] = name;
+}
 void __hipRegisterVar(void *, void *, char *, const char *, int, size_t, int, int) {}
 void __hipUnregisterFatBinary(void *) {}
 int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t s, void *st) { call = {g, b, s, st}; return 0; }
@@ -84,7 +97,11 @@ int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *s, void **st)
     *st = call.stream;
     return 0;
 }
-int hipLaunchKernel(const void *, Dim3, Dim3, void **, size_t, void *) { return 0; }
+int hipLaunchKernel(const void *f, Dim3, Dim3, void **, size_t, void *)
+{
+    launches += kernels[f] + " ";
+    return 0;
+}
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 1; return 0; }
 
 // ---- device, streams, events, graphs ----
