@@ -93,7 +93,9 @@ struct SpecItem {
 // (X(Q, RA, RB, NF)): every even 5-smooth length from 18 to 180 but 162, which has no two
 // factors up to 16. RA is at least 8, so that the residual's reads come in runs of 32 bytes
 // or more. Two frames of 120 or more would need more registers than 1024 threads have (128
-// is the exception), or more LDS than there is.
+// is the exception), or more LDS than there is. 192 has a body for s = 1 without point sources
+// (frame_body_frames), the only frames of that length whose plane and tables fit: 300 frames of
+// 128^2 207 us on the line passes, 127 with it.
 #define STARRED_FRAME_LENGTHS(X) \
     X(18, 9, 2, 4)               \
     X(20, 10, 2, 4)              \
@@ -120,6 +122,7 @@ struct SpecItem {
     X(160, 16, 10, 1)            \
     X(180, 15, 12, 1)
 constexpr int kFrameMaxQ = 180;
+constexpr int kFrameLongQ = 192;
 
 // frames that a work group may take of a class with transform length Q (0: no body);
 // several of them only for s = 2 (compile time)
@@ -129,11 +132,11 @@ inline int frame_body_frames(int Q, int s)
     if (Q == QQ) return s == 2 ? NF : 1;
     STARRED_FRAME_LENGTHS(STARRED_FRAME_NF)
 #undef STARRED_FRAME_NF
-    return 0;
+    return Q == kFrameLongQ && s == 1 ? 1 : 0;
 }
 
-// sources whose tables a work group holds: the bodies take 1, 4 or (a loop) M of them
-__host__ __device__ constexpr int frame_sources(int M) { return M <= 1 ? 1 : (M <= 4 ? 4 : M); }
+// sources whose tables a work group holds: the bodies take up to 1, 4 or (a loop) M of them
+__host__ __device__ constexpr int frame_sources(int M) { return M <= 1 ? M : (M <= 4 ? 4 : M); }
 
 // bytes of LDS of a work group with `per` frames: their planes of Q/2+1 lines of Q+1
 // values, the Q twiddles and the tables of P values (the window's, two per source)

@@ -65,6 +65,9 @@ __device__ __forceinline__ void frame_body(const FrameItem &f, const FrameArgs &
     // ---- the model spectrum: RA bins ky = j + r RB of a column, and their DFT
     if constexpr (MS > 0) {
     constexpr int MR = MS;
+    // (without sources there are no tables for the one that MS = 1 takes with amplitude zero: it
+    // reads the window's)
+    const int tk = M > 0 ? P : 0;
     for (int it = tid; it < HQ * RB; it += NT) {
         const int j = it / HQ, kx = it - j * HQ;
         float2 wxG[S], px[S][MR];
@@ -73,7 +76,7 @@ __device__ __forceinline__ void frame_body(const FrameItem &f, const FrameArgs &
             wxG[b] = cscale(t[kx + b * Q], G);
             #pragma unroll
             for (int k = 0; k < MR; ++k)
-                px[b][k] = cscale(t[(1 + 2 * k) * P + kx + b * Q], k < M ? ai[k] : 0.f);
+                px[b][k] = cscale(t[(1 + 2 * k) * tk + kx + b * Q], k < M ? ai[k] : 0.f);
         }
         float2 v[RA];
         #pragma unroll
@@ -94,7 +97,7 @@ __device__ __forceinline__ void frame_body(const FrameItem &f, const FrameArgs &
                     F.y = fmaf(wy.x, wxG[b].y, fmaf(wy.y, wxG[b].x, F.y));
                     #pragma unroll
                     for (int k = 0; k < MR; ++k) {
-                        const float2 gy = t[(2 + 2 * k) * P + Ky];
+                        const float2 gy = t[(2 + 2 * k) * tk + Ky];
                         F.x = fmaf(gy.x, px[b][k].x, fmaf(-gy.y, px[b][k].y, F.x));
                         F.y = fmaf(gy.x, px[b][k].y, fmaf(gy.y, px[b][k].x, F.y));
                     }
@@ -392,6 +395,9 @@ __global__ __launch_bounds__(kFusedThreads) void k_frame(const FrameItem *__rest
         break;
         STARRED_FRAME_LENGTHS(STARRED_FRAME_CASE)
 #undef STARRED_FRAME_CASE
+    case kFrameLongQ * 8 + 1:
+        if constexpr (S == 1 && MS == 1) frame_body<S, MS, 16, 12, 1>(f, g, sm, red);
+        break;
     default: break;
     }
 }

@@ -18,6 +18,8 @@ CASES = [
     (8, 5, 2, 2, 18, True),
     (6, 5, 3, 300, 8, False),
     (150, 80, 1, 1, 192, False),
+    (150, 80, 1, 0, 192, True),
+    (160, 126, 2, 0, 192, False),
 ]
 
 
