@@ -114,15 +114,29 @@ __device__ __forceinline__ void psf_taps(float c, int s, float sigma, int T, flo
 // FP64 copy of the narrow PSF for the forward model: with star amplitudes up to
 // 1e6 the chi-square near the truth is set by model errors far below an FP32
 // ulp of the brightest pixels, so the (small) PSF-mode forward runs in FP64.
+// The launches below may carry a pass of the starlet prior in work groups behind their own. They
+// are compiled with and without one (Carry = StarPiece, NoPiece): the pass's registers (the
+// render 109 for 42) and code cost a launch that carries none (loss and gradient of 30 stars of
+// 100^2 on a grid of 300^2: 93.3 us with them, 90.2 without).
+struct NoPiece {};
+template <int NT>
+__device__ __forceinline__ bool carried(NoPiece, void *) { return false; }
+template <int NT>
+__device__ __forceinline__ bool carried(const StarPiece &star, void *lds)
+{
+    __shared__ double red[NT / 64];
+    return star_piece_run<NT>(star, lds, red);
+}
+
 // dm (or null): the Moffat derivatives dm/deta per pixel, [5][N^2], for the adjoint.
 // tick (or null): the step counter, advanced here (the step's first launch) for the
 // update at its end.
+template <class Carry>
 __global__ __launch_bounds__(256) void k_psf_render64(int N, const float *__restrict__ params, double *__restrict__ s64,
-                               float *__restrict__ dm, int *__restrict__ tick, StarPiece star)
+                               float *__restrict__ dm, int *__restrict__ tick, Carry star)
 {
     extern __shared__ double slds[];
-    __shared__ double sred[256 / 64];
-    if (star_piece_run<256>(star, slds, sred)) return;  // a pass of the starlet prior carried by this launch
+    if (carried<256>(star, slds)) return;
     const int pix = blockIdx.x * blockDim.x + threadIdx.x;
     const long long NN = (long long)N * N;
     if (pix >= NN) return;
@@ -153,7 +167,9 @@ hipError_t launch_psf_render64(hipStream_t st, int N, const float *params, doubl
     const int main = (N * N + 255) / 256;
     size_t lds = 0;
     const StarPiece p = psf_piece(star, main, &lds);
-    hipLaunchKernelGGL(k_psf_render64, dim3(main + p.jobs), dim3(256), lds, st, N, params, s64, dm, tick, p);
+    const dim3 grid(main + p.jobs), block(256);
+    if (p.group >= 0) hipLaunchKernelGGL(k_psf_render64<StarPiece>, grid, block, lds, st, N, params, s64, dm, tick, p);
+    else hipLaunchKernelGGL(k_psf_render64<NoPiece>, grid, block, 0, st, N, params, s64, dm, tick, NoPiece());
     return hipGetLastError();
 }
 
@@ -201,19 +217,18 @@ size_t psf_fwd_lds(int s)
 // adjoint), and the tile's chi-square, dchi/da and the two sums dchi/dc needs
 // (divided by a_k), as four FP64 partials in part[(k * tiles + tile) * 4 ..].
 // params = [eta 5 | b N^2 | a S | c 2S]
-template <int SS>
+template <int SS, class Carry>
 __global__ __launch_bounds__(kPsfThreads) void k_psf_fwd(
     int S, int n, int N, float sigma, const float *__restrict__ params,
     const double *__restrict__ s64, const float *__restrict__ data, const float *__restrict__ invvar,
-    float *__restrict__ rho, double *__restrict__ part, float *__restrict__ model, int tp, int tq, StarPiece star)
+    float *__restrict__ rho, double *__restrict__ part, float *__restrict__ model, int tp, int tq, Carry star)
 {
     using Win = PsfFwdWin<SS>;
     constexpr int T = Win::T, RM = Win::RM, CM = Win::CM, QT = kPsfColTile;
     extern __shared__ double smd[];
     __shared__ double G[2][kPsfMaxT], dG[2][kPsfMaxT];
     __shared__ double red[kPsfThreads / 64][4];
-    __shared__ double sred[kPsfThreads / 64];
-    if (star_piece_run<kPsfThreads>(star, smd, sred)) return;  // a pass of the starlet prior
+    if (carried<kPsfThreads>(star, smd)) return;
     // work groups: tile rows fastest, then tile columns (tp x tq tiles), then stars
     const int k = blockIdx.x / (tp * tq), bq = blockIdx.x / tp % tq, bp = blockIdx.x % tp;
     const long long NN = (long long)N * N;
@@ -353,13 +368,13 @@ int psf_adj_tiles(int N) { return ((N + kPsfAdjTx - 1) / kPsfAdjTx) * ((N + kPsf
 // floor(a / b) for b > 0
 __device__ __forceinline__ int psf_fdiv(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
-template <int SS>
+template <int SS, class Carry>
 __global__ __launch_bounds__(kPsfAdjThreads) void k_psf_adjsum(int S, int n, int N, float sigma, int kb,
                                                                const float *__restrict__ params,
                                                                const float *__restrict__ rho,
                                                                const float *__restrict__ dm,
                                                                float *__restrict__ grad,
-                                                               double *__restrict__ part_eta, int tx, StarPiece star)
+                                                               double *__restrict__ part_eta, int tx, Carry star)
 {
     using Win = PsfAdjWin<SS>;
     constexpr int T = Win::T, PR = Win::PR, QC = Win::QC, KT = Win::KT, TX = kPsfAdjTx;
@@ -372,8 +387,7 @@ __global__ __launch_bounds__(kPsfAdjThreads) void k_psf_adjsum(int S, int n, int
     float *Rt = Gt + 2 * kb * T;            // residual windows [kb][PR][QC]
     float *U = Rt + (size_t)kb * PR * QC;   // [kb][PR][TX]
     const long long NN = (long long)N * N;
-    __shared__ double sred[kPsfAdjThreads / 64];
-    if (star_piece_run<kPsfAdjThreads>(star, sm, sred)) return;  // a pass of the starlet prior
+    if (carried<kPsfAdjThreads>(star, sm)) return;
     const int X0 = blockIdx.x % tx * TX, Y0 = blockIdx.x / tx * kPsfAdjTy;
     const int pix_l = threadIdx.x % kPsfAdjPix, grp = threadIdx.x / kPsfAdjPix;
     const int xl = pix_l % TX, yl = pix_l / TX;
@@ -515,13 +529,14 @@ size_t psf_adj_lds(int s, int S) { return psf_adj_per_star(s) * psf_adj_batch(s,
 // from the star's tiles, dchi/deta from the adjoint tiles (every sum a fixed-order
 // strided pass and a fixed-order reduction), then the update of eta, a and c. Work
 // groups 1..: grad_b = dchi/ds + the prior's gradient, per pixel, and its update.
+template <class Carry>
 __global__ __launch_bounds__(256) void k_psf_finalize(int S, int N, int tiles, const double *__restrict__ part,
                                                       int n_l1, const double *__restrict__ part_l1,
                                                       int n_eta, const double *__restrict__ part_eta,
                                                       const float *params,  // updated through ad.params
                                                       const float *__restrict__ prior,
                                                       float *__restrict__ grad, double *__restrict__ loss,
-                                                      AdamDev ad, StarPiece star)
+                                                      AdamDev ad, Carry star)
 {
     if (blockIdx.x > 0) {
         const long long NN = (long long)N * N;
@@ -538,15 +553,15 @@ __global__ __launch_bounds__(256) void k_psf_finalize(int S, int N, int tiles, c
                 ad.params[5 + i] = pi;
             }
         };
-        if (star.group >= 0) {
+        if constexpr (std::is_same<Carry, StarPiece>::value) {
             // the prior's last pass, tile by tile: its pixels go straight into the gradient
             extern __shared__ double slds[];
             star_piece_adjoint<256>(star, blockIdx.x - 1, slds, pixel);
-            return;
+        } else {
+            const long long i = (long long)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
+            if (!grad || i >= NN) return;
+            pixel(i, prior ? prior[i] : 0.f);
         }
-        const long long i = (long long)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
-        if (!grad || i >= NN) return;
-        pixel(i, prior ? prior[i] : 0.f);
         return;
     }
     const long long NN = (long long)N * N;
@@ -635,6 +650,8 @@ __global__ __launch_bounds__(256) void k_psf_finalize(int S, int N, int tiles, c
     }
 }
 
+#define PSF_KERNEL(KERNEL, SS, CARRY) ((SS) == 1 ? KERNEL<1, CARRY> : (SS) == 2 ? KERNEL<2, CARRY> : KERNEL<3, CARRY>)
+
 hipError_t launch_psf_fwd(hipStream_t st, int S, int n, int ss, int N, float sigma, const float *params,
                           const double *s64, const float *data, const float *invvar, float *rho, double *part,
                           float *model, const StarPiece *star)
@@ -642,9 +659,12 @@ hipError_t launch_psf_fwd(hipStream_t st, int S, int n, int ss, int N, float sig
     const int tp = (n + kPsfRowChunk - 1) / kPsfRowChunk, tq = (n + kPsfColTile - 1) / kPsfColTile;
     size_t lds = psf_fwd_lds(ss);
     const StarPiece p = psf_piece(star, tp * tq * S, &lds);
-    auto kern = ss == 1 ? k_psf_fwd<1> : ss == 2 ? k_psf_fwd<2> : k_psf_fwd<3>;
-    hipLaunchKernelGGL(kern, dim3(tp * tq * S + p.jobs), dim3(kPsfThreads), lds, st, S, n, N, sigma, params, s64, data,
-                       invvar, rho, part, model, tp, tq, p);
+    const auto launch = [&](auto kern, auto carry) {
+        hipLaunchKernelGGL(kern, dim3(tp * tq * S + p.jobs), dim3(kPsfThreads), lds, st, S, n, N, sigma, params, s64,
+                           data, invvar, rho, part, model, tp, tq, carry);
+    };
+    if (p.group >= 0) launch(PSF_KERNEL(k_psf_fwd, ss, StarPiece), p);
+    else launch(PSF_KERNEL(k_psf_fwd, ss, NoPiece), NoPiece());
     return hipGetLastError();
 }
 
@@ -654,9 +674,12 @@ hipError_t launch_psf_adjsum(hipStream_t st, int S, int n, int ss, int N, float 
     const int kb = psf_adj_batch(ss, S), tx = (N + kPsfAdjTx - 1) / kPsfAdjTx;
     size_t lds = psf_adj_per_star(ss) * kb;
     const StarPiece p = psf_piece(star, psf_adj_tiles(N), &lds);
-    auto kern = ss == 1 ? k_psf_adjsum<1> : ss == 2 ? k_psf_adjsum<2> : k_psf_adjsum<3>;
-    hipLaunchKernelGGL(kern, dim3(psf_adj_tiles(N) + p.jobs), dim3(kPsfAdjThreads), lds, st, S, n, N, sigma, kb, params,
-                       rho, dm, grad, part_eta, tx, p);
+    const auto launch = [&](auto kern, auto carry) {
+        hipLaunchKernelGGL(kern, dim3(psf_adj_tiles(N) + p.jobs), dim3(kPsfAdjThreads), lds, st, S, n, N, sigma, kb,
+                           params, rho, dm, grad, part_eta, tx, carry);
+    };
+    if (p.group >= 0) launch(PSF_KERNEL(k_psf_adjsum, ss, StarPiece), p);
+    else launch(PSF_KERNEL(k_psf_adjsum, ss, NoPiece), NoPiece());
     return hipGetLastError();
 }
 
@@ -668,8 +691,12 @@ hipError_t launch_psf_finalize(hipStream_t st, int S, int N, int tiles, const do
     size_t lds = 0;
     const StarPiece p = psf_piece(star, 1, &lds);
     const unsigned groups = grad ? 1 + (p.group >= 0 ? (unsigned)p.jobs : (unsigned)((NN + 255) / 256)) : 1;
-    hipLaunchKernelGGL(k_psf_finalize, dim3(groups), dim3(256), lds, st, S, N, tiles, part, n_l1, part_l1, n_eta,
-                       part_eta, params, prior, grad, loss, adam, p);
+    const auto launch = [&](auto kern, auto carry) {
+        hipLaunchKernelGGL(kern, dim3(groups), dim3(256), lds, st, S, N, tiles, part, n_l1, part_l1, n_eta, part_eta,
+                           params, prior, grad, loss, adam, carry);
+    };
+    if (p.group >= 0) launch(k_psf_finalize<StarPiece>, p);
+    else launch(k_psf_finalize<NoPiece>, NoPiece());
     return hipGetLastError();
 }
 

@@ -21,3 +21,16 @@ print(*launches(["k_star_plane", "k_star_forward", "k_star_adjoint", "k_copy", "
     evaluation = ["k_psf_render64", "k_psf_fwd", "k_psf_adjsum", "k_psf_finalize"]
     assert out == prior + evaluation
     assert bool(prior) == (J == 1 or n * s > 256)
+
+
+@pytest.mark.parametrize("n,s,J,carried", [(32, 2, 1, 0), (129, 2, 6, 0), (16, 2, 2, 2), (33, 2, 7, 4)])
+def test_psf_launches_without_a_pass_are_compiled_without_one(tmp_path, n, s, J, carried):
+    out = fake_hip.run(tmp_path, f"""
+h = make_plan([{n}] * 3, [1] * 3, {s}, {n * s}, 0, {J}, mode=st.PSF)
+assert L.starred_set_frames(h, ptr(f32(3 * {n} ** 2)), ptr(f32(3 * {n} ** 2)), None, ptr(f32({J}))) == st.OK
+P = L.starred_num_params(h)
+launches([])
+assert L.starred_loss_grad(h, ptr(f32(P)), ptr(f32(P)), ptr(np.zeros(3))) == st.OK
+print(*[("StarPiece" in k) + ("NoPiece" in k) * 10 for k in hip.fake_launches().decode().split() if "k_psf" in k])
+""").split()
+    assert sorted(out) == ["1"] * carried + ["10"] * (4 - carried)
