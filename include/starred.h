@@ -148,7 +148,8 @@ int starred_psf_model(starred_plan *plan, const float *params, float *model);
 /* Starlet transform Phi^T (Eq. 6): coeffs = J planes of N^2; plane j < J-1 is
  * c_j - c_{j+1}, plane J-1 the coarse c_{J-1}; c_0 = img, c_{j+1} = H_j c_j with
  * the B3 filter [1,4,6,4,1]/16 at dilation 2^j and a whole-sample mirror
- * boundary. starred_starlet_adj applies the exact transpose Phi. */
+ * boundary. starred_starlet_adj applies the exact transpose Phi. img may lie in the
+ * coefficients' memory. */
 int starred_starlet_fwd(starred_plan *plan, const float *img, float *coeffs);
 int starred_starlet_adj(starred_plan *plan, const float *coeffs, float *img);
 

@@ -1373,9 +1373,23 @@ int starred_convolve_subsample_adj(starred_plan *p, const float *resid, float *g
     return STARRED_OK;
 }
 
+// an image that lies in the coefficients' memory (a pass's work groups read what others write,
+// so its input is then taken from a copy); the one plane of J = 1 is copied pixel by pixel
+static bool star_in_place(const starred_plan *p, const float *img, const float *coeffs)
+{
+    const size_t NN = (size_t)p->N * p->N;
+    const uintptr_t i = (uintptr_t)img, c = (uintptr_t)coeffs;
+    return i < c + sizeof(float) * p->J * NN && c < i + sizeof(float) * NN && !(p->J == 1 && i == c);
+}
+
 int starred_starlet_fwd(starred_plan *p, const float *img, float *coeffs)
 {
     if (!p || !img || !coeffs) return fail(STARRED_EINVAL, "NULL argument");
+    const size_t NN = (size_t)p->N * p->N;
+    if (star_in_place(p, img, coeffs)) {
+        HIP_TRY(hipMemcpyAsync(p->d_prior, img, sizeof(float) * NN, hipMemcpyDeviceToDevice, p->st));
+        img = p->d_prior;
+    }
     StarArgs a = star_args(p, 1, img);
     a.coeffs = coeffs;  // the transform alone: no weights
     HIP_TRY(launch_star_forward(p->st, a));
@@ -1385,6 +1399,11 @@ int starred_starlet_fwd(starred_plan *p, const float *img, float *coeffs)
 int starred_starlet_adj(starred_plan *p, const float *coeffs, float *img)
 {
     if (!p || !coeffs || !img) return fail(STARRED_EINVAL, "NULL argument");
+    const size_t JNN = (size_t)p->J * p->N * p->N;
+    if (star_in_place(p, img, coeffs)) {
+        HIP_TRY(hipMemcpyAsync(p->d_z, coeffs, sizeof(float) * JNN, hipMemcpyDeviceToDevice, p->st));
+        coeffs = p->d_z;
+    }
     StarArgs a = star_args(p, 1, nullptr);
     a.z = const_cast<float *>(coeffs);  // (only read)
     a.out = img;
