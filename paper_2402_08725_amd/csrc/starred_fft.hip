@@ -270,14 +270,16 @@ struct has_extra : std::false_type {};
 template <class Op>
 struct has_extra<Op, std::void_t<decltype(Op::extra)>> : std::true_type {};
 
-template <class Op>
+// Carry: DensePiece where a launch carries starlet-prior jobs (work groups after the line groups
+// and extras), else NoPiece: the jobs' registers (105 for 44) halve the waves a SIMD holds of the
+// line groups.
+template <class Op, class Carry>
 __global__ __launch_bounds__(kFftThreads) void k_lines(const LineItem *__restrict__ items,
                                                        const ClassFft *__restrict__ classes,
-                                                       const float2 *__restrict__ tw, Op op, DensePiece dp)
+                                                       const float2 *__restrict__ tw, Op op, Carry dp)
 {
     extern __shared__ float2 sm[];
-    {
-        // a starlet-prior job carried by this launch (work groups after the line groups and extras)
+    if constexpr (std::is_same<Carry, DensePiece>::value) {
         __shared__ double dred[kFftThreads / 64];
         if (dense_piece_run(dp, sm, dred)) return;
     }
@@ -1326,22 +1328,30 @@ static size_t piece_lds(const DensePiece &p)
     return dense_lds_y(p.d.J);
 }
 
-// n_main work groups of line groups (and extras), then the carried pass's jobs
+// n_main work groups of line groups and extras (default: the line groups)
 template <class Op>
 static hipError_t run_lines(hipStream_t st, const LinePass &lp, const ClassFft *classes, const float2 *tw,
-                            const Op &op, int n_main = -1, DensePiece *piece = nullptr)
+                            const Op &op, int n_main = -1)
 {
     if (n_main < 0) n_main = lp.n_items;
-    DensePiece dp;
-    size_t lds = lp.lds_bytes;
-    if (piece && piece->pass >= 0) {
-        dp = *piece;
-        dp.first = n_main;
-        lds = std::max(lds, piece_lds(dp));
-    }
-    const int grid = n_main + (dp.pass >= 0 ? dp.jobs : 0);
+    if (n_main <= 0) return hipSuccess;
+    hipLaunchKernelGGL((k_lines<Op, NoPiece>), dim3(n_main), dim3(kFftThreads), lp.lds_bytes, st, lp.items, classes,
+                       tw, op, NoPiece());
+    return hipGetLastError();
+}
+
+// the same, then the jobs of a carried pass (piece, or null)
+template <class Op>
+static hipError_t run_lines_carrying(hipStream_t st, const LinePass &lp, const ClassFft *classes, const float2 *tw,
+                                     const Op &op, int n_main, const DensePiece *piece)
+{
+    if (!piece || piece->pass < 0) return run_lines(st, lp, classes, tw, op, n_main);
+    DensePiece dp = *piece;
+    dp.first = n_main < 0 ? lp.n_items : n_main;
+    const int grid = dp.first + dp.jobs;
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_lines<Op>), dim3(grid), dim3(kFftThreads), lds, st, lp.items, classes, tw, op, dp);
+    hipLaunchKernelGGL((k_lines<Op, DensePiece>), dim3(grid), dim3(kFftThreads), std::max(lp.lds_bytes, piece_lds(dp)),
+                       st, lp.items, classes, tw, op, dp);
     return hipGetLastError();
 }
 
@@ -1358,9 +1368,9 @@ hipError_t fft_spectra(hipStream_t st, const FftPlanDev &d, const float *params,
     // rows of the h windows, with the factor tables in extra work groups
     const int extra = M > 0 ? d.n_classes * tab_blocks(M) : 0;
     const OpHRows op{params, N, d.Th, d.hrows.n_items, E, M, sigma, d.tab, tick};
-    hipError_t e = run_lines(st, d.hrows, d.classes, d.tw, op, d.hrows.n_items + extra, pa);
+    hipError_t e = run_lines_carrying(st, d.hrows, d.classes, d.tw, op, d.hrows.n_items + extra, pa);
     if (e != hipSuccess) return e;
-    return run_lines(st, d.hcols, d.classes, d.tw, OpHCols{d.Th, d.Hh}, -1, pb);
+    return run_lines_carrying(st, d.hcols, d.classes, d.tw, OpHCols{d.Th, d.Hh}, -1, pb);
 }
 
 hipError_t fft_spec_fwd(hipStream_t st, const FftPlanDev &d, const float *params, int N, int E, int M, int s,
@@ -1562,7 +1572,7 @@ hipError_t fft_adj_sums(hipStream_t st, const FftPlanDev &d, int M, double *fsum
 
 hipError_t fft_grad_h_cols(hipStream_t st, const FftPlanDev &d, DensePiece *pd)
 {
-    return run_lines(st, d.gcols, d.classes, d.tw, OpGCols{d.Gp, d.Th}, -1, pd);
+    return run_lines_carrying(st, d.gcols, d.classes, d.tw, OpGCols{d.Gp, d.Th}, -1, pd);
 }
 
 hipError_t fft_grad_h_rows_final(hipStream_t st, const FftPlanDev &d, const float *prior, const FinalArgs &fin,
@@ -1574,7 +1584,7 @@ hipError_t fft_grad_h_rows_final(hipStream_t st, const FftPlanDev &d, const floa
 
 hipError_t fft_grad_h_inverse(hipStream_t st, const FftPlanDev &d, DensePiece *pd)
 {
-    hipError_t e = run_lines(st, d.gcols, d.classes, d.tw, OpGCols{d.Gp, d.Th}, -1, pd);
+    hipError_t e = run_lines_carrying(st, d.gcols, d.classes, d.tw, OpGCols{d.Gp, d.Th}, -1, pd);
     if (e != hipSuccess) return e;
     return run_lines(st, d.grows, d.classes, d.tw, OpGRows{d.Th, d.hcls});
 }

@@ -131,6 +131,8 @@ hipError_t launch_finalize_small(hipStream_t st, int E, int M, int n_chi, const 
 hipError_t launch_copy_probe(hipStream_t st, const float *src, float *dst, long long n);
 hipError_t launch_idle(hipStream_t st, int iters);
 
+// in the place of a carried pass (DensePiece, StarPiece) where a launch carries none
+struct NoPiece {};
 // Starlet transform (starred_scales.h, starred_starlet.hip)
 struct StarArgs;
 bool star_fp64(int N, int J);                // whether one or two images are transformed in FP64

@@ -118,7 +118,6 @@ __device__ __forceinline__ void psf_taps(float c, int s, float sigma, int T, flo
 // are compiled with and without one (Carry = StarPiece, NoPiece): the pass's registers (the
 // render 109 for 42) and code cost a launch that carries none (loss and gradient of 30 stars of
 // 100^2 on a grid of 300^2: 93.3 us with them, 90.2 without).
-struct NoPiece {};
 template <int NT>
 __device__ __forceinline__ bool carried(NoPiece, void *) { return false; }
 template <int NT>

@@ -34,3 +34,20 @@ assert L.starred_loss_grad(h, ptr(f32(P)), ptr(f32(P)), ptr(np.zeros(3))) == st.
 print(*[("StarPiece" in k) + ("NoPiece" in k) * 10 for k in hip.fake_launches().decode().split() if "k_psf" in k])
 """).split()
     assert sorted(out) == ["1"] * carried + ["10"] * (4 - carried)
+
+
+def test_line_passes_carry_prior_jobs_only_where_some_ride(tmp_path):
+    """Kernels of the spectra's and of dL/dh's passes, without and with the prior's passes in
+    them: compiled for the jobs where they ride, and never elsewhere."""
+    out = fake_hip.run(tmp_path, """
+for J in (1, 4):  # (one plane has nothing to ride)
+    h = make_plan([32] * 4, [16] * 4, 2, 64, 1, J)
+    n = 4 * 32 * 32
+    assert L.starred_set_frames(h, ptr(f32(n)), ptr(f32(n)), ptr(f32(4 * 256)), ptr(f32(4))) == st.OK
+    P = L.starred_num_params(h)
+    launches([])
+    assert L.starred_loss_grad(h, ptr(f32(P)), ptr(f32(P)), ptr(np.zeros(3))) == st.OK
+    names = [k for k in hip.fake_launches().decode().split() if "7k_lines" in k]
+    print(sum("DensePiece" in k for k in names), sum("NoPiece" in k for k in names), len(names))
+""").splitlines()
+    assert out == ["0 4 4", "3 1 4"]
