@@ -337,7 +337,8 @@ int starred_frame_transforms_info(const starred_plan *plan, int32_t *algo_out, d
  * the current value): adj_frames, frames per chunk of the frequency-domain adjoint
  * (2 or 4; 8 with at most one point source; 1 with more than eight; one summed
  * spectrum per chunk goes through memory; a chunk of one frame takes 16 sources per
- * pass over its spectra, two frames 8 when there are more than four, otherwise 4);
+ * pass over its spectra (8 with subsample 3), two frames 8 when there are more than
+ * four, otherwise 4);
  * adj_blocks, work groups its launch aims at; line_groups, work groups a line pass
  * aims at; split_forward (-1 keeps it): 1
  * runs the one-launch forward of the smaller classes on a second stream of the plan,

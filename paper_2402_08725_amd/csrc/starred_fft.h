@@ -17,7 +17,7 @@ constexpr int kAdjFrames = 2;          // spectral adjoint: frames of a work gro
 constexpr int kAdjMaxFrames = 8;       // spectral adjoint: most frames of a chunk
 constexpr int kAdjSB = 4;              // spectral adjoint: sources per pass over the rows (M > 1)
 constexpr int kAdjSBWide = 8;          // the same with 2-frame chunks and more than kAdjSB sources
-constexpr int kAdjSBOne = 16;          // the same with 1-frame chunks (more than kAdjSBWide sources)
+constexpr int kAdjSBOne = 16;          // the same with 1-frame chunks (more than kAdjSBWide sources; s < 3)
 constexpr int kAdjBlocks = 512;        // spectral adjoint: work groups aimed at per launch
 constexpr int kAdjMinRows = 4;         // spectral adjoint: fewest rows of the P grid per thread
 constexpr int kAdjMaxRows = 64;        // spectral adjoint: most rows of the P grid per work group

@@ -1017,7 +1017,7 @@ __device__ void tables_part(const ClassFft &c, const float2 *__restrict__ tw, co
 // spectra in row order, which took s^2 narrow loads and their index arithmetic per bin); many
 // sources: by the column sums' registers (12 frames of 256^2, 30 sources: 72 us).
 template <int S, int FC, int SB>
-__global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restrict__ items,
+__global__ __launch_bounds__(kFftThreads, 2) void k_spec_adj(const AdjItem *__restrict__ items,
                                                           const float2 *__restrict__ Sp,
                                                           const float2 *__restrict__ Rh,
                                                           const float2 *__restrict__ tab, int M, int maxpb,
@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restr
 {
     constexpr int NY = 1 + 2 * SB, NQ = 1 + 3 * SB;
     // rows of a thread whose loads are issued together: about 8-16 wide loads in flight
-    constexpr int RB = FC >= 4 ? (S == 1 && FC == 4 ? 2 : 1) : (FC == 2 ? 2 : kAdjRB);
+    constexpr int RB = FC >= 4 ? (S == 1 && FC == 4 ? 2 : 1) : S * SB + 8 * FC > 36 ? 1 : (FC == 2 ? 2 : kAdjRB);
     static_assert(FC <= kAdjMaxFrames, "chunk larger than the work items hold");
     constexpr int kRow = kFftThreads + 8;  // padded LDS rows of per-thread partials
     // rows of per-thread partials reduced per pass (LDS kept small for occupancy)
@@ -1041,7 +1041,14 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restr
     const float2 *t = tab + it.tab_off;
     const int Q3 = 1 + 3 * M;
     float2 *gout = Gp + it.gout;
-    __shared__ float2 tys[NY * kAdjMaxRows];  // y-tables of the block's rows, [u][row][a]
+    // y-tables of the block's rows, [u][row][a]; with many sources [u][a][row], one alias's in
+    // registers at a time. The bound of two waves per SIMD and fewer loads in flight keep those
+    // variants (S = 3 with eight sources per pass, S = 2 with sixteen) within 256 registers; with
+    // a single wave, 300 frames of 90^2 at s = 3 and 12 sources took 369 us, 280 now, and 12 frames
+    // of 256^2, 30 sources, one frame per chunk 86, 58 now.
+    constexpr bool kApart = S > 1 && S * NY > 34;
+    constexpr int kRowStep = kApart ? 1 : S, kAliasStep = kApart ? kAdjMaxRows / S : 1;
+    __shared__ float2 tys[NY * kAdjMaxRows];
     for (int k0 = 0; k0 < max(M, 1); k0 += SB) {
         const int nk = min(SB, M - k0);  // sources of this group (may be 0 when M = 0)
         const bool first = (k0 == 0);
@@ -1053,7 +1060,7 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restr
             if (u == 0) v = t[Ky];
             else if (u <= SB) { if (u - 1 < nk) v = t[(1 + 4 * (k0 + u - 1)) * P + P + Ky]; }
             else if (u - 1 - SB < nk) v = t[(1 + 4 * (k0 + u - 1 - SB)) * P + 3 * P + Ky];
-            tys[u * kAdjMaxRows + ra] = v;
+            tys[u * kAdjMaxRows + ra / S * kRowStep + ra % S * kAliasStep] = v;
         }
         __syncthreads();
         // spectra of the chunk's frames (a slot past the chunk's frames reads its first
@@ -1096,27 +1103,25 @@ __global__ __launch_bounds__(kFftThreads) void k_spec_adj(const AdjItem *__restr
                 for (int q = 0; q < RB; ++q) {
                     const int li = ib + q * RG;
                     if (li >= nrow) continue;
-                    float2 ty[S][NY], gsum[S];
+                    float2 gsum[S];
                     #pragma unroll
                     for (int a = 0; a < S; ++a) {
+                        if constexpr (kApart) asm volatile("" ::: "memory");
                         gsum[a] = make_float2(0.f, 0.f);
+                        float2 ty[NY];
                         #pragma unroll
-                        for (int u = 0; u < NY; ++u) ty[a][u] = tys[u * kAdjMaxRows + li * S + a];
-                    }
-                    #pragma unroll
-                    for (int f = 0; f < FC; ++f) {
-                        // a missing frame's product is replaced by zero with a select (a branch
-                        // here would let the compiler sink the loads above back to their use;
-                        // a product with zero would let a non-finite value through)
-                        const bool on = f < it.nf;
-                        const float2 z = make_float2(0.f, 0.f);
-                        const float2 r = on ? rv[q][f] : z;
+                        for (int u = 0; u < NY; ++u) ty[u] = tys[u * kAdjMaxRows + li * kRowStep + a * kAliasStep];
                         #pragma unroll
-                        for (int a = 0; a < S; ++a) {
-                            const float2 G = cmulc(r, on ? sv[q][f][a] : z);
+                        for (int f = 0; f < FC; ++f) {
+                            // a missing frame's product is replaced by zero with a select (a branch
+                            // here would let the compiler sink the loads above back to their use;
+                            // a product with zero would let a non-finite value through)
+                            const bool on = f < it.nf;
+                            const float2 z = make_float2(0.f, 0.f);
+                            const float2 G = cmulc(on ? rv[q][f] : z, on ? sv[q][f][a] : z);
                             gsum[a] = cadd(gsum[a], G);
                             #pragma unroll
-                            for (int u = 0; u < NY; ++u) V[f][u] = cadd(V[f][u], cmulc(G, ty[a][u]));
+                            for (int u = 0; u < NY; ++u) V[f][u] = cadd(V[f][u], cmulc(G, ty[u]));
                         }
                     }
                     if (first) {
@@ -1539,7 +1544,10 @@ static hipError_t spec_adj(hipStream_t st, const FftPlanDev &d, int M)
         }
     } else {
         switch (d.adj_fc) {
-        case 1: SPEC_ADJ(1, kAdjSBOne); break;
+        case 1:
+            if constexpr (S == 3) SPEC_ADJ(1, kAdjSBWide);  // (16: 402 us for 8's 265, the case above)
+            else SPEC_ADJ(1, kAdjSBOne);
+            break;
         case 2:
             if (M > kAdjSB)
                 SPEC_ADJ(2, kAdjSBWide);

@@ -857,7 +857,12 @@ static int build_fft_lists(starred_plan *p)
             // a block takes rows of the Q grid, s rows of the P grid each: at least kAdjMinRows
             // of those per thread, at most kAdjMaxRows per block
             const int rows = std::max(kAdjMinRows * RG, (cl.P + want - 1) / want);
-            const int arr = std::min((rows + S - 1) / S, kAdjMaxRows / S);
+            int arr = std::min((rows + S - 1) / S, kAdjMaxRows / S);
+            // (many sources: two groups fit a compute unit, and a few more than that would take as
+            // long again; 100 frames of 64^2, 30 sources: 550 groups 74 us, 500 groups 48 us)
+            const auto groups = [&] { return nchunks * ((cl.Q + arr - 1) / arr); };
+            while (M > kAdjSB && groups() > p->adj_blocks && 4 * groups() < 5 * p->adj_blocks && arr < kAdjMaxRows / S)
+                ++arr;
             cl.arr = arr;
             cl.nrr = (cl.Q + arr - 1) / arr;
             maxpb = std::max(maxpb, cl.nrr);
