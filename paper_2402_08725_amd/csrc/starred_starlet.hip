@@ -61,12 +61,18 @@ int star_l1_slots(const StarArgs &a)
     return a.J == 1 ? (int)(((long long)a.N * a.N + 255) / 256) : a.l1_slots();
 }
 
-// tiles of 16 on 512 threads (two waves per SIMD hide more than one), of 32 on 1024
-#define STAR_LAUNCH_L(KERNEL, V, L)                                                                             \
-    if (q.T == kStarTile)                                                                                       \
-        hipLaunchKernelGGL((KERNEL<V, L, kStarTile, 512>), grid, dim3(512), q.lds(), st, a, g);                 \
-    else                                                                                                        \
-        hipLaunchKernelGGL((KERNEL<float, L, kStarTileLarge, 1024>), grid, dim3(1024), q.lds(), st, a, g)
+// tiles of 16 on 512 threads (two waves per SIMD hide more than one); of 32 on 1024, but on 512 for
+// one level, whose groups are short (the transform of 512^2 with two planes 4.9 us on 1024, 4.0 on
+// 512; of 1024^2 11.3 and 8.5)
+constexpr int star_wide_threads(int L) { return L == 1 ? 512 : 1024; }
+#define STAR_LAUNCH_WIDE(KERNEL, L)                                                                                 \
+    hipLaunchKernelGGL((KERNEL<float, L, kStarTileLarge, star_wide_threads(L)>), grid, dim3(star_wide_threads(L)), \
+                       q.lds(), st, a, g)
+#define STAR_LAUNCH_L(KERNEL, V, L)                                                             \
+    if (q.T == kStarTile)                                                                       \
+        hipLaunchKernelGGL((KERNEL<V, L, kStarTile, 512>), grid, dim3(512), q.lds(), st, a, g); \
+    else                                                                                        \
+        STAR_LAUNCH_WIDE(KERNEL, L)
 #define STAR_LAUNCH(KERNEL)                                          \
     do {                                                             \
         const StarArgs::Group q = a.group(g);                        \
@@ -75,7 +81,7 @@ int star_l1_slots(const StarArgs &a)
         case 1: STAR_LAUNCH_L(KERNEL, float, 1); break;              \
         case 2: STAR_LAUNCH_L(KERNEL, float, 2); break;              \
         case 3: STAR_LAUNCH_L(KERNEL, float, 3); break;              \
-        case 4: STAR_LAUNCH_L(KERNEL, float, 4); break;              \
+        case 4: STAR_LAUNCH_WIDE(KERNEL, 4); break;                  \
         case 9: STAR_LAUNCH_L(KERNEL, double, 1); break;             \
         case 10: STAR_LAUNCH_L(KERNEL, double, 2); break;            \
         case 11: STAR_LAUNCH_L(KERNEL, double, 3); break;            \

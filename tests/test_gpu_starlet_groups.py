@@ -1,0 +1,29 @@
+"""The starlet passes' groups of levels: 3 + 2 + 2 for eight planes, on grids whose subimages fill
+their tiles badly, eleven planes (3 + 3 + 4, the only group of four), one level on the wide tiles.
+
+Bar as in the parity suite: 2e-6 of the largest value."""
+import numpy as np
+import pytest
+
+from oracle import oracle as ora
+from paper_2402_08725_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("N,J", [(129, 8), (257, 8), (300, 8), (700, 8), (257, 2), (700, 2), (1025, 11), (1100, 11)])
+def test_transform_and_transpose(N, J):
+    from paper_2402_08725_amd import starred as st
+    print(f"N {N} J {J}", flush=True)
+    rng = np.random.default_rng(N * 16 + J)
+    plan = st.Plan(st.DECONV, [N], [3], 1, N, 0, J, 3.0)
+    img = synth.f32(rng.standard_normal(N * N) * 10)
+    got = plan.starlet_fwd(img).cpu().numpy()
+    ref = ora.starlet_fwd(N, J, img).reshape(-1)
+    assert np.abs(got - ref).max() <= 2e-6 * np.abs(ref).max()
+    z = synth.f32(rng.standard_normal(J * N * N))
+    gota = plan.starlet_adj(z).cpu().numpy()
+    refa = ora.starlet_adj(N, J, z).reshape(-1)
+    assert np.abs(gota - refa).max() <= 2e-6 * np.abs(refa).max()
