@@ -2254,7 +2254,7 @@ int starred_estimate_lambda_pts(starred_plan *p, const float *params, double *la
     const long long NN = (long long)p->N * p->N;
     StarArgs sa = star_args(p, 1, nullptr);
     sa.W = p->W;
-    sa.lam0 = 1.f;
+    sa.lam0 = sa.lam1 = 1.f;
     sa.fp64 = false;
     const int B = p->M + 2, slots = star_l1_slots(sa);
     int rc = p->est_img ? STARRED_OK : p->alloc(&p->est_img, (size_t)B * NN);
@@ -2263,8 +2263,11 @@ int starred_estimate_lambda_pts(starred_plan *p, const float *params, double *la
     if (rc) return rc;
     HIP_TRY(launch_fill_d(p->st, p->est_part, (long long)B * slots));
     HIP_TRY(launch_pts_images(p->st, p->N, p->E, p->M, p->sigma, params, p->est_img));
-    for (int b = 0; b < B; ++b) {
+    // four images at a time: the planes between the groups hold so many in FP32
+    for (int b = 0; b < B; b += sa.B) {
+        sa.B = std::min(4, B - b);
         sa.img = p->est_img + b * NN;
+        sa.img1 = sa.img + NN;
         sa.part_l1 = p->est_part + (long long)b * slots;
         HIP_TRY(launch_star_forward(p->st, sa));
     }

@@ -27,3 +27,16 @@ def test_transform_and_transpose(N, J):
     gota = plan.starlet_adj(z).cpu().numpy()
     refa = ora.starlet_adj(N, J, z).reshape(-1)
     assert np.abs(gota - refa).max() <= 2e-6 * np.abs(refa).max()
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 7])  # three, four, five and nine images, four at a time
+def test_lambda_pts_estimate_over_batches_of_images(M):
+    from paper_2402_08725_amd import starred as st
+    prob = synth.make_small_deconv(M, 3, [24], 9, 2, 48, M, 4)
+    rng = np.random.default_rng(M)
+    d, w = synth.add_noise(rng.uniform(0, 300, prob.data_size), rng)
+    plan = st.Plan.for_problem(prob, conv_algo=st.CONV_FFT)
+    plan.set_frames(d, w, prob.kernels, prob.W)
+    p = synth.eval_point(prob, "near", rng)
+    # the parity suite's bar for this value
+    assert plan.estimate_lambda_pts(p) == pytest.approx(ora.lambda_pts_estimate(prob, p), rel=1e-4)

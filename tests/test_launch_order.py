@@ -51,3 +51,14 @@ for J in (1, 4):  # (one plane has nothing to ride)
     print(sum("DensePiece" in k for k in names), sum("NoPiece" in k for k in names), len(names))
 """).splitlines()
     assert out == ["0 4 4", "3 1 4"]
+
+
+def test_lambda_pts_estimate_transforms_four_images_per_launch(tmp_path):
+    out = fake_hip.run(tmp_path, """
+h = make_plan([32] * 2, [9] * 2, 1, 32, 7, 4)
+assert L.starred_set_frames(h, ptr(f32(2048)), ptr(f32(2048)), ptr(f32(162)), ptr(f32(4))) == st.OK
+launches([])
+L.starred_estimate_lambda_pts(h, ptr(f32(L.starred_num_params(h))), ctypes.byref(ctypes.c_double()))
+print(len(launches(["k_star_forward"])))
+""")
+    assert int(out) == 3  # nine images, one group of three levels
