@@ -175,6 +175,7 @@ struct AdjItem {
 struct LinePass {
     LineItem *items = nullptr;  // device
     int n_items = 0;
+    int aliases = 1;  // k_fold, k_unfold: lines of a column transformed at a time (1 or s)
     size_t lds_bytes = 0;
 };
 

@@ -511,7 +511,8 @@ struct OpKCols {
 // are each used once, up to kx = 0 and Q/2). The P-point transforms, the product with S'' and
 // the Q-point transform run on one line in LDS: no spectrum of the P or Q grid goes through
 // memory between them.
-// LDS: two planes of nl lines of P + 1 (transform and scratch) and nl lines of Q + 1.
+// LDS: two planes of nl lines of P + 1 for each alias transformed at a time (transform and scratch;
+// one alias, or all s where few columns leave the chip idle) and nl lines of Q + 1.
 // Bound by the LDS passes of the P-point transforms and by the row spectra's way through memory.
 // Models and back-projected residuals of 60 frames (64^2 and 90^2, s = 2): 205 us with a launch
 // per pass and whole spectra between them, 165 with these and the rows in pairs; loss and gradient
@@ -523,33 +524,37 @@ __global__ __launch_bounds__(kFftThreads) void k_fold(const LineItem *__restrict
                                                       const ClassFft *__restrict__ classes,
                                                       const FrameFft *__restrict__ fr, const float2 *__restrict__ tw,
                                                       const float2 *__restrict__ rowspec,
-                                                      const float2 *__restrict__ Sp, float2 *__restrict__ T)
+                                                      const float2 *__restrict__ Sp, float2 *__restrict__ T, int step)
 {
     extern __shared__ float2 sm[];
     const LineItem it = items[blockIdx.x];
     const ClassFft &c = classes[it.cls];
     const FrameFft &f = fr[it.frame];
     const int P = c.P, Q = c.Q, HP = P / 2 + 1, HQ = Q / 2 + 1, nl = it.nl, Ls = P + 1;
-    float2 *a = sm, *b = sm + nl * Ls, *m = sm + 2 * nl * Ls;
+    const int nq = nl * step;  // lines transformed at a time: step aliases of nl columns
+    float2 *a = sm, *b = sm + nq * Ls, *m = sm + 2 * nq * Ls;
     const float2 *X = rowspec + f.t3_off, *Si = Sp + f.s_off;
-    for (int be = 0; be < S; ++be) {
-        for (int e = threadIdx.x; e < nl * P; e += kFftThreads) {
-            const int y = e / nl, l = e - y * nl, Kx = it.line0 + l + be * Q;
-            a[l * Ls + y] = y < c.F ? X[y * HP + (2 * Kx <= P ? Kx : P - Kx)] : make_float2(0.f, 0.f);
+    for (int b0 = 0; b0 < S; b0 += step) {
+        for (int e = threadIdx.x; e < nq * P; e += kFftThreads) {
+            const int y = e / nq, q = e - y * nq, be = q / nl, Kx = it.line0 + q - be * nl + (b0 + be) * Q;
+            a[q * Ls + y] = y < c.F ? X[y * HP + (2 * Kx <= P ? Kx : P - Kx)] : make_float2(0.f, 0.f);
         }
         __syncthreads();
-        const float2 *r = lds_fft_any<false>(a, b, nl, c.fP, tw + c.fP.tw_off);
+        const float2 *r = lds_fft_any<false>(a, b, nq, c.fP, tw + c.fP.tw_off);
         for (int e = threadIdx.x; e < nl * Q; e += kFftThreads) {
             const int ky = e / nl, l = e - ky * nl, kx = it.line0 + l;
-            const bool lo = 2 * (kx + be * Q) <= P;
-            float2 sk[S], acc = be ? m[l * (Q + 1) + ky] : make_float2(0.f, 0.f);
-            alias_load<S>(Si, ((ky * HQ + kx) * S + be) * S, sk);
-            #pragma unroll
-            for (int al = 0; al < S; ++al) {
-                const int Ky = ky + al * Q;
-                float2 v = r[l * Ls + (lo || Ky == 0 ? Ky : P - Ky)];
-                v.y = lo ? v.y : -v.y;
-                acc = cadd(acc, cmul(sk[al], v));
+            float2 acc = b0 ? m[l * (Q + 1) + ky] : make_float2(0.f, 0.f);
+            for (int be = 0; be < step; ++be) {
+                const bool lo = 2 * (kx + (b0 + be) * Q) <= P;
+                float2 sk[S];
+                alias_load<S>(Si, ((ky * HQ + kx) * S + b0 + be) * S, sk);
+                #pragma unroll
+                for (int al = 0; al < S; ++al) {
+                    const int Ky = ky + al * Q;
+                    float2 v = r[(be * nl + l) * Ls + (lo || Ky == 0 ? Ky : P - Ky)];
+                    v.y = lo ? v.y : -v.y;
+                    acc = cadd(acc, cmul(sk[al], v));
+                }
             }
             m[l * (Q + 1) + ky] = acc;
         }
@@ -568,14 +573,15 @@ __global__ __launch_bounds__(kFftThreads) void k_unfold(const LineItem *__restri
                                                         const ClassFft *__restrict__ classes,
                                                         const FrameFft *__restrict__ fr, const float2 *__restrict__ tw,
                                                         const float2 *__restrict__ T2, const float2 *__restrict__ Sp,
-                                                        float2 *__restrict__ rowspec)
+                                                        float2 *__restrict__ rowspec, int step)
 {
     extern __shared__ float2 sm[];
     const LineItem it = items[blockIdx.x];
     const ClassFft &c = classes[it.cls];
     const FrameFft &f = fr[it.frame];
     const int P = c.P, Q = c.Q, HP = P / 2 + 1, HQ = Q / 2 + 1, nl = it.nl, Ls = P + 1;
-    float2 *a = sm, *b = sm + nl * Ls, *m = sm + 2 * nl * Ls;
+    const int nq = nl * step;  // lines transformed at a time: step aliases of nl columns
+    float2 *a = sm, *b = sm + nq * Ls, *m = sm + 2 * nq * Ls;
     for (int e = threadIdx.x; e < nl * Q; e += kFftThreads) {
         const int y = e / nl, l = e - y * nl;
         m[l * (Q + 1) + y] = y < c.n ? T2[f.t_off + (long long)y * HQ + it.line0 + l] : make_float2(0.f, 0.f);
@@ -588,20 +594,20 @@ __global__ __launch_bounds__(kFftThreads) void k_unfold(const LineItem *__restri
     }
     float2 *X = rowspec + f.t3_off;
     const float2 *Si = Sp + f.s_off;
-    for (int be = 0; be < S; ++be) {
-        for (int e = threadIdx.x; e < nl * Q; e += kFftThreads) {
-            const int ky = e / nl, l = e - ky * nl, kx = it.line0 + l;
+    for (int b0 = 0; b0 < S; b0 += step) {
+        for (int e = threadIdx.x; e < nq * Q; e += kFftThreads) {
+            const int ky = e / nq, q = e - ky * nq, be = q / nl, l = q - be * nl, kx = it.line0 + l;
             float2 sk[S];
-            alias_load<S>(Si, ((ky * HQ + kx) * S + be) * S, sk);
+            alias_load<S>(Si, ((ky * HQ + kx) * S + b0 + be) * S, sk);
             const float2 v = m[l * (Q + 1) + ky];
             #pragma unroll
-            for (int al = 0; al < S; ++al) a[l * Ls + ky + al * Q] = cmulc(v, sk[al]);
+            for (int al = 0; al < S; ++al) a[q * Ls + ky + al * Q] = cmulc(v, sk[al]);
         }
         __syncthreads();
-        const float2 *r = lds_fft_any<true>(a, b, nl, c.fP, tw + c.fP.tw_off);
-        for (int e = threadIdx.x; e < nl * c.F; e += kFftThreads) {
-            const int y = e / nl, l = e - y * nl, kx = it.line0 + l, Kx = kx + be * Q;
-            const float2 v = r[l * Ls + y];
+        const float2 *r = lds_fft_any<true>(a, b, nq, c.fP, tw + c.fP.tw_off);
+        for (int e = threadIdx.x; e < nq * c.F; e += kFftThreads) {
+            const int y = e / nq, q = e - y * nq, be = q / nl, kx = it.line0 + q - be * nl, Kx = kx + (b0 + be) * Q;
+            const float2 v = r[q * Ls + y];
             if (2 * Kx <= P) X[y * HP + Kx] = v;
             else if (kx > 0 && 2 * kx < Q) X[y * HP + P - Kx] = conjf2(v);  // (else another column's own)
         }
@@ -1438,7 +1444,7 @@ static hipError_t scene_forward(hipStream_t st, const FftPlanDev &d, const LineP
 {
     hipError_t e = run_row_pairs(st, srows, d, OpSceneRows{d.frames, scene, d.T3});
     if (e != hipSuccess) return e;
-    FOLD_LAUNCH(k_fold, fold, d.frames, d.tw, d.T3, d.S, d.T);
+    FOLD_LAUNCH(k_fold, fold, d.frames, d.tw, d.T3, d.S, d.T, fold.aliases);
     if (frows.n_items > 0)
         hipLaunchKernelGGL(k_fwd_rows, dim3(frows.n_items), dim3(kFftThreads), frows.lds_bytes, st, frows.items,
                            d.classes, d.frames, d.tw, d.T, data, invvar, d.T2, model, part_chi);
@@ -1449,7 +1455,7 @@ static hipError_t scene_forward(hipStream_t st, const FftPlanDev &d, const LineP
 static hipError_t resid_adjoint(hipStream_t st, const FftPlanDev &d, const LinePass &unfold, const LinePass &arows,
                                 int s, float *g)
 {
-    FOLD_LAUNCH(k_unfold, unfold, d.frames, d.tw, d.T2, d.S, d.T3);
+    FOLD_LAUNCH(k_unfold, unfold, d.frames, d.tw, d.T2, d.S, d.T3, unfold.aliases);
     hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : run_row_pairs(st, arows, d, OpAdjRows{d.frames, d.T3, g});
 }

@@ -921,7 +921,8 @@ static int build_fft_lists(starred_plan *p)
         // lines per work group: about kFftTargetElems elements, fewer when the
         // pass is small so that every compute unit gets work
         const long long want_groups = p->line_groups;
-        const int cap = (int)std::max((long long)min_lines, total_lines / want_groups);
+        const int cap = (int)std::max(std::min((long long)min_lines, total_lines / device_cus()),
+                                      std::max(1LL, total_lines / want_groups));
         int maxL = 1;
         for (int u = 0; u < nunits; ++u) {
             if (skip(u)) continue;
@@ -962,19 +963,33 @@ static int build_fft_lists(starred_plan *p)
     if ((rc = make_pass(d.gcols, true, [](const ClassFft &c) { return c.P / 2 + 1; }, LP))) return rc;
     if ((rc = make_pass(d.grows, true, [](const ClassFft &c) { return c.F; }, LP))) return rc;
     // operators on given scenes and residuals: rows in pairs, and columns of the Q grid with
-    // their P-point lines (k_fold: two planes of P + 1 and one of Q + 1 per line; four lines at
-    // least, whose columns share memory sectors)
+    // their P-point lines (k_fold: `aliases` of them at a time, two planes of P + 1 for each and
+    // one of Q + 1 per column; four columns at least, which share memory sectors). Where there are
+    // fewer than four columns per compute unit their chain is what takes the time: fewer columns in a
+    // group then, and all s lines of a column at once (three frames of 64^2 at s = 3, model and
+    // back-projection: 34 and 31 us with four columns and a line at a time, 20 and 19 so).
     auto pairsF = [](const ClassFft &c) { return (c.F + 1) / 2; };
     auto pairsn = [](const ClassFft &c) { return (c.n + 1) / 2; };
-    auto colsQ = [](const ClassFft &c) { return c.Q / 2 + 1; };
-    auto LF = [](const ClassFft &c) { return c.P + 1 + (c.Q + 1) / 2; };
+    auto fold_pass = [&](LinePass &lp, bool all) {
+        long long cols = 0, most = 0;
+        for (int i = 0; i < E; ++i) {
+            const ClassFft &c = p->cls[fcls[i]];
+            if (!all && is_direct(fcls[i])) continue;
+            cols += c.Q / 2 + 1;
+            most = std::max(most, (long long)p->s * (c.P + 1) + (c.Q + 1) / 2);
+        }
+        const bool few = cols < 4LL * device_cus() && most <= kFftTargetElems;
+        lp.aliases = few ? p->s : 1;
+        return make_pass(lp, false, [](const ClassFft &c) { return c.Q / 2 + 1; },
+                         [&](const ClassFft &c) { return lp.aliases * (c.P + 1) + (c.Q + 1) / 2; }, false, all, 4);
+    };
     if ((rc = make_pass(d.srows, false, pairsF, LP))) return rc;
     if ((rc = make_pass(d.rrows, false, pairsn, LQ))) return rc;
     if ((rc = make_pass(d.arows, false, pairsF, LP))) return rc;
-    if ((rc = make_pass(d.fold, false, colsQ, LF, false, false, 4))) return rc;
+    if ((rc = fold_pass(d.fold, false))) return rc;
     // every frame: the per-frame convolution of the rendered scenes (frame transforms)
     if ((rc = make_pass(d.srows_x, false, pairsF, LP, false, true))) return rc;
-    if ((rc = make_pass(d.fold_x, false, colsQ, LF, false, true, 4))) return rc;
+    if ((rc = fold_pass(d.fold_x, true))) return rc;
     if ((rc = make_pass(d.frows_x, false, [](const ClassFft &c) { return c.n; }, LQ, false, true))) return rc;
     if ((rc = make_pass(d.arows_x, false, pairsF, LP, false, true))) return rc;
     // the direct path's lists for the frames of the direct classes
