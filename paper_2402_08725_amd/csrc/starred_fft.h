@@ -90,13 +90,14 @@ struct SpecItem {
 
 // The transform lengths of the one-launch forward (starred_frame.h): Q = RA RB, and the
 // frames NF that a work group takes of a class when frames outnumber the compute units
-// (X(Q, RA, RB, NF)): every even 5-smooth length from 18 to 180 but 162, which has no two
+// (X(Q, RA, RB, NF)): every even 5-smooth length from 16 to 180 but 162, which has no two
 // factors up to 16. RA is at least 8, so that the residual's reads come in runs of 32 bytes
 // or more. Two frames of 120 or more would need more registers than 1024 threads have (128
 // is the exception), or more LDS than there is. 192 has a body for s = 1 without point sources
 // (frame_body_frames), the only frames of that length whose plane and tables fit: 300 frames of
 // 128^2 207 us on the line passes, 127 with it.
 #define STARRED_FRAME_LENGTHS(X) \
+    X(16, 8, 2, 4)               \
     X(18, 9, 2, 4)               \
     X(20, 10, 2, 4)              \
     X(24, 12, 2, 4)              \
@@ -121,7 +122,7 @@ struct SpecItem {
     X(150, 15, 10, 1)            \
     X(160, 16, 10, 1)            \
     X(180, 15, 12, 1)
-constexpr int kFrameMaxQ = 180;
+constexpr int kFrameMinQ = 16, kFrameMaxQ = 180;
 constexpr int kFrameLongQ = 192;
 
 // frames that a work group may take of a class with transform length Q (0: no body);

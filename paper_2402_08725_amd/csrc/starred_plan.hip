@@ -562,17 +562,18 @@ static bool frame_fits(int P, int s, int M, int per = 1)
 }
 
 // smallest P >= need with P a multiple of 2s and P = 2^a 3^b 5^c; where that has no one-launch
-// forward, the next one that has, for s = 1 and 2 or up to Q = 18. Q = 162 becomes 180 so: 300
+// forward, the next one that has, for s = 1 and 2 or up to Q = 16. Q = 162 becomes 180 so: 300
 // frames of 100^2 (s = 1, one source) 213 -> 123 us, of 130^2 (s = 2) 304 -> 218 us. It stays
 // where the sources' tables leave no room at 180 (s = 2, four sources: 347 us, 354 at 180 on the
 // line passes) and for s = 3, whose spectra grow the most (one source: 412 us, 425 at 180).
-// Shorter ones than 18: 3000 frames of 8^2 (s = 1) 199 -> 135 us, of 6^2 (s = 3) 216 -> 192 us.
+// Shorter ones than 16: 3000 frames of 8^2 (s = 1) 198 us at 10, 131 at 16; of 6^2
+// (s = 3) 216 us at 8, 180 at 16.
 static int good_size(int need, int s, int M)
 {
     const auto smooth = [&](int P) { return P % (2 * s) == 0 && smooth235(P); };
     int P = need;
     while (!smooth(P)) ++P;
-    for (int R = P; R <= (s < 3 ? kFrameMaxQ : 18) * s; ++R)
+    for (int R = P; R <= (s < 3 ? kFrameMaxQ : kFrameMinQ) * s; ++R)
         if (smooth(R) && frame_fits(R, s, M)) return R;
     return P;
 }

@@ -14,8 +14,10 @@ CASES = [
     (150, 46, 2, 2, 162, False),
     (155, 40, 3, 1, 162, False),
     (155, 40, 3, 2, 162, False),
-    (8, 3, 1, 1, 18, True),
-    (8, 5, 2, 2, 18, True),
+    (8, 3, 1, 1, 16, True),
+    (8, 5, 2, 2, 16, True),
+    (13, 9, 3, 1, 16, True),
+    (13, 13, 1, 1, 20, True),
     (6, 5, 3, 300, 8, False),
     (150, 80, 1, 1, 192, False),
     (150, 80, 1, 0, 192, True),

@@ -46,6 +46,24 @@ def test_sources_of_the_largest_transforms(Q, s, M):
         assert parity.rel_err(blk, parity.deconv_blocks(prob, go)[name]) <= 1e-4, name
 
 
+@pytest.mark.parametrize("s", [1, 2, 3])
+@pytest.mark.parametrize("n,K,E", [(2, 3, 3), (8, 5, 3), (13, 3, 3), (16, 1, 3), (11, 9, 0)])
+def test_the_shortest_transform(s, n, K, E):
+    """Q = 16, for shorter needs too; E = 0: more frames than compute units."""
+    print(f"n {n} K {K} s {s}", flush=True)
+    E = E or torch.cuda.get_device_properties(0).multi_processor_count + 2
+    prob, d, w, p = _problem(n, K, s, E, 1 if n == 2 else 3, n + s)
+    plan = _plan(prob, d, w)
+    ci = plan.classes()[0]
+    assert ci["Q"] == 16 and ci["fused"], ci
+    loss, grad = plan.loss_grad(p)
+    loss, grad = loss.cpu().numpy(), grad.cpu().numpy().astype(np.float64)
+    lo, go = ora.loss_grad(prob, d, w, p)
+    assert abs(loss[2] - lo[2]) <= 1e-6 * abs(lo[2])
+    for name, blk in parity.deconv_blocks(prob, grad).items():
+        assert parity.rel_err(blk, parity.deconv_blocks(prob, go)[name]) <= 1e-4, name
+
+
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("n,K", [(12, 24), (40, 80)])  # groups of four frames, and of two
 def test_a_frame_that_is_not_finite_leaves_the_others(n, K, bad):
