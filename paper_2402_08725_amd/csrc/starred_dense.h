@@ -28,24 +28,23 @@
 
 namespace starred {
 
-constexpr int kDenseMaxJ = 8;  // at most 7 scales (eight need more LDS than the cap: the cascade)
+constexpr int kDenseMaxJ = 8;  // levels 1 .. 6 fit the LDS cap (seven scales)
 constexpr int kDenseTile = 16;  // y-pass output tiles
 constexpr int kDenseThreads = 256;
 
 struct DenseStar {
-    int N = 0, J = 0, B = 0;
+    int N = 0, J = 0;
     int rx = 1;                  // rows per x-pass job
     const double *taps = nullptr;  // levels 1 .. J-1 one after the other (plen(j) entries each)
-    const float *img = nullptr;  // image 0 (N x N)
-    const float *img1 = nullptr; // image 1 (N x N), when B = 2
-    double *T = nullptr;         // [B][J][N][N]: plane j >= 1 = x M_j^T, then (pass D1) D^-1 (M_j U_j) D^-1
-    double *C = nullptr;         // [B][J][N][N]: plane j >= 1 = c_j
-    double *U = nullptr;         // [B][J][N][N]: plane 0 = z_0, plane j >= 1 = (D Y_j D) M_j^T
+    const float *img = nullptr;  // the image (N x N)
+    double *T = nullptr;         // [J][N][N]: plane j >= 1 = x M_j^T, then (pass D1) D^-1 (M_j U_j) D^-1
+    double *C = nullptr;         // [J][N][N]: plane j >= 1 = c_j
+    double *U = nullptr;         // [J][N][N]: plane 0 = z_0, plane j >= 1 = (D Y_j D) M_j^T
     const float *W = nullptr;    // weights: per pixel [J][N][N] (w_stride != 0) or per scale [J]
     int w_stride = 0;
-    float lam0 = 0.f, lam1 = 0.f;  // image 0's and image 1's weight
+    float lam = 0.f;
     bool want_grad = false;      // build U_j and T_j
-    double *part_l1 = nullptr;   // [B][J][rows jobs]
+    double *part_l1 = nullptr;   // [J][rows jobs]
 
     // half width of level j's composite filter, 2^{j+1} - 2; its 2 bw + 1 taps
     // zero-padded to plen(j), a multiple of 16 (the filter loops read whole blocks
@@ -56,13 +55,12 @@ struct DenseStar {
     __host__ __device__ static constexpr int toff(int j) { return j >= 2 ? (4 << j) : 0; }
     __host__ __device__ int xjobs() const { return (N + rx - 1) / rx; }
     __host__ __device__ int tiles() const { return (N + kDenseTile - 1) / kDenseTile; }
-    __host__ __device__ int jobs_a() const { return B * (J - 1) * xjobs(); }
-    __host__ __device__ int jobs_b() const { return B * (J - 1) * tiles() * tiles(); }
-    __host__ __device__ int jobs_c() const { return B * J * xjobs(); }
-    __host__ __device__ int jobs_d1() const { return B * (J - 1) * tiles() * tiles(); }
-    __host__ __device__ int l1_slots() const { return B * J * xjobs(); }
-    __host__ __device__ const float *image(int b) const { return b ? img1 : img; }
-    __host__ __device__ long long plane(int b, int j) const { return ((long long)b * J + j) * N * N; }
+    __host__ __device__ int jobs_a() const { return (J - 1) * xjobs(); }
+    __host__ __device__ int jobs_b() const { return (J - 1) * tiles() * tiles(); }
+    __host__ __device__ int jobs_c() const { return J * xjobs(); }
+    __host__ __device__ int jobs_d1() const { return (J - 1) * tiles() * tiles(); }
+    __host__ __device__ int l1_slots() const { return J * xjobs(); }
+    __host__ __device__ long long plane(int j) const { return (long long)j * N * N; }
 };
 
 __device__ __forceinline__ int dmirror(int i, int N)
@@ -237,11 +235,10 @@ __device__ __forceinline__ double dense_ysum(const DenseStar &d, int j, const do
 // ---- pass A: T_j = x M_j^T ----
 __device__ __forceinline__ void dense_job_a(const DenseStar &d, int job, double *lds)
 {
-    const int xj = d.xjobs(), per_b = (d.J - 1) * xj;
-    const int b = job / per_b, rem = job - b * per_b, j = 1 + rem / xj, y0 = (rem % xj) * d.rx;
+    const int xj = d.xjobs(), j = 1 + job / xj, y0 = (job % xj) * d.rx;
     const int ny = min(d.rx, d.N - y0), N = d.N;
-    const float *im = d.image(b);
-    double *T = d.T + d.plane(b, j);
+    const float *im = d.img;
+    double *T = d.T + d.plane(j);
     dense_xpass(
         d, j, y0, ny, lds, [&](int y, int k) { return (double)im[y * N + k]; },
         [&](int y, int x, double v) { T[y * N + x] = v; });
@@ -250,43 +247,41 @@ __device__ __forceinline__ void dense_job_a(const DenseStar &d, int job, double 
 // ---- pass B: c_j = M_j T_j ----
 __device__ __forceinline__ void dense_job_b(const DenseStar &d, int job, double *lds)
 {
-    const int nt = d.tiles(), per_j = nt * nt, per_b = (d.J - 1) * per_j;
-    const int b = job / per_b, rem = job - b * per_b, j = 1 + rem / per_j, tile = rem % per_j;
+    const int nt = d.tiles(), per_j = nt * nt, j = 1 + job / per_j, tile = job % per_j;
     const int y0 = (tile / nt) * kDenseTile, x0 = (tile % nt) * kDenseTile, N = d.N;
-    const double *T = d.T + d.plane(b, j);
+    const double *T = d.T + d.plane(j);
     dense_ystage(d, j, y0, x0, lds, [&](int y, int x) { return T[y * N + x]; });
     __syncthreads();
     const int ty = threadIdx.x / kDenseTile, tx = threadIdx.x % kDenseTile;
     if (threadIdx.x < kDenseTile * kDenseTile && y0 + ty < N && x0 + tx < N)
-        d.C[d.plane(b, j) + (y0 + ty) * N + x0 + tx] = dense_ysum(d, j, lds, ty, tx);
+        d.C[d.plane(j) + (y0 + ty) * N + x0 + tx] = dense_ysum(d, j, lds, ty, tx);
 }
 
-// alpha_j at (y, k) of image b: c_j - c_{j+1} with c_0 the image, c_J = 0
-__device__ __forceinline__ double dense_alpha(const DenseStar &d, int b, int j, int y, int k)
+// alpha_j at (y, k): c_j - c_{j+1} with c_0 the image, c_J = 0
+__device__ __forceinline__ double dense_alpha(const DenseStar &d, int j, int y, int k)
 {
     const int N = d.N;
     const long long pix = (long long)y * N + k;
-    const double cj = j == 0 ? (double)d.image(b)[pix] : d.C[d.plane(b, j) + pix];
-    const double cn = j + 1 < d.J ? d.C[d.plane(b, j + 1) + pix] : 0.0;
+    const double cj = j == 0 ? (double)d.img[pix] : d.C[d.plane(j) + pix];
+    const double cn = j + 1 < d.J ? d.C[d.plane(j + 1) + pix] : 0.0;
     return cj - cn;
 }
 
 // z_j at (y, k): lambda W_j sgn(alpha_j) (FP32 product)
-__device__ __forceinline__ float dense_z(const DenseStar &d, int b, int j, int y, int k, float lam)
+__device__ __forceinline__ float dense_z(const DenseStar &d, int j, int y, int k, float lam)
 {
     const long long pix = (long long)y * d.N + k, NN = (long long)d.N * d.N;
     const float w = d.w_stride ? d.W[j * NN + pix] : d.W[j];
-    return lam * w * dsgn(dense_alpha(d, b, j, y, k));
+    return lam * w * dsgn(dense_alpha(d, j, y, k));
 }
 
 // ---- pass C: z, the L1 share, U_j = (D Y_j D) M_j^T ----
 __device__ __forceinline__ void dense_job_c(const DenseStar &d, int job, double *lds, double *red)
 {
-    const int xj = d.xjobs(), per_b = d.J * xj;
-    const int b = job / per_b, rem = job - b * per_b, j = rem / xj, y0 = (rem % xj) * d.rx;
+    const int xj = d.xjobs(), j = job / xj, y0 = (job % xj) * d.rx;
     const int ny = min(d.rx, d.N - y0), N = d.N;
     const long long NN = (long long)N * N;
-    const float lam = b ? d.lam1 : d.lam0;
+    const float lam = d.lam;
     double l1 = 0.0;
     {
         // the level's L1 share over this job's rows
@@ -294,29 +289,29 @@ __device__ __forceinline__ void dense_job_c(const DenseStar &d, int job, double 
             const int y = y0 + e / N, k = e % N;
             const long long pix = (long long)y * N + k;
             const float w = d.w_stride ? d.W[j * NN + pix] : d.W[j];
-            l1 += (double)lam * (double)w * fabs(dense_alpha(d, b, j, y, k));
+            l1 += (double)lam * (double)w * fabs(dense_alpha(d, j, y, k));
         }
     }
-    double *U = d.U + d.plane(b, j);
+    double *U = d.U + d.plane(j);
     if (!d.want_grad) {
         // the loss alone: no subgradient image
     } else if (j == 0) {
         for (int e = threadIdx.x; e < ny * N; e += blockDim.x) {
             const int y = y0 + e / N, k = e % N;
-            U[y * N + k] = (double)dense_z(d, b, 0, y, k, lam);
+            U[y * N + k] = (double)dense_z(d, 0, y, k, lam);
         }
     } else {
         dense_xpass(
             d, j, y0, ny, lds,
             [&](int y, int k) {
-                const double yv = (double)dense_z(d, b, j, y, k, lam) - (double)dense_z(d, b, j - 1, y, k, lam);
+                const double yv = (double)dense_z(d, j, y, k, lam) - (double)dense_z(d, j - 1, y, k, lam);
                 return dend(y, N) * dend(k, N) * yv;
             },
             [&](int y, int x, double v) { U[y * N + x] = v; });
     }
     if (d.part_l1) {
         const double s = dense_block_sum(l1, red);
-        if (threadIdx.x == 0) d.part_l1[(b * d.J + j) * xj + (y0 / d.rx)] = s;
+        if (threadIdx.x == 0) d.part_l1[job] = s;
     }
 }
 
@@ -325,22 +320,21 @@ __device__ __forceinline__ void dense_job_c(const DenseStar &d, int job, double 
 // U_0 + sum_j T_j at each pixel (dense_prior_at), summed by its reader.
 __device__ __forceinline__ void dense_job_d1(const DenseStar &d, int job, double *lds)
 {
-    const int nt = d.tiles(), per_j = nt * nt, per_b = (d.J - 1) * per_j;
-    const int b = job / per_b, rem = job - b * per_b, j = 1 + rem / per_j, tile = rem % per_j;
+    const int nt = d.tiles(), per_j = nt * nt, j = 1 + job / per_j, tile = job % per_j;
     const int y0 = (tile / nt) * kDenseTile, x0 = (tile % nt) * kDenseTile, N = d.N;
-    const double *U = d.U + d.plane(b, j);
+    const double *U = d.U + d.plane(j);
     dense_ystage(d, j, y0, x0, lds, [&](int y, int x) { return U[y * N + x]; });
     __syncthreads();
     const int ty = threadIdx.x / kDenseTile, tx = threadIdx.x % kDenseTile, y = y0 + ty, x = x0 + tx;
     if (threadIdx.x < kDenseTile * kDenseTile && y < N && x < N)
-        d.T[d.plane(b, j) + y * N + x] = dense_ysum(d, j, lds, ty, tx) / (dend(y, N) * dend(x, N));
+        d.T[d.plane(j) + y * N + x] = dense_ysum(d, j, lds, ty, tx) / (dend(y, N) * dend(x, N));
 }
 
-// the subgradient image of image b at pixel pix after pass D1
-__device__ __forceinline__ double dense_prior_at(const DenseStar &d, int b, long long pix)
+// the subgradient image at pixel pix after pass D1
+__device__ __forceinline__ double dense_prior_at(const DenseStar &d, long long pix)
 {
-    double v = d.U[d.plane(b, 0) + pix];
-    for (int j = 1; j < d.J; ++j) v += d.T[d.plane(b, j) + pix];
+    double v = d.U[d.plane(0) + pix];
+    for (int j = 1; j < d.J; ++j) v += d.T[d.plane(j) + pix];
     return v;
 }
 
@@ -350,7 +344,7 @@ namespace starred {
 
 // One pass of the composite-filter prior carried by another launch: its work
 // groups first .. first+jobs-1 run the pass's jobs (they need at least
-// kDenseThreads threads and dense_piece_lds bytes of dynamic LDS).
+// kDenseThreads threads and the LDS of dense_lds_xr or dense_lds_y).
 struct DensePiece {
     DenseStar d;
     int pass = -1;  // 0..2: A..C, 4: D1; -1: none

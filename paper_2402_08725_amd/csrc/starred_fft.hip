@@ -12,11 +12,12 @@
 // is g = window of IDFT_P( conj(S''(K)) rho_hat(K mod Q) ), rho_hat = DFT_Q(rho).
 // Transforms are unnormalised; every constant sits in S''.
 //
-// All 2-D transforms are row/column passes of batched 1-D Stockham FFTs
-// (radices 4, 2, 3, 5) staged in LDS; each pass is one launch over every frame
+// The 2-D transforms here are row/column passes of batched 1-D Stockham FFTs
+// (radices 8, 4, 2, 3, 5) staged in LDS; each pass is one launch over every frame
 // of every shape class (a table of line groups), with loads and stores that
 // fuse the spectral products, the Hermitian extensions, the crops and the
-// residual / chi-square epilogue.
+// residual / chi-square epilogue. Frames whose Q-grid plane fits in LDS take the
+// one-launch forward of starred_frame.h instead, with register transforms.
 #include "starred_fft.h"
 #include "starred_finalize.h"
 #include "starred_radix.h"
@@ -354,21 +355,6 @@ __global__ __launch_bounds__(kFftThreads) void k_row_pairs(const LineItem *__res
             if (y + 1 < rows) op.store(cl, it.frame, y + 1, j, make_float2(0.5f * (z.y + m.y), 0.5f * (m.x - z.x)));
         }
     }
-}
-
-// Half-spectrum access with Hermitian symmetry: X is [P][P/2+1]; returns X(ky, kx)
-// for any kx in [0, P).
-// Branch-free (selects, one unconditional load) so that the loads of several
-// calls can be in flight together.
-__device__ __forceinline__ float2 half_get(const float2 *__restrict__ X, int P, int ky, int kx)
-{
-    const int H = P / 2 + 1;
-    const bool lo = kx < H;
-    const int ry = lo ? ky : (ky == 0 ? 0 : P - ky);
-    const int rx = lo ? kx : P - kx;
-    float2 v = X[(long long)ry * H + rx];
-    v.y = lo ? v.y : -v.y;
-    return v;
 }
 
 // Spectra that meet an alias fold (S'', the class's H and the summed adjoint spectra) are
@@ -1322,7 +1308,7 @@ struct OpGRowsFin {
         const long long pix = (long long)y * fin.N + x;
         float bc1, bc2;
         adam_bias(fin.adam, bc1, bc2);
-        const float pg = psum.U ? (float)dense_prior_at(psum, 0, pix) : (prior ? prior[pix] : 0.f);
+        const float pg = psum.U ? (float)dense_prior_at(psum, pix) : (prior ? prior[pix] : 0.f);
         finalize_h_pixel(fin.adam, bc1, bc2, pix, pg + v.x, fin.grad);
     }
 };

@@ -152,7 +152,7 @@ void dense_taps(int J, double *out);  // host: the composite filters of levels 1
 size_t dense_lds_x(int N, int J);
 size_t dense_lds_xr(int N, int J, int rx);  // rx rows per job
 size_t dense_lds_y(int J);
-hipError_t launch_pts_render(hipStream_t st, int N, int E, int M, float sigma, const float *params, float *h_out,
+hipError_t launch_pts_render(hipStream_t st, int N, int E, int M, float sigma, const float *params,
                              float *P_out);
 hipError_t launch_pts_dots(hipStream_t st, int N, int E, int M, float sigma, const float *params, const float *q,
                            double *pts);

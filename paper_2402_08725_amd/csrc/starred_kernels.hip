@@ -856,7 +856,7 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize_small(FinalArgs fa, co
     float bc1, bc2;
     adam_bias(fa.adam, bc1, bc2);
     const int Y = (int)(pix / N), X = (int)(pix % N);
-    float acc = psum.U ? (float)dense_prior_at(psum, 0, pix) : (prior ? prior[pix] : 0.f);
+    float acc = psum.U ? (float)dense_prior_at(psum, pix) : (prior ? prior[pix] : 0.f);
     for (int ci = 0; ci < ncls; ++ci) {
         const ClassFft &c = classes[ci];
         if (c.direct) continue;  // its frames' windows are in prior (the direct path's sum)
@@ -903,9 +903,9 @@ hipError_t launch_finalize_small(hipStream_t st, int E, int M, int n_chi, const 
 // carry its prior's gradient to a and c.
 // --------------------------------------------------------------------------
 
-// P_out = P and, when h_out is given, h_out = h (copied); <a_k> per work group
+// P_out = P; <a_k> per work group
 __global__ __launch_bounds__(256) void k_pts_render(int N, int E, int M, float sigma, const float *__restrict__ params,
-                                                     float *__restrict__ h_out, float *__restrict__ P_out)
+                                                     float *__restrict__ P_out)
 {
     extern __shared__ float am[];  // <a_k>
     const long long NN = (long long)N * N;
@@ -925,16 +925,15 @@ __global__ __launch_bounds__(256) void k_pts_render(int N, int E, int M, float s
         const float dx = (float)X - c[2 * k], dy = (float)Y - c[2 * k + 1];
         if (fabsf(dx) <= kGaussRadius && fabsf(dy) <= kGaussRadius) v += am[k] * norm * expf(-(dx * dx + dy * dy) * inv2s2);
     }
-    if (h_out) h_out[pix] = params[pix];
     P_out[pix] = v;
 }
 
-hipError_t launch_pts_render(hipStream_t st, int N, int E, int M, float sigma, const float *params, float *h_out,
+hipError_t launch_pts_render(hipStream_t st, int N, int E, int M, float sigma, const float *params,
                              float *P_out)
 {
     const long long NN = (long long)N * N;
     hipLaunchKernelGGL(k_pts_render, dim3((unsigned)((NN + 255) / 256)), dim3(256), sizeof(float) * (M > 0 ? M : 1),
-                       st, N, E, M, sigma, params, h_out, P_out);
+                       st, N, E, M, sigma, params, P_out);
     return hipGetLastError();
 }
 

@@ -96,9 +96,9 @@ struct starred_plan {
     double *d_part_chi = nullptr, *d_part_l1 = nullptr, *d_fsum = nullptr;
     float *d_z = nullptr, *d_prior = nullptr;
     double *d_ca = nullptr, *d_cb = nullptr;  // starlet planes between the passes
-    // Eq. 11, third term: weight, [h | P] images, shares of dL/da and dL/dc (3M)
+    // Eq. 11, third term: weight, the image P, shares of dL/da and dL/dc (3M)
     double lam_pts = 0.0;
-    float *d_pair = nullptr;
+    float *d_pts_img = nullptr;
     double *d_pts = nullptr;
     double *d_lbfgs_alpha = nullptr;  // two-loop coefficients of starred_lbfgs_direction
     // its App. C estimate: images [f | h | r_k], L1 partials, norms and <a_k>
@@ -354,7 +354,7 @@ static int validate(const starred_desc *d)
     return STARRED_OK;
 }
 
-// The starlet transform of B images (image 0 at img, the others at d_pair + N^2) with the
+// The starlet transform of B images (image 0 at img, image 1 the point-source image) with the
 // plan's weights: which outputs it has is the caller's to set.
 static StarArgs star_args(const starred_plan *p, int B, const float *img)
 {
@@ -364,7 +364,7 @@ static StarArgs star_args(const starred_plan *p, int B, const float *img)
     a.B = B;
     a.fp64 = star_fp64(p->N, p->J);
     a.img = img;
-    a.img1 = p->d_pair ? p->d_pair + (size_t)p->N * p->N : nullptr;
+    a.img1 = p->d_pts_img;
     a.w_stride = p->w_stride;
     a.lam0 = (float)p->lam;
     a.lam1 = (float)p->lam_pts;
@@ -396,7 +396,6 @@ static DenseStar dense_desc(const starred_plan *p, const float *img)
     DenseStar d;
     d.N = p->N;
     d.J = p->J;
-    d.B = 1;
     d.rx = dense_rows_per_job(p->N);
     d.taps = p->d_dense_taps;
     d.img = img;
@@ -405,7 +404,7 @@ static DenseStar dense_desc(const starred_plan *p, const float *img)
     d.U = p->d_dense_U;
     d.W = p->W;
     d.w_stride = p->w_stride;
-    d.lam0 = (float)p->lam;
+    d.lam = (float)p->lam;
     return d;
 }
 
@@ -469,7 +468,7 @@ static int build_deconv(starred_plan *p)
     if ((rc = p->alloc(&p->d_z, (size_t)2 * p->J * NN))) return rc;
     if ((rc = p->alloc(&p->d_ca, 2 * NN))) return rc;
     if ((rc = p->alloc(&p->d_cb, 2 * NN))) return rc;
-    if ((rc = p->alloc(&p->d_pair, 2 * NN))) return rc;
+    if ((rc = p->alloc(&p->d_pts_img, NN))) return rc;
     if ((rc = p->alloc(&p->d_pts, (size_t)3 * std::max(1, p->M)))) return rc;
     if ((rc = p->alloc(&p->d_prior, 2 * NN))) return rc;
     p->hpart_chunks = finalize_h_chunks(E);
@@ -1432,13 +1431,7 @@ int starred_starlet_adj(starred_plan *p, const float *coeffs, float *img)
     return STARRED_OK;
 }
 
-// Starlet transform, L1 term, subgradient and adjoint of the image part of
-// params (h, or b in PSF mode) on the second stream: fork from st, join with
-// ev_join (the caller waits on it before the final reductions).
-// The prior terms on stream st: lambda ||W (.) Phi^T img||_1 with its gradient
-// Phi z in d_prior and, when lambda_pts != 0 (deconvolution), the point-source
-// term of Eq. 11 transformed together with h (a batch of two images): its
-// gradient's shares of dL/da and dL/dc land in d_pts.
+// the prior's transform of img (B = 2: and of the point-source image)
 static StarArgs prior_args(const starred_plan *p, int B, const float *img, bool want_grad)
 {
     StarArgs a = star_args(p, B, img);
@@ -1449,11 +1442,15 @@ static StarArgs prior_args(const starred_plan *p, int B, const float *img, bool 
     return a;
 }
 
+// The prior terms on stream st: lambda ||W (.) Phi^T img||_1 with its gradient
+// Phi z in d_prior and, when lambda_pts != 0 (deconvolution), the point-source
+// term of Eq. 11 transformed together with h (a batch of two images): its
+// gradient's shares of dL/da and dL/dc land in d_pts.
 static int prior_launches(starred_plan *p, hipStream_t st, const float *img, bool want_grad, int *n_l1)
 {
     const bool pts = p->mode == STARRED_DECONV && p->lam_pts != 0.0;
     const long long NN = (long long)p->N * p->N;
-    if (pts) HIP_TRY(launch_pts_render(st, p->N, p->E, p->M, p->sigma, img, nullptr, p->d_pair + NN));
+    if (pts) HIP_TRY(launch_pts_render(st, p->N, p->E, p->M, p->sigma, img, p->d_pts_img));
     const StarArgs a = prior_args(p, pts ? 2 : 1, img, want_grad);
     HIP_TRY(launch_star_forward(st, a));
     *n_l1 = a.B * star_l1_slots(a);
@@ -2257,7 +2254,7 @@ int starred_pts_image(starred_plan *p, const float *params, float *P_out)
 {
     if (!p || !params || !P_out) return fail(STARRED_EINVAL, "NULL argument");
     if (p->mode != STARRED_DECONV) return fail(STARRED_EUNSUPPORTED, "the point-source prior is a deconvolution term");
-    HIP_TRY(launch_pts_render(p->st, p->N, p->E, p->M, p->sigma, params, nullptr, P_out));
+    HIP_TRY(launch_pts_render(p->st, p->N, p->E, p->M, p->sigma, params, P_out));
     return STARRED_OK;
 }
 

@@ -27,7 +27,7 @@
 // Precision: V is the type of the pixels in a pass and of the planes between the groups.
 // FP64 for one or two images up to 256^2 with at most seven planes (prior and transform),
 // FP32 beyond (larger grids, eight planes and more, batches of noise fields), where a wide
-// tile's LDS traffic bounds the pass and a cascade of FP32 launches did the same before.
+// tile's LDS traffic bounds the pass.
 //
 // What bounds a pass: with FP64 tiles of 16 the latency of its loads, barriers and LDS reads
 // (1.9 k to 6.4 k filtered pixels per job, five reads and a write each); with FP32 tiles of
