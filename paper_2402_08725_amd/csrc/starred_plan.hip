@@ -1562,7 +1562,8 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
         HIP_TRY(fft_spectra(p->st, p->fd, params, p->N, p->E, p->M, p->sigma, adam ? tick : nullptr,
                             ride ? &pa : nullptr, ride ? &pb : nullptr));
         p->prof_stop(STARRED_STAGE_SPECTRA, e0);
-        if (int rc = prior_flush()) return rc;
+        if (fused)
+            if (int rc = prior_flush()) return rc;
         e0 = p->prof_start();
         hipEvent_t e1;
         // chi-square partials: the line-pass frames' row groups, then one per fused frame
@@ -1586,6 +1587,9 @@ static int loss_grad_impl(starred_plan *p, const float *params, float *grad, dou
         e1 = p->prof_start();
         HIP_TRY(fused ? fft_model_cols_lg(p->st, p->fd) : fft_model_cols(p->st, p->fd));
         p->prof_stop(STARRED_STAGE_FFT_MCOLS, e1);
+        // (the line passes alone: two launches further on, so that in a call outside a graph the
+        // main stream has work while the host launches the branch)
+        if (int rc = prior_flush()) return rc;
         e1 = p->prof_start();
         HIP_TRY(fused ? fft_model_rows_lg(p->st, p->fd, p->data, p->invvar, p->d_part_chi_fft, grad != nullptr)
                       : fft_model_rows(p->st, p->fd, p->data, p->invvar, p->d_part_chi_fft, nullptr, grad != nullptr));

@@ -62,3 +62,18 @@ L.starred_estimate_lambda_pts(h, ptr(f32(L.starred_num_params(h))), ctypes.byref
 print(len(launches(["k_star_forward"])))
 """)
     assert int(out) == 3  # nine images, one group of three levels
+
+
+def test_line_passes_go_on_while_the_prior_is_launched(tmp_path):
+    """An evaluation on the line passes alone: the main stream has its spectra, product and columns
+    before the host turns to the prior's branch."""
+    out = fake_hip.run(tmp_path, """
+h = make_plan([32] * 2, [16] * 2, 2, 64, 1, 4)
+assert L.starred_set_frames(h, ptr(f32(2048)), ptr(f32(2048)), ptr(f32(512)), ptr(f32(4))) == st.OK
+assert L.starred_set_fft_fused(h, 0) == st.OK
+P = L.starred_num_params(h)
+launches([])
+assert L.starred_loss_grad(h, ptr(f32(P)), ptr(f32(P)), ptr(np.zeros(3))) == st.OK
+print(*launches(["OpHCols", "k_spec_fwd", "OpMCols", "k_star_forward", "k_fwd_rows"]))
+""").split()
+    assert out == ["OpHCols", "k_spec_fwd", "OpMCols", "k_star_forward", "k_fwd_rows"]
