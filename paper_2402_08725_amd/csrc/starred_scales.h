@@ -11,18 +11,17 @@
 // operator satisfies M^T = E^-1 M E, so v = z_j + H_j^T (v - z_j) is, for E v E and E z_j E,
 // the same mirror filtering; the factors are exact powers of two.
 //
-// J planes are J-1 levels, in groups of up to three (four where that ends the list on subimages
-// of 64 pixels' stride or more): one forward pass per group (the coefficients, their subgradient z
-// and the L1 share leave in the pass that forms them, the smoothed plane goes on to the next group)
-// and one transposed pass per group, last to first. Six passes for J = 8, four for J <= 7 and two
-// for J <= 4, where a launch per level made 2 (J - 1) and composite filters straight from the image
-// cost hundreds of FP64 operations per pixel. Four levels in one pass need 1024 threads and 68 KB
-// per 32 x 32 tile, most of it halo: against two passes of two, loss and gradient of four frames of
-// 512^2 with eight planes 176 us for 162, two images of 257^2 (whose subimages of 33 pixels take
-// four tiles each) 173 for 152, the transform of 2048^2 300 for 201; 512^2 alone 27.4 for 28.3. At
-// strides of 64 and more each pass is bound by its scattered lines, and one is better than two
-// (2048^2 with eleven planes: 479 us for 553). Measured: 512^2 with eight planes, transform and
-// transpose 98 -> 58 us.
+// J planes are J-1 levels, in groups of two and three (one for J = 2): one forward pass per group
+// (the coefficients, their subgradient z and the L1 share leave in the pass that forms them, the
+// smoothed plane goes on to the next group) and one transposed pass per group, last to first: two
+// passes for J <= 4, four for J <= 7, six for J <= 10, where a launch per level made 2 (J - 1) and
+// composite filters straight from the image cost hundreds of FP64 operations per pixel. Larger
+// groups come last, where subimages are small and every pass reads scattered lines; a group of
+// four needs 68 KB and 1024 threads for a tile that is mostly halo, and fills the chip beside an
+// evaluation's kernels. Measured, 3 + 4 levels against 2 + 2 + 3: 512^2 with eight planes, transform
+// and transpose 56 -> 52 us, loss and gradient of four such frames 176 -> 154; two images of 257^2
+// (whose subimages of 33 pixels take four tiles of 32 each) 172 -> 145; and nine planes of 512^2 as
+// 3 + 3 + 2 against 3 + 2 + 3: 98 -> 64.
 //
 // Precision: V is the type of the pixels in a pass and of the planes between the groups.
 // FP64 for one or two images up to 256^2 with at most seven planes (prior and transform),
@@ -31,7 +30,7 @@
 //
 // What bounds a pass: with FP64 tiles of 16 the latency of its loads, barriers and LDS reads
 // (1.9 k to 6.4 k filtered pixels per job, five reads and a write each); with FP32 tiles of
-// 32 the LDS traffic (14 k filtered pixels for three levels, 42 k for four).
+// 32 the LDS traffic (14 k filtered pixels for three levels).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -43,16 +42,14 @@ constexpr int kStarTileLarge = 32;  // FP32 tiles (fewer halo pixels per pixel)
 constexpr int kStarSmall = 256;     // grids up to this side ...
 constexpr int kStarFewPlanes = 7;   // ... with at most this many planes run in FP64
 
-// levels of the group that starts at level l0 with `rest` levels to go
-__host__ __device__ constexpr int star_group_len(int rest, int l0)
-{
-    return rest <= 3 ? rest : (rest == 4 ? (l0 < 6 ? 2 : 4) : 3);
-}
+// levels of the group that starts with `rest` levels to go (two bits each: 1, 2, 3, 2, 2, 3, 2
+// for one to seven, then 3)
+__host__ __device__ constexpr int star_group_len(int rest) { return (0xFFFFBAE4u >> 2 * rest) & 3; }
 
 __host__ __device__ inline int star_num_groups(int J)
 {
     int n = 0;
-    for (int l = 0; l < J - 1; ++n) l += star_group_len(J - 1 - l, l);
+    for (int l = 0; l < J - 1; ++n) l += star_group_len(J - 1 - l);
     return n;
 }
 
@@ -86,10 +83,10 @@ struct StarArgs {
     {
         Group q;
         q.l0 = 0;
-        q.L = star_group_len(J - 1, 0);
+        q.L = star_group_len(J - 1);
         for (; g > 0; --g) {
             q.l0 += q.L;
-            q.L = star_group_len(J - 1 - q.l0, q.l0);
+            q.L = star_group_len(J - 1 - q.l0);
         }
         q.D = 1 << q.l0;
         const int side = (N + q.D - 1) / q.D;
@@ -382,7 +379,7 @@ __device__ __forceinline__ void star_adjoint(const StarArgs &a, int g, int job, 
 }
 
 // One FP64 pass carried by another launch: its work groups first .. first+jobs-1 run the
-// pass's jobs (groups of up to three levels, lds() bytes of dynamic LDS).
+// pass's jobs (lds() bytes of dynamic LDS).
 struct StarPiece {
     StarArgs a;
     int group = -1;  // -1: none

@@ -1,5 +1,6 @@
-"""The starlet passes' groups of levels: 3 + 2 + 2 for eight planes, on grids whose subimages fill
-their tiles badly, eleven planes (3 + 3 + 4, the only group of four), one level on the wide tiles.
+"""The starlet passes' groups of levels: 2 + 2 + 3 for eight planes, on grids whose subimages fill
+their tiles badly, six, nine and eleven planes (2 + 3, 3 + 2 + 3, 3 + 2 + 2 + 3), one level on the wide
+tiles, work groups that run over jobs in order and in turn (above 1024, and short strides).
 
 Bar as in the parity suite: 2e-6 of the largest value."""
 import numpy as np
@@ -13,7 +14,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("N,J", [(129, 8), (257, 8), (300, 8), (700, 8), (257, 2), (700, 2), (1025, 11), (1100, 11)])
+@pytest.mark.parametrize("N,J", [(129, 8), (257, 8), (300, 8), (700, 8), (257, 2), (700, 2), (130, 6), (300, 9), (1025, 11), (1100, 11)])
 def test_transform_and_transpose(N, J):
     from paper_2402_08725_amd import starred as st
     print(f"N {N} J {J}", flush=True)
