@@ -375,7 +375,10 @@ enum {
     STARRED_STAGE_CONV_FWD,     /* S_i and D with the residual and chi-square (Eqs. 8, 10) */
     STARRED_STAGE_CONV_ADJ,     /* S_i^T D^T of the weighted residuals */
     STARRED_STAGE_GRAD_SUMS,    /* per-frame sums for Gamma, a and c */
-    STARRED_STAGE_STARLET,      /* starlet transform, L1 term, subgradient and adjoint (Eq. 6) */
+    STARRED_STAGE_STARLET,      /* starlet transform, L1 term, subgradient and adjoint (Eq. 6);
+                                   empty where its passes are carried by other stages' launches
+                                   (PSF mode up to N = 256 and 7 planes: RENDER, CONV_FWD,
+                                   CONV_ADJ and FINALIZE; deconvolution: see prior_late = 2) */
     STARRED_STAGE_FINALIZE,     /* cross-frame gradient of h and the final reductions */
     STARRED_STAGE_ADAM,         /* optimiser update */
     STARRED_STAGE_SPECTRA,      /* FFT path: spectra shared by all frames */
