@@ -1936,13 +1936,15 @@ static int psf_loss_grad_impl(starred_plan *p, const float *params, float *grad,
         if (grad) pass(piece[3], 0, true);
         n_l1 = star_l1_slots(sa);
     } else {
-        // first: its chain is about as long as the stars' (render, forward, adjoint)
+        // launched first, its chain being about as long as the stars' (render, forward, adjoint), or
+        // after the render where it is the one plane of J = 1 (50 stars of 64^2: 68 us first, 60 so)
         if ((rc = starlet_fork(p))) return rc;
-        if ((rc = starlet_launch(p, params + 5, grad != nullptr, &n_l1))) return rc;
+        if (p->J > 1 && (rc = starlet_launch(p, params + 5, grad != nullptr, &n_l1))) return rc;
     }
     hipEvent_t e0 = p->prof_start();
     HIP_TRY(launch_psf_render64(p->st, N, params, p->d_s64, grad ? p->d_dm : nullptr, tick, &piece[0]));
     p->prof_stop(STARRED_STAGE_RENDER, e0);
+    if (!ride && p->J == 1 && (rc = starlet_launch(p, params + 5, grad != nullptr, &n_l1))) return rc;
     e0 = p->prof_start();
     HIP_TRY(launch_psf_fwd(p->st, S, n, p->s, N, p->sigma, params, p->d_s64, p->data, p->invvar, p->d_rho,
                            p->d_part_chi, nullptr, &piece[1]));

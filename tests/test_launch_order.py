@@ -5,9 +5,9 @@ import fake_hip
 
 
 @pytest.mark.parametrize("n,s,J", [(32, 2, 1), (129, 2, 6), (33, 2, 7)])
-def test_psf_prior_on_its_own_stream_is_launched_first(tmp_path, n, s, J):
-    """PSF mode, the prior's passes not carried by other launches (one plane, or a grid above
-    256; of the last case they are)."""
+def test_psf_prior_on_its_own_stream_is_launched_by_its_length(tmp_path, n, s, J):
+    """PSF mode, the prior's passes not carried by other launches: a chain (a grid above 256) goes
+    first, the one plane of J = 1 after the render. (Of the last case the passes are carried.)"""
     out = fake_hip.run(tmp_path, f"""
 h = make_plan([{n}] * 3, [1] * 3, {s}, {n * s}, 0, {J}, mode=st.PSF)
 assert L.starred_set_frames(h, ptr(f32(3 * {n} ** 2)), ptr(f32(3 * {n} ** 2)), None, ptr(f32({J}))) == st.OK
@@ -19,7 +19,7 @@ print(*launches(["k_star_plane", "k_star_forward", "k_star_adjoint", "k_copy", "
 """).split()
     prior = [k for k in out if k.startswith("k_star") or k == "k_copy"]
     evaluation = ["k_psf_render64", "k_psf_fwd", "k_psf_adjsum", "k_psf_finalize"]
-    assert out == prior + evaluation
+    assert out == (evaluation[:1] + prior + evaluation[1:] if J == 1 else prior + evaluation)
     assert bool(prior) == (J == 1 or n * s > 256)
 
 
