@@ -136,14 +136,18 @@ inline int frame_body_frames(int Q, int s)
     return Q == kFrameLongQ && s == 1 ? 1 : 0;
 }
 
-// sources whose tables a work group holds: the bodies take up to 1, 4 or (a loop) M of them
-__host__ __device__ constexpr int frame_sources(int M) { return M <= 1 ? M : (M <= 4 ? 4 : M); }
+// sources whose tables a work group of transform length Q holds: the bodies take 1, 4 or (a loop) M
+// of them, the one of kFrameLongQ none
+__host__ __device__ constexpr int frame_sources(int M, int Q)
+{
+    return Q == kFrameLongQ && M == 0 ? 0 : (M <= 1 ? 1 : (M <= 4 ? 4 : M));
+}
 
 // bytes of LDS of a work group with `per` frames: their planes of Q/2+1 lines of Q+1
 // values, the Q twiddles and the tables of P values (the window's, two per source)
 inline size_t frame_lds_bytes(int Q, int P, int M, int per)
 {
-    return ((size_t)per * (Q / 2 + 1) * (Q + 1) + Q + (size_t)(1 + 2 * frame_sources(M)) * P) * 8;
+    return ((size_t)per * (Q / 2 + 1) * (Q + 1) + Q + (size_t)(1 + 2 * frame_sources(M, Q)) * P) * 8;
 }
 
 // A work group of the one-launch forward: up to `per` frames of a class.

@@ -54,7 +54,7 @@ __device__ __forceinline__ void frame_body(const FrameItem &f, const FrameArgs &
         // last source (the product below takes MS sources without a test)
         const float2 *tg = g.tab + f.tab_off;
         for (int e = threadIdx.x; e < Q; e += kFusedThreads) twl[e] = g.tw[f.tw_off + e];
-        for (int e = threadIdx.x; e < (1 + 2 * frame_sources(M)) * P; e += kFusedThreads) {
+        for (int e = threadIdx.x; e < (1 + 2 * frame_sources(M, Q)) * P; e += kFusedThreads) {
             const int k2 = e / P;  // 0: w, then gx_0, gy_0, gx_1, ...
             t[e] = e < (1 + 2 * M) * P ? tg[e + (k2 > 0 ? (k2 - 1) / 2 * 2 * P : 0)] : make_float2(0.f, 0.f);
         }
@@ -66,9 +66,10 @@ __device__ __forceinline__ void frame_body(const FrameItem &f, const FrameArgs &
     // ---- the model spectrum: RA bins ky = j + r RB of a column, and their DFT
     if constexpr (MS > 0) {
     constexpr int MR = MS;
-    // (without sources there are no tables for the one that MS = 1 takes with amplitude zero: it
-    // reads the window's)
-    const int tk = M > 0 ? P : 0;
+    // (the body without sources has no tables for the one that MS = 1 takes with amplitude zero: it
+    // reads the window's. Known at compile time: as a value of M it cost every body its constant
+    // LDS offsets, 1000 frames of 32^2 .. 128^2 78.4 -> 80.7 us)
+    constexpr int tk = Q == kFrameLongQ ? 0 : P;
     for (int it = tid; it < HQ * RB; it += NT) {
         const int j = it / HQ, kx = it - j * HQ;
         float2 wxG[S], px[S][MR];
