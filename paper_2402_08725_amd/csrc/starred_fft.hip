@@ -1000,14 +1000,15 @@ __device__ void tables_part(const ClassFft &c, const float2 *__restrict__ tw, co
 // RG-th of them): per row and frame one wide load of S'' and one of rho_hat. The sum over
 // the full spectrum is the sum over all (ky, a, b) and kx in [0, Q/2], with weight 2 off
 // the columns kx = 0 and Q/2. A block takes a chunk of FC frames and a range of rows, SB
-// sources per pass (one when M <= 1; four, or eight with 2-frame chunks and more than four
-// sources, otherwise), folds V with the x-tables and reduces the dot products once per
+// sources per pass (one when M <= 1; else four, eight with 2-frame chunks and more than four
+// sources, sixteen with single frames, there eight at s = 3), folds V with the x-tables and reduces the dot products once per
 // group of SB sources through LDS. Each pass reads the chunk's spectra again, so fewer,
 // wider passes save reads. The per-block partials are summed per frame (and the chunk
 // spectra over chunks) by k_adj_sums. One source, eight frames per chunk: bound by memory (1000
 // frames of 32^2 .. 128^2: 260 MB in 49 us, 5.3 TB/s, what a plain copy reaches; 61 us from half
 // spectra in row order, which took s^2 narrow loads and their index arithmetic per bin); many
-// sources: by the column sums' registers (12 frames of 256^2, 30 sources: 72 us).
+// sources: by the column sums' registers (12 frames of 256^2, 30 sources: 72 us, 58 since they are
+// one alias at a time).
 template <int S, int FC, int SB>
 __global__ __launch_bounds__(kFftThreads, 2) void k_spec_adj(const AdjItem *__restrict__ items,
                                                           const float2 *__restrict__ Sp,
